@@ -1,4 +1,4 @@
-// Piecewise-linear transfer function evaluated on the device (Sec. 3, Transfer Function):
+// Piecewise-linear transfer function in the form the kernels take it (Sec. 3, Transfer Function):
 // RGBA by linear interpolation between ascending control points, constant beyond the end points.
 #pragma once
 
@@ -15,22 +15,6 @@ struct DevTF {
   float rgba[VBM_TF_MAX_POINTS][4];
   int n;
 };
-
-__device__ __forceinline__ float4 tf_eval(const DevTF& tf, float f) {
-  if (!(f > tf.x[0])) return make_float4(tf.rgba[0][0], tf.rgba[0][1], tf.rgba[0][2], tf.rgba[0][3]);
-  const int n = tf.n;
-  if (f >= tf.x[n - 1])
-    return make_float4(tf.rgba[n - 1][0], tf.rgba[n - 1][1], tf.rgba[n - 1][2], tf.rgba[n - 1][3]);
-  int j = 0;
-  for (int i = 1; i < n - 1; ++i)
-    if (tf.x[i] <= f) j = i;
-  const float x0 = tf.x[j], x1 = tf.x[j + 1];
-  const float t = x1 > x0 ? (f - x0) / (x1 - x0) : 1.0f;
-  return make_float4(tf.rgba[j][0] + t * (tf.rgba[j + 1][0] - tf.rgba[j][0]),
-                     tf.rgba[j][1] + t * (tf.rgba[j + 1][1] - tf.rgba[j][1]),
-                     tf.rgba[j][2] + t * (tf.rgba[j + 1][2] - tf.rgba[j][2]),
-                     tf.rgba[j][3] + t * (tf.rgba[j + 1][3] - tf.rgba[j][3]));
-}
 
 inline DevTF make_dev_tf(const vbm_tf& tf) {
   DevTF d;
