@@ -100,15 +100,36 @@ vbm_status scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n_max, 
                               uint32_t* total_dev, void* scratch, hipStream_t s);
 
 // Stable LSD radix sort of (key, value) pairs over key bits [0, end_bit) (end_bit <= 32), digit
-// width 4..8 bits.  Passes ping-pong between (k0, v0) and (k1, v1); returns in *result_in_k1
-// whether the sorted data ends in the second buffer.  The element count is read from *n_dev
-// (<= n_max) when non-null.
+// width 4..8 bits.  ceil(end_bit / width) passes ping-pong between (k0, v0) and (k1, v1), starting in the
+// first.  The element count is read from *n_dev (<= n_max) when non-null.  The caller clears the
+// kMaxRadixTotals words at radix_totals() beforehand; the first kRadixHead bytes of the scratch stay as they are.
+constexpr size_t kRadixHead = 4096;
+constexpr int kMaxRadixTotals = 8 * 256;    // any sort
+constexpr int kMaxDepthTotals = 4 * 256;    // 8-bit digits
 size_t radix_scratch_bytes(int64_t n_max, int digit_bits);
-template <class K>
-vbm_status radix_sort_pairs(K* k0, uint32_t* v0, K* k1, uint32_t* v1, int64_t n_max, const uint32_t* n_dev,
-                            int end_bit, int digit_bits, void* scratch, hipStream_t s, bool* result_in_k1);
+uint32_t* radix_totals(int64_t n_max, int digit_bits, void* scratch);
+vbm_status radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, int64_t n_max,
+                            const uint32_t* n_dev, int end_bit, int digit_bits, void* scratch, hipStream_t s);
+// The same sort of the elements i in [0, n) with keys[i] != 0, each with value i; the first pass writes
+// (k0, v0), the last one (k0, v0) or (k1, v1), in turn; *count_dev receives the number of elements.
+vbm_status radix_sort_sparse(const uint32_t* keys, int64_t n, uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1,
+                             int end_bit, int digit_bits, uint32_t* count_dev, void* scratch, hipStream_t s);
 
 // Device fill (used instead of memset nodes so every step stays capturable).
 vbm_status fill_u32(uint32_t* p, uint32_t value, int64_t n, hipStream_t s);
+
+// Several short runs of 32-bit words cleared by one launch.
+struct ClearList {
+  static constexpr int kMax = 6;
+  uint32_t* p[kMax];
+  int64_t n[kMax];
+  int count = 0;
+  void add(void* q, int64_t words) {
+    p[count] = static_cast<uint32_t*>(q);
+    n[count] = words;
+    ++count;
+  }
+};
+vbm_status clear_words(const ClearList& c, hipStream_t s);
 
 }  // namespace vbm

@@ -1,9 +1,9 @@
 // Host side of the renderer: batch planning, workspace layout and the launch sequence of
 // vbm_render_fwd / vbm_render_bwd.
 //
-// Forward: project every (view, Gaussian) item -> stable compaction of visible items with their
-// float32 depth bits as keys -> radix sort of those 31-bit keys (items in depth order, all views
-// together, item index as the tie-break) -> exclusive scan of tile counts in that order -> emit
+// Forward: project every (view, Gaussian) item -> sparse radix sort of the visible items by their float32
+// depth bits, 31-bit keys (items in depth order, all views
+// together, item index as the tie-break) -> number and emit
 // (tile, item) pairs in depth/item order -> stable radix sort by global tile id alone, which leaves
 // every tile's list (a tile belongs to one view) in (depth, item) order -> tile ranges -> tile
 // launch order, longest lists first -> compositing.  Sorting items by depth once and then pairs by
@@ -21,11 +21,8 @@ namespace vbm {
 
 __global__ void k_project(const DevView*, int, vbm_gaussians_c, float*, uint32_t*, float4*, float4*, float*,
                           uint32_t*, uint4*, unsigned long long*, unsigned long long*, uint32_t);
-__global__ void k_compact_visible(const DevView*, const uint32_t*, const float*, const uint32_t*, uint32_t*,
-                                  uint32_t*);
-__global__ void k_gather_bins(const uint32_t*, const uint4*, const uint32_t*, int64_t, uint32_t*, uint4*);
-__global__ void k_emit(const DevView*, int, const uint32_t*, const uint32_t*, const uint4*,
-                       const float4*, const float4*, const unsigned long long*, int, uint32_t*, int64_t, int64_t,
+__global__ void k_emit(const DevView*, int, const uint32_t*, const uint4*, const float4*, const float4*,
+                       const unsigned long long*, int, uint32_t*, int64_t, int64_t, unsigned long long*, uint32_t*,
                        uint32_t*, uint32_t*);
 __global__ void k_ranges(const uint32_t*, const uint32_t*, int64_t, uint2*);
 __global__ void k_status(const uint32_t*, int32_t*);
@@ -60,17 +57,16 @@ enum Region {
   R_VKEYS_ALT = 11,
   R_VVALS = 12,
   R_VVALS_ALT = 13,
-  R_POFFS = 14,
+  R_ESTATUS = 14,   // uint64 [n_items / 256, rounded up]: the emission's look-back words
   R_PTILE_ALT = 15,
   R_PITEM_ALT = 16,
   R_SCRATCH = 17,
-  R_VISFLAG = 18,
+  R_SORTKEY = 18,   // uint32 [n_items]: depth bits of the visible items, 0 for the others
   R_COEF = VBM_REGION_ITEM_COEF,
   R_UNUSED20 = 20,
   R_TORDER = 21,   // uint32 [4][n_tiles]: sort keys, tiles, and the sorted keys and tiles (the launch order)
   R_WORDS = 22,    // uint64 [ballot_words(n_items)]: large rectangles' reached-tile ballots
-  R_SBIN = 23,     // uint4 [n_items]: the visible items' bin entries in depth order
-  R_COUNT = 24
+  R_COUNT = 23
 };
 static_assert(R_COUNT <= VBM_WS_REGIONS, "plan has room for every region");
 
@@ -104,23 +100,20 @@ void layout(vbm_plan* p) {
   sz[R_VKEYS_ALT] = I * 4;
   sz[R_VVALS] = I * 4;
   sz[R_VVALS_ALT] = I * 4;
-  sz[R_POFFS] = I * 4;
+  sz[R_ESTATUS] = ceil_div(I, 256) * 8;
   sz[R_PTILE_ALT] = P * 4;
   sz[R_PITEM_ALT] = P * 4;
-  size_t scr = scan_scratch_bytes(I);
-  const size_t r1 = radix_scratch_bytes(I, 8);
+  size_t scr = radix_scratch_bytes(I, 8);
   const size_t r2 = radix_scratch_bytes(P, p->sort_bits);
-  if (r1 > scr) scr = r1;
   if (r2 > scr) scr = r2;
   const size_t r3 = radix_scratch_bytes(NT, 8);
   if (r3 > scr) scr = r3;
   sz[R_SCRATCH] = scr;
-  sz[R_VISFLAG] = I * 4;
+  sz[R_SORTKEY] = I * 4;
   sz[R_COEF] = I * 32;
   sz[R_UNUSED20] = 0;
   sz[R_TORDER] = 4 * NT * 4;
   sz[R_WORDS] = 8 * ballot_words(I);
-  sz[R_SBIN] = I * 16;
   size_t off = 0;
   for (int r = 0; r < VBM_WS_REGIONS; ++r) {
     p->region_offset[r] = 0;
@@ -331,44 +324,47 @@ extern "C" vbm_status vbm_render_fwd(const vbm_plan* p, const void* view_table, 
   float4* rec = region<float4>(p, ws, R_REC);
   float4* coef = region<float4>(p, ws, R_COEF);
   float* blue = region<float>(p, ws, R_BLUE);
-  uint32_t* visflag = region<uint32_t>(p, ws, R_VISFLAG);
+  uint32_t* sort_key = region<uint32_t>(p, ws, R_SORTKEY);
   uint32_t* vk[2] = {region<uint32_t>(p, ws, R_VKEYS), region<uint32_t>(p, ws, R_VKEYS_ALT)};
   uint32_t* vv[2] = {region<uint32_t>(p, ws, R_VVALS), region<uint32_t>(p, ws, R_VVALS_ALT)};
-  uint32_t* poffs = region<uint32_t>(p, ws, R_POFFS);
   uint32_t* pt[2] = {region<uint32_t>(p, ws, R_PTILE), region<uint32_t>(p, ws, R_PTILE_ALT)};
   uint32_t* pi[2] = {region<uint32_t>(p, ws, R_PITEM), region<uint32_t>(p, ws, R_PITEM_ALT)};
   uint2* ranges = region<uint2>(p, ws, R_RANGES);
   void* scratch = region<void>(p, ws, R_SCRATCH);
 
-  VBM_TRY(fill_u32(counters, 0u, 16, s));
+  // Everything that starts from zero is cleared by one launch: the counters, the depth sort's digit totals,
+  // the emission's look-back words and the tile ranges.
+  unsigned long long* emit_status = region<unsigned long long>(p, ws, R_ESTATUS);
+  const int64_t emit_blocks = ceil_div(I, 256);
+  constexpr int kDepthKeyBits = 31, kDepthDigit = 8;
+  ClearList clear;
+  clear.add(counters, 16);
+  if (I > 0) clear.add(radix_totals(I, kDepthDigit, scratch), kMaxDepthTotals);
+  clear.add(emit_status, 2 * emit_blocks);
+  clear.add(ranges, 2 * p->n_tiles);
+  VBM_TRY(clear_words(clear, s));
+  const int tile_passes = static_cast<int>(ceil_div(p->tile_key_bits, p->sort_bits));
+  const int pfirst = tile_passes % 2;
   // grid.x covers the largest scene (bounded by the total Gaussian count); grid.y is the view
   const int gx = static_cast<int>(ceil_div(p->n_gaussians > 0 ? p->n_gaussians : 1, 256));
   if (I > 0) {
     hipLaunchKernelGGL(k_project, dim3(gx, p->n_views), dim3(256), 0, s, views, p->tile, g, depth, ntiles, rec,
-                       coef, blue, visflag, region<uint4>(p, ws, R_BIN),
+                       coef, blue, sort_key, region<uint4>(p, ws, R_BIN),
                        reinterpret_cast<unsigned long long*>(counters + 4), region<unsigned long long>(p, ws, R_WORDS),
                        static_cast<uint32_t>(ballot_words(I)));
     VBM_LAUNCH_CHECK("project");
-    VBM_TRY(scan_exclusive_u32(visflag, visflag, I, nullptr, &counters[0], scratch, s));
     // Visible items sorted by depth alone, all views together: a visible item's depth is positive,
-    // so its float32 bits order like the depths and the sign bit is 0 (31 key bits, 4 passes).
-    // Items of different views interleave, but every tile belongs to one view and the stable tile
+    // so its float32 bits order like the depths and the sign bit is 0 (31 key bits, 4 passes; the last
+    // one writes slot 0).  Items of different views interleave, but every tile belongs to one view and the stable tile
     // sort that follows keeps this order inside each tile: (tile, depth, item).
-    constexpr int kDepthKeyBits = 31;
-    const int item_passes = static_cast<int>(ceil_div(kDepthKeyBits, 8));
-    const int first = item_passes % 2;  // compact into the buffer that leaves the sorted data in slot 0
-    hipLaunchKernelGGL(k_compact_visible, dim3(gx, p->n_views), dim3(256), 0, s, views, ntiles, depth, visflag,
-                       vk[first], vv[first]);
-    VBM_LAUNCH_CHECK("compact_visible");
-    bool in_alt = false;
-    VBM_TRY(radix_sort_pairs<uint32_t>(vk[first], vv[first], vk[1 - first], vv[1 - first], I, &counters[0],
-                                       kDepthKeyBits, 8, scratch, s, &in_alt));
-    hipLaunchKernelGGL(k_gather_bins, dim3(grid_cap(I, 8192)), dim3(256), 0, s, vv[0], region<uint4>(p, ws, R_BIN),
-                       counters, I, poffs, region<uint4>(p, ws, R_SBIN));
-    VBM_LAUNCH_CHECK("gather_bins");
-    VBM_TRY(scan_exclusive_u32(poffs, poffs, I, &counters[0], &counters[1], scratch, s));
+    VBM_TRY(radix_sort_sparse(sort_key, I, vk[1], vv[1], vk[0], vv[0], kDepthKeyBits, kDepthDigit, &counters[0],
+                              scratch, s));
+    hipLaunchKernelGGL(k_emit, dim3(emit_blocks), dim3(256), 0, s, views, p->n_views, vv[0],
+                       region<uint4>(p, ws, R_BIN), rec, coef, region<unsigned long long>(p, ws, R_WORDS), p->tile,
+                       counters, I, cap, emit_status, radix_totals(cap, p->sort_bits, scratch), pt[pfirst],
+                       pi[pfirst]);
+    VBM_LAUNCH_CHECK("emit");
   }
-  int64_t emit_grid_n = I;
   int64_t pair_n = cap;
   const uint32_t* pair_n_dev = &counters[1];
   if (p->mode == VBM_MODE_EXACT) {
@@ -377,25 +373,12 @@ extern "C" vbm_status vbm_render_fwd(const vbm_plan* p, const void* view_table, 
     if (e != hipSuccess) return hip_check(e, "vbm_render_fwd: count readback");
     e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_check(e, "vbm_render_fwd: stream sync");
-    emit_grid_n = host_counts[0];
     pair_n = host_counts[1] < cap ? host_counts[1] : cap;
     pair_n_dev = nullptr;
   }
-  const int tile_passes = static_cast<int>(ceil_div(p->tile_key_bits, p->sort_bits));
-  const int pfirst = tile_passes % 2;
-  if (I > 0 && emit_grid_n > 0) {
-    hipLaunchKernelGGL(k_emit, dim3(grid_cap(emit_grid_n, 16384)), dim3(256), 0, s, views, p->n_views, vv[0], poffs,
-                       region<uint4>(p, ws, R_SBIN), rec, coef, region<unsigned long long>(p, ws, R_WORDS), p->tile,
-                       counters, I, cap, pt[pfirst], pi[pfirst]);
-    VBM_LAUNCH_CHECK("emit");
-  }
   if (pair_n > 0) {
-    bool in_alt = false;
-    VBM_TRY(radix_sort_pairs<uint32_t>(pt[pfirst], pi[pfirst], pt[1 - pfirst], pi[1 - pfirst], pair_n, pair_n_dev,
-                                       p->tile_key_bits, p->sort_bits, scratch, s, &in_alt));
-  }
-  VBM_TRY(fill_u32(reinterpret_cast<uint32_t*>(ranges), 0u, 2 * p->n_tiles, s));
-  if (pair_n > 0) {
+    VBM_TRY(radix_sort_pairs(pt[pfirst], pi[pfirst], pt[1 - pfirst], pi[1 - pfirst], pair_n, pair_n_dev,
+                             p->tile_key_bits, p->sort_bits, scratch, s));
     hipLaunchKernelGGL(k_ranges, dim3(grid_cap(pair_n, 16384)), dim3(256), 0, s, pt[0], counters, cap, ranges);
     VBM_LAUNCH_CHECK("ranges");
   }
@@ -405,8 +388,9 @@ extern "C" vbm_status vbm_render_fwd(const vbm_plan* p, const void* view_table, 
     uint32_t* tk = region<uint32_t>(p, ws, R_TORDER);
     hipLaunchKernelGGL(k_tile_keys, dim3(ceil_div(NT, 256)), dim3(256), 0, s, ranges, NT, tk, tk + NT);
     VBM_LAUNCH_CHECK("tile_keys");
-    bool in_alt = false;   // one pass, so the sorted tiles land in the last quarter
-    VBM_TRY(radix_sort_pairs<uint32_t>(tk, tk + NT, tk + 2 * NT, tk + 3 * NT, NT, nullptr, 8, 8, scratch, s, &in_alt));
+    VBM_TRY(fill_u32(radix_totals(NT, 8, scratch), 0u, 256, s));
+    // one pass, so the sorted tiles land in the last quarter
+    VBM_TRY(radix_sort_pairs(tk, tk + NT, tk + 2 * NT, tk + 3 * NT, NT, nullptr, 8, 8, scratch, s));
   }
   VBM_TRY(record(0, s));
   // the sorted pair values stay in pi[0]; the forward's marked copy goes to the idle ping-pong buffer

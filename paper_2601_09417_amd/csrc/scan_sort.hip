@@ -9,6 +9,8 @@
 // runs).
 #include <hip/hip_runtime.h>
 
+#include <utility>
+
 #include "block_scan.h"
 #include "common.h"
 
@@ -156,19 +158,28 @@ __global__ void k_fill_u32(uint32_t* p, uint32_t v, int64_t n) {
   }
 }
 
+__global__ __launch_bounds__(256) void k_clear_words(ClearList c) {
+  const int64_t first = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * 256;
+  for (int k = 0; k < c.count; ++k)
+    for (int64_t i = first; i < c.n[k]; i += stride) c.p[k][i] = 0u;
+}
+
 // ------------------------------------------------------------------ radix sort
 // One-sweep LSD radix sort (after Adinets and Garland's Onesweep, built on Merrill and Garland's
-// decoupled look-back): one histogram kernel counts the digits of every pass in a single read of
-// the keys, a small kernel adds the per-block counts into digit totals, and then every pass is one
-// kernel.  A pass block takes its key tile in acquisition order from a counter, ranks the tile's
-// keys, publishes the tile's digit counts, and finds how many keys of each digit the earlier tiles
+// decoupled look-back): one histogram kernel adds the digit counts of every pass into digit totals in a
+// single read of the keys, and then every pass is one kernel.  A pass block ranks its tile's keys, publishes
+// the tile's digit counts, and finds how many keys of each digit the earlier tiles
 // hold by walking back over their published counts (a tile that has already found its own prefix
 // publishes that, so the walk stops there).  No per-pass histogram or scan launch and no per-tile
 // digit offsets in memory.
+//
+// A sparse sort begins from one key per element, 0 meaning absent: its first pass reads all of them, takes the
+// element's index as the value and moves only the keys that are there, so a compaction before the sort (a
+// scan of the flags and a scattered copy) is not needed; it also writes how many there are.
 constexpr int kUpThreads = 512;       // histogram block
 constexpr int kUpBlocksMax = 256;     // histogram grid: enough loads in flight to stream at the HBM rate
 constexpr int kMaxPasses = 8;         // 32-bit keys with digits of at least 4 bits
-constexpr int kTopThreads = 1024;     // digit-total block: 16 row groups x 64 columns
 constexpr uint32_t kFlagAgg = 1u << 30;   // status word: the tile's own count of the digit
 constexpr uint32_t kFlagInc = 2u << 30;   // status word: the count in this tile and every earlier one
 constexpr uint32_t kCountMask = kFlagAgg - 1u;
@@ -209,22 +220,22 @@ __device__ __forceinline__ void status_store(uint32_t* p, uint32_t v) {
 
 // Keys of digit d in the full tile j of CH keys (the look-back's fallback for a tile whose block has
 // not published its counts).
-template <int CH, class K>
-__device__ uint32_t count_digit(const K* __restrict__ kin, int64_t j, int shift, uint32_t mask, uint32_t d) {
-  const K* src = kin + j * CH;
+template <int CH, bool kSparse>
+__device__ uint32_t count_digit(const uint32_t* __restrict__ kin, int64_t j, int shift, uint32_t mask, uint32_t d) {
+  const uint32_t* src = kin + j * CH;
   uint32_t c = 0;
-  for (int i = 0; i < CH; ++i) c += (static_cast<uint32_t>(src[i] >> shift) & mask) == d ? 1u : 0u;
+  for (int i = 0; i < CH; ++i) c += (!kSparse || src[i] != 0u) && ((src[i] >> shift) & mask) == d ? 1u : 0u;
   return c;
 }
 
 // Digit counts of every pass in one read of the keys.  Block b takes 4096-key chunks b, b + G, ...
-// and writes its counts as row b of part[G][passes * 256]; lane l adds into LDS copy l & 3, so
-// equal digits within a wave (the top digits of clustered keys) contend four ways less.  The block
-// also clears its share of the passes' look-back status words.
-template <class K>
-__global__ __launch_bounds__(kUpThreads) void k_radix_upsweep(const K* __restrict__ keys, int64_t n_max,
+// and adds its counts to tot[passes * 256] (cleared by an earlier kernel; at most 256 additions
+// to an address); lane l adds into LDS copy l & 3, so equal digits within a wave (the top digits of clustered
+// keys) contend four ways less.  The block also clears its share of the passes' look-back status words.
+template <bool kSparse>
+__global__ __launch_bounds__(kUpThreads) void k_radix_upsweep(const uint32_t* __restrict__ keys, int64_t n_max,
                                                               const uint32_t* n_dev, int end_bit, int digit_bits,
-                                                              int passes, uint32_t* __restrict__ part,
+                                                              int passes, uint32_t* __restrict__ tot,
                                                               uint32_t* __restrict__ clear, int64_t clear_n) {
   __shared__ uint32_t s_h[4][kMaxPasses * 256];
   const int R = passes * 256;
@@ -238,26 +249,27 @@ __global__ __launch_bounds__(kUpThreads) void k_radix_upsweep(const K* __restric
   constexpr int kPer = kChunk / kUpThreads;   // 8 keys per thread and chunk
   for (int64_t c = blockIdx.x; c * kChunk < n; c += gridDim.x) {
     const int64_t base = c * kChunk;
-    K k[kPer];
+    uint32_t k[kPer];
     bool ok[kPer];
-    if (sizeof(K) == 4 && base + kChunk <= n && aligned16(keys)) {
+    if (base + kChunk <= n && aligned16(keys)) {
       // two 16-byte loads per thread, consecutive across the block
       const uint4* src = reinterpret_cast<const uint4*>(keys + base);
 #pragma unroll
       for (int r = 0; r < kPer / 4; ++r) {
         const uint4 q = src[r * kUpThreads + threadIdx.x];
-        k[4 * r] = static_cast<K>(q.x);
-        k[4 * r + 1] = static_cast<K>(q.y);
-        k[4 * r + 2] = static_cast<K>(q.z);
-        k[4 * r + 3] = static_cast<K>(q.w);
-        ok[4 * r] = ok[4 * r + 1] = ok[4 * r + 2] = ok[4 * r + 3] = true;
+        k[4 * r] = q.x;
+        k[4 * r + 1] = q.y;
+        k[4 * r + 2] = q.z;
+        k[4 * r + 3] = q.w;
       }
+#pragma unroll
+      for (int r = 0; r < kPer; ++r) ok[r] = !kSparse || k[r] != 0u;
     } else {
 #pragma unroll
       for (int r = 0; r < kPer; ++r) {
         const int64_t i = base + r * kUpThreads + threadIdx.x;
-        ok[r] = i < n;
-        k[r] = ok[r] ? keys[i] : K(0);
+        k[r] = i < n ? keys[i] : 0u;
+        ok[r] = i < n && (!kSparse || k[r] != 0u);
       }
     }
     for (int p = 0; p < passes; ++p) {
@@ -266,31 +278,13 @@ __global__ __launch_bounds__(kUpThreads) void k_radix_upsweep(const K* __restric
       const uint32_t mask = (1u << bits) - 1u;
 #pragma unroll
       for (int r = 0; r < kPer; ++r)
-        if (ok[r]) atomicAdd(&h[p * 256 + (static_cast<uint32_t>(k[r] >> shift) & mask)], 1u);
+        if (ok[r]) atomicAdd(&h[p * 256 + ((k[r] >> shift) & mask)], 1u);
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < R; i += kUpThreads)
-    part[static_cast<int64_t>(blockIdx.x) * R + i] = (s_h[0][i] + s_h[1][i]) + (s_h[2][i] + s_h[3][i]);
-}
-
-// Digit totals: column sums of part[G][R].  Block c sums columns [64 c, 64 c + 64); its 16 row
-// groups take every 16th row, so each thread has at most G / 16 independent loads.
-__global__ __launch_bounds__(kTopThreads) void k_radix_totals(const uint32_t* __restrict__ part, int G, int R,
-                                                             uint32_t* __restrict__ tot) {
-  __shared__ uint32_t s[kTopThreads / 64][64];
-  const int col = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int rg = threadIdx.x >> 6;
-  uint32_t acc = 0;
-  if (col < R)
-    for (int r = rg; r < G; r += kTopThreads / 64) acc += part[static_cast<int64_t>(r) * R + col];
-  s[rg][threadIdx.x & 63] = acc;
-  __syncthreads();
-  if (threadIdx.x < 64 && col < R) {
-    uint32_t t = 0;
-#pragma unroll
-    for (int g = 0; g < kTopThreads / 64; ++g) t += s[g][threadIdx.x];
-    tot[col] = t;
+  for (int i = threadIdx.x; i < R; i += kUpThreads) {
+    const uint32_t c = (s_h[0][i] + s_h[1][i]) + (s_h[2][i] + s_h[3][i]);
+    if (c) atomicAdd(&tot[i], c);
   }
 }
 
@@ -301,17 +295,19 @@ __global__ __launch_bounds__(kTopThreads) void k_radix_totals(const uint32_t* __
 // between.  The per-wave counts give the tile's digit counts (published for the later tiles) and
 // per-wave bases; the look-back gives the keys of each digit in the earlier tiles; the tile is
 // partitioned in LDS and written out in digit order, so consecutive lanes store to consecutive
-// addresses of a digit's output run.
-template <int NT, class K>
-__global__ __launch_bounds__(NT) void k_radix_onesweep(const K* __restrict__ kin, const uint32_t* __restrict__ vin,
-                                                             K* __restrict__ kout, uint32_t* __restrict__ vout,
-                                                             const uint32_t* __restrict__ totals,
-                                                             uint32_t* __restrict__ status, int64_t n_max,
-                                                             const uint32_t* n_dev, int shift, int bits) {
+// addresses of a digit's output run.  kSparse: the first pass of a sparse sort (see above).
+template <int NT, bool kSparse>
+__global__ __launch_bounds__(NT) void k_radix_onesweep(const uint32_t* __restrict__ kin,
+                                                       const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
+                                                       uint32_t* __restrict__ vout,
+                                                       const uint32_t* __restrict__ totals,
+                                                       uint32_t* __restrict__ status, int64_t n_max,
+                                                       const uint32_t* n_dev, int shift, int bits,
+                                                       uint32_t* __restrict__ count_out) {
   constexpr int CH = NT * kItems;          // keys per tile
   constexpr int NW = NT / 64;
   constexpr int kPerWave = CH / NW;
-  __shared__ K s_key[CH];
+  __shared__ uint32_t s_key[CH];
   __shared__ uint32_t s_val[CH];
   __shared__ uint32_t s_cnt[NW][256];       // per-wave digit counts, then per-wave digit bases
   __shared__ uint32_t s_start[256];         // start of each digit in the partitioned tile
@@ -321,25 +317,26 @@ __global__ __launch_bounds__(NT) void k_radix_onesweep(const K* __restrict__ kin
   const int64_t base = tile * CH;
   if (base >= n) return;  // uniform per block; no tile waits on a later one
   for (int x = threadIdx.x; x < NW * 256; x += NT) (&s_cnt[0][0])[x] = 0;
-  const int count = static_cast<int>(min(static_cast<int64_t>(CH), n - base));
+  const int in_tile = static_cast<int>(min(static_cast<int64_t>(CH), n - base));
+  int count = in_tile;   // keys to move
   const int radix = 1 << bits;
   const uint32_t mask = static_cast<uint32_t>(radix - 1);
   const int w = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
-  K keys[kItems];
+  uint32_t keys[kItems];
   uint32_t vals[kItems];
 #pragma unroll
   for (int r = 0; r < kItems; ++r) {
     const int li = w * kPerWave + r * 64 + lane;
-    keys[r] = li < count ? kin[base + li] : K(0);
-    vals[r] = li < count ? vin[base + li] : 0u;
+    keys[r] = li < in_tile ? kin[base + li] : 0u;
+    vals[r] = kSparse ? static_cast<uint32_t>(base + li) : li < in_tile ? vin[base + li] : 0u;
   }
   __syncthreads();
   uint32_t slot[kItems];   // rank among the wave's keys of the same digit
 #pragma unroll
   for (int r = 0; r < kItems; ++r) {
-    const bool valid = w * kPerWave + r * 64 + lane < count;
-    const uint32_t d = static_cast<uint32_t>(keys[r] >> shift) & mask;
+    const bool valid = kSparse ? keys[r] != 0u : w * kPerWave + r * 64 + lane < in_tile;
+    const uint32_t d = (keys[r] >> shift) & mask;
     uint64_t m = __ballot(valid);
     for (int b = 0; b < bits; ++b) {
       const bool bit = (d >> b) & 1u;
@@ -363,6 +360,7 @@ __global__ __launch_bounds__(NT) void k_radix_onesweep(const K* __restrict__ kin
     }
     uint32_t tot;
     uint32_t run = block_excl_scan_n<NT>(t, &tot);
+    if (kSparse) count = static_cast<int>(tot);
     if (dig) {
       s_start[threadIdx.x] = run;
 #pragma unroll
@@ -374,6 +372,7 @@ __global__ __launch_bounds__(NT) void k_radix_onesweep(const K* __restrict__ kin
     // keys of lower digits in the whole input: the exclusive scan of the digit totals
     uint32_t all;
     const uint32_t below = block_excl_scan_n<NT>(has ? totals[threadIdx.x] : 0u, &all);
+    if (kSparse && tile == 0 && threadIdx.x == 0) *count_out = all;
     if (has) {
       uint32_t* mine = status + tile * radix + threadIdx.x;
       uint32_t excl = 0;
@@ -409,7 +408,7 @@ __global__ __launch_bounds__(NT) void k_radix_onesweep(const K* __restrict__ kin
           j -= k;
           if (k < kLookback) {
             if (++rounds > kFallbackRounds) {
-              excl += count_digit<CH>(kin, j, shift, mask, threadIdx.x);   // tile j < tile is full
+              excl += count_digit<CH, kSparse>(kin, j, shift, mask, threadIdx.x);   // tile j < tile is full
               --j;
               rounds = 0;
             } else {
@@ -425,8 +424,8 @@ __global__ __launch_bounds__(NT) void k_radix_onesweep(const K* __restrict__ kin
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < kItems; ++r) {
-    if (w * kPerWave + r * 64 + lane < count) {
-      const uint32_t pos = s_cnt[w][static_cast<uint32_t>(keys[r] >> shift) & mask] + slot[r];
+    if (kSparse ? keys[r] != 0u : w * kPerWave + r * 64 + lane < in_tile) {
+      const uint32_t pos = s_cnt[w][(keys[r] >> shift) & mask] + slot[r];
       s_key[pos] = keys[r];
       s_val[pos] = vals[r];
     }
@@ -437,8 +436,8 @@ __global__ __launch_bounds__(NT) void k_radix_onesweep(const K* __restrict__ kin
   for (int r = 0; r < kItems; ++r) {
     const int lp = r * NT + threadIdx.x;
     if (lp < count) {
-      const K key = s_key[lp];
-      const uint32_t d = static_cast<uint32_t>(key >> shift) & mask;
+      const uint32_t key = s_key[lp];
+      const uint32_t d = (key >> shift) & mask;
       const uint32_t gp = s_glob[d] + (static_cast<uint32_t>(lp) - s_start[d]);
       kout[gp] = key;
       vout[gp] = s_val[lp];
@@ -473,11 +472,6 @@ vbm_status scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n_max, 
   return scan_impl<uint32_t>(in, out, n_max, n_dev, total_dev, scratch, s);
 }
 
-vbm_status scan_exclusive_u64(const uint64_t* in, uint64_t* out, int64_t n_max, const uint32_t* n_dev,
-                              uint64_t* total_dev, void* scratch, hipStream_t s) {
-  return scan_impl<uint64_t>(in, out, n_max, n_dev, total_dev, scratch, s);
-}
-
 vbm_status fill_u32(uint32_t* p, uint32_t value, int64_t n, hipStream_t s) {
   if (n <= 0) return VBM_OK;
   int64_t blocks = ceil_div(ceil_div(n, 4), 256);
@@ -487,9 +481,18 @@ vbm_status fill_u32(uint32_t* p, uint32_t value, int64_t n, hipStream_t s) {
   return VBM_OK;
 }
 
+vbm_status clear_words(const ClearList& c, hipStream_t s) {
+  int64_t most = 1;
+  for (int k = 0; k < c.count; ++k) most = c.n[k] > most ? c.n[k] : most;
+  const int64_t blocks = ceil_div(most, 256 * 4);
+  hipLaunchKernelGGL(k_clear_words, dim3(blocks < 1024 ? blocks : 1024), dim3(256), 0, s, c);
+  VBM_LAUNCH_CHECK("clear_words");
+  return VBM_OK;
+}
+
 namespace {
-// Scratch of one sort: per-block digit counts of the histogram kernel, digit totals, then the
-// look-back status words of every pass, which the histogram kernel clears.
+// Scratch of one sort: a head of kRadixHead bytes that the sort leaves alone (the renderer keeps the tile-order
+// counts there), digit totals, then the look-back status words of every pass, which the histogram kernel clears.
 struct RadixLayout {
   int64_t nb;        // 4096-key tiles (status words are sized for them, twice what a pass uses)
   int passes_max;    // passes of a 32-bit key
@@ -504,11 +507,41 @@ RadixLayout radix_layout(int64_t n_max, int digit_bits) {
   L.passes_max = static_cast<int>(ceil_div(32, digit_bits));
   L.radix = 1 << digit_bits;
   L.G = static_cast<int>(L.nb < kUpBlocksMax ? L.nb : kUpBlocksMax);
-  const size_t part = static_cast<size_t>(L.G) * L.passes_max * 256 * 4;
-  L.off_tot = align_up(part, 256);
+  L.off_tot = kRadixHead;
   L.off_status = align_up(L.off_tot + static_cast<size_t>(L.passes_max) * 256 * 4, 256);
   L.bytes = align_up(L.off_status + static_cast<size_t>(L.passes_max) * L.nb * L.radix * 4, 256);
   return L;
+}
+
+vbm_status check_digits(int end_bit, int digit_bits) {
+  if (digit_bits < 4 || digit_bits > 8) {
+    set_error("radix digit width %d outside 4..8", digit_bits);
+    return VBM_ERR_INVALID;
+  }
+  if (end_bit > 32) {
+    set_error("radix sort over %d key bits (at most 32)", end_bit);
+    return VBM_ERR_INVALID;
+  }
+  return VBM_OK;
+}
+
+// Passes first .. passes - 1 of a sort whose histogram has run, ping-ponging from (k0, v0).
+vbm_status sweep(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, int64_t n_max, const uint32_t* n_dev,
+                 int end_bit, int digit_bits, int first, const RadixLayout& L, char* scratch, hipStream_t s) {
+  uint32_t* tot = reinterpret_cast<uint32_t*>(scratch + L.off_tot);
+  uint32_t* status = reinterpret_cast<uint32_t*>(scratch + L.off_status);
+  const int passes = static_cast<int>(ceil_div(end_bit, digit_bits));
+  for (int p = first; p < passes; ++p) {
+    const int shift = p * digit_bits;
+    const int bits = (end_bit - shift) < digit_bits ? (end_bit - shift) : digit_bits;
+    hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, false>), dim3(ceil_div(n_max, kSweepThreads * kItems)),
+                       dim3(kSweepThreads), 0, s, k0, v0, k1, v1, tot + p * 256, status + p * L.nb * L.radix, n_max,
+                       n_dev, shift, bits, static_cast<uint32_t*>(nullptr));
+    VBM_LAUNCH_CHECK("radix_onesweep");
+    std::swap(k0, k1);
+    std::swap(v0, v1);
+  }
+  return VBM_OK;
 }
 }  // namespace
 
@@ -517,56 +550,42 @@ size_t radix_scratch_bytes(int64_t n_max, int digit_bits) {
   return radix_layout(n_max, digit_bits).bytes;
 }
 
-template <class K>
-vbm_status radix_sort_pairs(K* k0, uint32_t* v0, K* k1, uint32_t* v1, int64_t n_max, const uint32_t* n_dev,
-                            int end_bit, int digit_bits, void* scratch, hipStream_t s, bool* result_in_k1) {
-  *result_in_k1 = false;
-  if (n_max <= 0 || end_bit <= 0) return VBM_OK;
-  if (digit_bits < 4 || digit_bits > 8) {
-    set_error("radix digit width %d outside 4..8", digit_bits);
-    return VBM_ERR_INVALID;
-  }
-  if (end_bit > 32 || end_bit > static_cast<int>(8 * sizeof(K))) {
-    set_error("radix sort over %d key bits (at most 32)", end_bit);
-    return VBM_ERR_INVALID;
-  }
-  const RadixLayout L = radix_layout(n_max, digit_bits);
-  const int passes = static_cast<int>(ceil_div(end_bit, digit_bits));
-  char* base = static_cast<char*>(scratch);
-  uint32_t* part = reinterpret_cast<uint32_t*>(base);
-  uint32_t* tot = reinterpret_cast<uint32_t*>(base + L.off_tot);
-  uint32_t* status = reinterpret_cast<uint32_t*>(base + L.off_status);
-  const int64_t pass_words = L.nb * L.radix;
-  const int64_t clear_n = static_cast<int64_t>(passes) * pass_words;
-  hipLaunchKernelGGL(k_radix_upsweep<K>, dim3(L.G), dim3(kUpThreads), 0, s, k0, n_max, n_dev, end_bit, digit_bits,
-                     passes, part, status, clear_n);
-  VBM_LAUNCH_CHECK("radix_upsweep");
-  const int R = passes * 256;
-  hipLaunchKernelGGL(k_radix_totals, dim3(ceil_div(R, 64)), dim3(kTopThreads), 0, s, part, L.G, R, tot);
-  VBM_LAUNCH_CHECK("radix_totals");
-  K* kin = k0;
-  uint32_t* vin = v0;
-  K* kout = k1;
-  uint32_t* vout = v1;
-  for (int p = 0; p < passes; ++p) {
-    const int shift = p * digit_bits;
-    const int bits = (end_bit - shift) < digit_bits ? (end_bit - shift) : digit_bits;
-    hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, K>), dim3(ceil_div(n_max, kSweepThreads * kItems)),
-                       dim3(kSweepThreads), 0, s, kin, vin, kout, vout, tot + p * 256, status + p * pass_words, n_max,
-                       n_dev, shift, bits);
-    VBM_LAUNCH_CHECK("radix_onesweep");
-    K* tk = kin;
-    kin = kout;
-    kout = tk;
-    uint32_t* tv = vin;
-    vin = vout;
-    vout = tv;
-    *result_in_k1 = !*result_in_k1;
-  }
-  return VBM_OK;
+uint32_t* radix_totals(int64_t n_max, int digit_bits, void* scratch) {
+  return reinterpret_cast<uint32_t*>(static_cast<char*>(scratch) + radix_layout(n_max, digit_bits).off_tot);
 }
 
-template vbm_status radix_sort_pairs<uint32_t>(uint32_t*, uint32_t*, uint32_t*, uint32_t*, int64_t, const uint32_t*,
-                                               int, int, void*, hipStream_t, bool*);
+vbm_status radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, int64_t n_max,
+                            const uint32_t* n_dev, int end_bit, int digit_bits, void* scratch, hipStream_t s) {
+  if (n_max <= 0 || end_bit <= 0) return VBM_OK;
+  VBM_TRY(check_digits(end_bit, digit_bits));
+  const RadixLayout L = radix_layout(n_max, digit_bits);
+  char* base = static_cast<char*>(scratch);
+  const int passes = static_cast<int>(ceil_div(end_bit, digit_bits));
+  hipLaunchKernelGGL(k_radix_upsweep<false>, dim3(L.G), dim3(kUpThreads), 0, s, k0, n_max, n_dev, end_bit, digit_bits,
+                     passes, reinterpret_cast<uint32_t*>(base + L.off_tot),
+                     reinterpret_cast<uint32_t*>(base + L.off_status), static_cast<int64_t>(passes) * L.nb * L.radix);
+  VBM_LAUNCH_CHECK("radix_upsweep");
+  return sweep(k0, v0, k1, v1, n_max, n_dev, end_bit, digit_bits, 0, L, base, s);
+}
+
+vbm_status radix_sort_sparse(const uint32_t* keys, int64_t n, uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1,
+                             int end_bit, int digit_bits, uint32_t* count_dev, void* scratch, hipStream_t s) {
+  if (n <= 0 || end_bit <= 0) return VBM_OK;
+  VBM_TRY(check_digits(end_bit, digit_bits));
+  const RadixLayout L = radix_layout(n, digit_bits);
+  char* base = static_cast<char*>(scratch);
+  uint32_t* tot = reinterpret_cast<uint32_t*>(base + L.off_tot);
+  uint32_t* status = reinterpret_cast<uint32_t*>(base + L.off_status);
+  const int passes = static_cast<int>(ceil_div(end_bit, digit_bits));
+  hipLaunchKernelGGL(k_radix_upsweep<true>, dim3(L.G), dim3(kUpThreads), 0, s, keys, n,
+                     static_cast<const uint32_t*>(nullptr), end_bit, digit_bits, passes, tot, status,
+                     static_cast<int64_t>(passes) * L.nb * L.radix);
+  VBM_LAUNCH_CHECK("radix_upsweep");
+  hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, true>), dim3(ceil_div(n, kSweepThreads * kItems)),
+                     dim3(kSweepThreads), 0, s, keys, static_cast<const uint32_t*>(nullptr), k0, v0, tot, status, n,
+                     static_cast<const uint32_t*>(nullptr), 0, end_bit < digit_bits ? end_bit : digit_bits, count_dev);
+  VBM_LAUNCH_CHECK("radix_onesweep");
+  return sweep(k0, v0, k1, v1, n, count_dev, end_bit, digit_bits, 1, L, base, s);
+}
 
 }  // namespace vbm

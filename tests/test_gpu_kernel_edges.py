@@ -5,9 +5,10 @@ import pytest
 import torch
 
 import vbm_inputs as vi
+from oracle import binning
 from oracle import dwt as odwt
 from oracle import tf as otf
-from tests.gpu_common import dev, say
+from tests.gpu_common import ITEM_MASK, dev, say, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -47,3 +48,34 @@ def test_dwt_tile_edges(G, J, wav, with_tf, offset):
         scale = max(np.abs(ref[:, blk]).max(), 1e-6)
         err = np.abs(got[:, blk] - ref[:, blk]).max() / scale
         assert err <= tol, ((j, o), err)
+
+
+# Item counts around the emission's 256-item blocks and the sorts' 4096- and 8192-key tiles; opacities with holes
+# in the depth keys, none visible at all (0), footprints on either side of the 32-tile rule.
+@pytest.mark.parametrize("n,tile,bits,opacity,log_scale", [
+    (1, 16, 8, (0.5, 0.9), -3.0), (255, 16, 8, (0.5, 0.9), -3.0), (256, 8, 8, (0.5, 0.9), -2.0),
+    (257, 16, 4, (0.5, 0.9), -1.6), (300, 16, 8, (0.001, 0.003), -3.0), (4097, 16, 8, (0.001, 0.007), -3.5),
+    (8192, 32, 8, (0.5, 0.9), -4.0), (8193, 16, 8, (0.001, 0.007), -3.5), (16500, 8, 5, (0.001, 0.02), -3.8)])
+def test_pair_lists_at_block_edges(n, tile, bits, opacity, log_scale):
+    api = _api()
+    say(f"pair lists n={n} tile={tile} digits={bits} opacity {opacity} log scale {log_scale}")
+    gs = vi.random_gaussians(n, 31 + n, log_scale_mean=log_scale, opacity_range=opacity)
+    cams = vi.orbit_cameras(2, 131, 77, azimuth0=0.2)
+    ref = binning.pair_lists(gs, cams, tile)
+    total = ref["tile"].size
+    rp = api.plan_batch(cams, [0, n], tile=tile, sort_bits=bits, pair_capacity=max(total, 1))
+    for _ in range(2):      # the second pass finds the first one's counters, totals and look-back words
+        out = api.render_fwd(rp, to_dev(gs))
+    torch.cuda.synchronize()
+    assert out.status[:2].tolist() == [0, total]
+    assert int(out.status[2]) == sum(int((p["n_tiles"] > 0).sum()) for p in ref["proj"])
+    assert np.array_equal(rp.region("pair_tile", torch.int32).cpu().numpy()[:total], ref["tile"])
+    assert np.array_equal(rp.region("pair_item", torch.int32).cpu().numpy()[:total] & ITEM_MASK, ref["item"])
+    ranges = rp.region("ranges", torch.int32).cpu().numpy().reshape(-1, 2)
+    full = ref["ranges"][:, 1] > ref["ranges"][:, 0]
+    assert np.array_equal(ranges[full], ref["ranges"][full])
+    assert np.all(ranges[~full, 0] == ranges[~full, 1])
+    if total > 1:           # one slot short: flagged, and the pairs that fit are the depth order's first
+        rp = api.plan_batch(cams, [0, n], tile=tile, sort_bits=bits, pair_capacity=total - 1)
+        out = api.render_fwd(rp, to_dev(gs))
+        assert out.status.tolist()[:2] == [1, total]
