@@ -99,21 +99,39 @@ size_t scan_scratch_bytes(int64_t n_max);
 vbm_status scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n_max, const uint32_t* n_dev,
                               uint32_t* total_dev, void* scratch, hipStream_t s);
 
-// Stable LSD radix sort of (key, value) pairs over key bits [0, end_bit) (end_bit <= 32), digit
-// width 4..8 bits.  ceil(end_bit / width) passes ping-pong between (k0, v0) and (k1, v1), starting in the
-// first.  The element count is read from *n_dev (<= n_max) when non-null.  The caller clears the
-// kMaxRadixTotals words at radix_totals() beforehand; the first kRadixHead bytes of the scratch stay as they are.
+// Stable LSD radix sorts of (key, value) pairs over key bits [0, end_bit) (end_bit <= 32), digit
+// width 4..8 bits.  The caller clears the kMaxRadixTotals words at radix_totals() beforehand.  The first
+// kRadixHead bytes of the scratch are not the sorts': tile_order_counts() lies there.
 constexpr size_t kRadixHead = 4096;
 constexpr int kMaxRadixTotals = 8 * 256;    // any sort
 constexpr int kMaxDepthTotals = 4 * 256;    // 8-bit digits
+constexpr int64_t kBlockSort = 16384;       // elements that one block sorts in LDS
 size_t radix_scratch_bytes(int64_t n_max, int digit_bits);
 uint32_t* radix_totals(int64_t n_max, int digit_bits, void* scratch);
-vbm_status radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, int64_t n_max,
-                            const uint32_t* n_dev, int end_bit, int digit_bits, void* scratch, hipStream_t s);
-// The same sort of the elements i in [0, n) with keys[i] != 0, each with value i; the first pass writes
-// (k0, v0), the last one (k0, v0) or (k1, v1), in turn; *count_dev receives the number of elements.
+// The elements i in [0, n) with keys[i] != 0, each with value i; ceil(end_bit / width) passes write (k0, v0) and
+// (k1, v1) in turn, so the sorted data ends in the first for an odd number of passes; *count_dev
+// receives the number of elements.
 vbm_status radix_sort_sparse(const uint32_t* keys, int64_t n, uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1,
                              int end_bit, int digit_bits, uint32_t* count_dev, void* scratch, hipStream_t s);
+
+// The tiles' lists after the pair sort.
+struct TileLists {
+  uint2* ranges;             // [n_tiles]: [start, end) of each tile's list
+  int64_t n_tiles;
+  uint32_t* order;           // [n_tiles]: tiles in launch order, the longest lists first (in steps of 8 entries, stable)
+  uint32_t* keys;            // [2][n_tiles]: the order's sort keys
+  const uint32_t* counters;  // of the forward
+  int32_t* status;           // the caller's
+};
+// Sorts the pairs in (k[first], v[first]) by tile into (k[0], v[0]) (first as sort_pairs_first says; the count is
+// read from *n_dev when non-null, and is at most n_max), and writes the tiles' ranges (cleared beforehand),
+// launch order and the status (scratch: radix_scratch_bytes of n_max and of the tiles).  The kTileOrderCounts words at tile_order_counts() are cleared beforehand.
+constexpr int kTileOrderCounts = 2 * 256;
+inline uint32_t* tile_order_counts(void* scratch) { return static_cast<uint32_t*>(scratch); }
+int sort_pairs_first(int64_t n_max, int64_t n_tiles, int end_bit, int digit_bits);
+vbm_status sort_pairs_by_tile(uint32_t* const k[2], uint32_t* const v[2], int first, int64_t capacity, int64_t n_max,
+                              const uint32_t* n_dev, int end_bit, int digit_bits, const TileLists& lists,
+                              void* scratch, hipStream_t s);
 
 // Device fill (used instead of memset nodes so every step stays capturable).
 vbm_status fill_u32(uint32_t* p, uint32_t value, int64_t n, hipStream_t s);

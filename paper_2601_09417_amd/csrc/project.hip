@@ -590,38 +590,6 @@ __global__ __launch_bounds__(256) void k_emit(const DevView* __restrict__ views,
   }
 }
 
-__global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ pair_tile,
-                                                const uint32_t* __restrict__ counters, int64_t capacity,
-                                                uint2* __restrict__ ranges) {
-  const int64_t P = min(static_cast<int64_t>(counters[1]), capacity);
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < P;
-       i += static_cast<int64_t>(gridDim.x) * 256) {
-    const uint32_t t = pair_tile[i];
-    if (i == 0 || pair_tile[i - 1] != t) ranges[t].x = static_cast<uint32_t>(i);
-    if (i == P - 1 || pair_tile[i + 1] != t) ranges[t].y = static_cast<uint32_t>(i + 1);
-  }
-}
-
-// Sort keys that put the tiles with the longest lists first (one key step per 8 list entries,
-// lists of 2040 or more share the first key); the values are the tile indices.
-__global__ __launch_bounds__(256) void k_tile_keys(const uint2* __restrict__ ranges, int64_t n_tiles,
-                                                   uint32_t* __restrict__ keys, uint32_t* __restrict__ tiles) {
-  const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (t >= n_tiles) return;
-  const uint2 r = ranges[t];
-  keys[t] = 255u - min(255u, (r.y - r.x) >> 3);
-  tiles[t] = static_cast<uint32_t>(t);
-}
-
-__global__ void k_status(const uint32_t* __restrict__ counters, int32_t* __restrict__ status) {
-  if (threadIdx.x == 0) {
-    status[0] = static_cast<int32_t>(counters[2]);
-    status[1] = static_cast<int32_t>(counters[1]);
-    status[2] = static_cast<int32_t>(counters[0]);
-    status[3] += counters[2] ? 1 : 0;
-  }
-}
-
 // ------------------------------------------------------------------ projection backward
 // Chain rule from the per-item 2D gradients (mean2d, conic, opacity, rgb) to the activated 3D
 // parameters, summed over the views that show the Gaussian's scene (deterministic: one thread per

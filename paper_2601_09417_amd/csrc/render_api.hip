@@ -24,9 +24,6 @@ __global__ void k_project(const DevView*, int, vbm_gaussians_c, float*, uint32_t
 __global__ void k_emit(const DevView*, int, const uint32_t*, const uint4*, const float4*, const float4*,
                        const unsigned long long*, int, uint32_t*, int64_t, int64_t, unsigned long long*, uint32_t*,
                        uint32_t*, uint32_t*);
-__global__ void k_ranges(const uint32_t*, const uint32_t*, int64_t, uint2*);
-__global__ void k_status(const uint32_t*, int32_t*);
-__global__ void k_tile_keys(const uint2*, int64_t, uint32_t*, uint32_t*);
 __global__ void k_project_bwd(const DevView*, int, const DevScene*, int, vbm_gaussians_c, float*, const float4*,
                               int64_t, const uint32_t*, vbm_gaussians, int, int64_t);
 vbm_status launch_composite_fwd(int tile, int lds_batch, const DevView* views, int n_views, int64_t n_tiles,
@@ -64,7 +61,7 @@ enum Region {
   R_SORTKEY = 18,   // uint32 [n_items]: depth bits of the visible items, 0 for the others
   R_COEF = VBM_REGION_ITEM_COEF,
   R_UNUSED20 = 20,
-  R_TORDER = 21,   // uint32 [4][n_tiles]: sort keys, tiles, and the sorted keys and tiles (the launch order)
+  R_TORDER = 21,   // uint32 [4][n_tiles]: sort keys, sorted keys, (unused), the tiles in launch order
   R_WORDS = 22,    // uint64 [ballot_words(n_items)]: large rectangles' reached-tile ballots
   R_COUNT = 23
 };
@@ -133,8 +130,8 @@ T* region(const vbm_plan* p, void* ws, int r) {
   return reinterpret_cast<T*>(static_cast<char*>(ws) + p->region_offset[r]);
 }
 
-// Launch order of the tiles for compositing (written by the forward): the sorted-tiles quarter of
-// the order region.
+// Launch order of the tiles for compositing (written by the forward): the last quarter of the order
+// region.
 uint32_t* tile_order(const vbm_plan* p, void* ws) { return region<uint32_t>(p, ws, R_TORDER) + 3 * p->n_tiles; }
 
 vbm_status check_gaussians(const vbm_gaussians_c& g, const vbm_plan* p, const char* who) {
@@ -342,9 +339,9 @@ extern "C" vbm_status vbm_render_fwd(const vbm_plan* p, const void* view_table, 
   if (I > 0) clear.add(radix_totals(I, kDepthDigit, scratch), kMaxDepthTotals);
   clear.add(emit_status, 2 * emit_blocks);
   clear.add(ranges, 2 * p->n_tiles);
+  clear.add(tile_order_counts(scratch), kTileOrderCounts);
   VBM_TRY(clear_words(clear, s));
-  const int tile_passes = static_cast<int>(ceil_div(p->tile_key_bits, p->sort_bits));
-  const int pfirst = tile_passes % 2;
+  const int pfirst = sort_pairs_first(cap, p->n_tiles, p->tile_key_bits, p->sort_bits);
   // grid.x covers the largest scene (bounded by the total Gaussian count); grid.y is the view
   const int gx = static_cast<int>(ceil_div(p->n_gaussians > 0 ? p->n_gaussians : 1, 256));
   if (I > 0) {
@@ -376,30 +373,21 @@ extern "C" vbm_status vbm_render_fwd(const vbm_plan* p, const void* view_table, 
     pair_n = host_counts[1] < cap ? host_counts[1] : cap;
     pair_n_dev = nullptr;
   }
-  if (pair_n > 0) {
-    VBM_TRY(radix_sort_pairs(pt[pfirst], pi[pfirst], pt[1 - pfirst], pi[1 - pfirst], pair_n, pair_n_dev,
-                             p->tile_key_bits, p->sort_bits, scratch, s));
-    hipLaunchKernelGGL(k_ranges, dim3(grid_cap(pair_n, 16384)), dim3(256), 0, s, pt[0], counters, cap, ranges);
-    VBM_LAUNCH_CHECK("ranges");
-  }
-  if (p->n_tiles > 0) {
-    // Longest lists first: one stable 8-bit pass over coarse length keys.
-    const int64_t NT = p->n_tiles;
-    uint32_t* tk = region<uint32_t>(p, ws, R_TORDER);
-    hipLaunchKernelGGL(k_tile_keys, dim3(ceil_div(NT, 256)), dim3(256), 0, s, ranges, NT, tk, tk + NT);
-    VBM_LAUNCH_CHECK("tile_keys");
-    VBM_TRY(fill_u32(radix_totals(NT, 8, scratch), 0u, 256, s));
-    // one pass, so the sorted tiles land in the last quarter
-    VBM_TRY(radix_sort_pairs(tk, tk + NT, tk + 2 * NT, tk + 3 * NT, NT, nullptr, 8, 8, scratch, s));
-  }
+  TileLists lists;
+  lists.ranges = ranges;
+  lists.n_tiles = p->n_tiles;
+  lists.order = tile_order(p, ws);
+  lists.keys = region<uint32_t>(p, ws, R_TORDER);
+  lists.counters = counters;
+  lists.status = status;
+  VBM_TRY(sort_pairs_by_tile(pt, pi, pfirst, cap, pair_n, pair_n_dev, p->tile_key_bits, p->sort_bits, lists, scratch,
+                             s));
   VBM_TRY(record(0, s));
   // the sorted pair values stay in pi[0]; the forward's marked copy goes to the idle ping-pong buffer
   VBM_TRY(launch_composite_fwd(p->tile, p->lds_batch, views, p->n_views, p->n_tiles, ranges, tile_order(p, ws), pi[0],
                                cap, pi[1],
                                reinterpret_cast<const float*>(coef), blue, I, image, final_T, n_contrib, g_stats, s));
   VBM_TRY(record(1, s));
-  hipLaunchKernelGGL(k_status, dim3(1), dim3(64), 0, s, counters, status);
-  VBM_LAUNCH_CHECK("status");
   return VBM_OK;
 }
 

@@ -296,14 +296,17 @@ __global__ __launch_bounds__(kUpThreads) void k_radix_upsweep(const uint32_t* __
 // per-wave bases; the look-back gives the keys of each digit in the earlier tiles; the tile is
 // partitioned in LDS and written out in digit order, so consecutive lanes store to consecutive
 // addresses of a digit's output run.  kSparse: the first pass of a sparse sort (see above).
-template <int NT, bool kSparse>
+// kRanges: the last pass of the pair sort.  Its input is in order of the lower digits, so the partitioned
+// tile is in order of the whole key and equal keys are neighbours; their first and last places go
+// to ranges[key] as (~first, last + 1), both by maximum from 0, since a key's run can span tiles.
+template <int NT, bool kSparse, bool kRanges>
 __global__ __launch_bounds__(NT) void k_radix_onesweep(const uint32_t* __restrict__ kin,
                                                        const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
                                                        uint32_t* __restrict__ vout,
                                                        const uint32_t* __restrict__ totals,
                                                        uint32_t* __restrict__ status, int64_t n_max,
                                                        const uint32_t* n_dev, int shift, int bits,
-                                                       uint32_t* __restrict__ count_out) {
+                                                       uint32_t* __restrict__ count_out, uint2* __restrict__ ranges) {
   constexpr int CH = NT * kItems;          // keys per tile
   constexpr int NW = NT / 64;
   constexpr int kPerWave = CH / NW;
@@ -441,8 +444,191 @@ __global__ __launch_bounds__(NT) void k_radix_onesweep(const uint32_t* __restric
       const uint32_t gp = s_glob[d] + (static_cast<uint32_t>(lp) - s_start[d]);
       kout[gp] = key;
       vout[gp] = s_val[lp];
+      if (kRanges) {
+        if (lp == 0 || s_key[lp - 1] != key) atomicMax(&ranges[key].x, ~gp);
+        if (lp + 1 == count || s_key[lp + 1] != key) atomicMax(&ranges[key].y, gp + 1u);
+      }
     }
   }
+}
+
+// ------------------------------------------------------------------ one-block sort
+// Up to kBlockSort elements are sorted by one block in LDS, all passes in one launch: at these sizes a pass of the
+// one-sweep sort is its launch and the latency of one tile (about 10 us), however few keys there are.
+// 2,048 items and 2,079 pairs (64 tiles): sorts, ranges and tile order 75 us in 13 launches before, 33 us in two
+// now; 5,000 items and 7,749 pairs: 85 and 46 us.  The bound is what LDS holds (two words per element
+// and the per-wave counters, 144 KB); at it the passes take about as long as the larger sort's launches.
+constexpr int kBlockSortThreads = 1024;
+constexpr int kBlockSortItems = static_cast<int>(kBlockSort / kBlockSortThreads);
+constexpr int kBlockSortWaves = kBlockSortThreads / 64;
+
+// Coarse length key of a tile's list: the longest first, one step per 8 entries, lists of 2040 or more share
+// the first.
+__device__ __forceinline__ uint32_t length_key(uint2 r) { return 255u - min(255u, (r.y - r.x) >> 3); }
+
+__device__ __forceinline__ void write_status(const uint32_t* __restrict__ counters, int32_t* __restrict__ status) {
+  status[0] = static_cast<int32_t>(counters[2]);
+  status[1] = static_cast<int32_t>(counters[1]);
+  status[2] = static_cast<int32_t>(counters[0]);
+  status[3] += counters[2] ? 1 : 0;
+}
+
+// Stable places of a block's elements by an 8-bit digit.  Element r of a lane is (wave * rounds + r) * 64 + lane;
+// digit 256 or more: not there.  Afterwards slot[r] is its place, and the number of elements is returned.
+__device__ __forceinline__ uint32_t block_places(const uint32_t (&digit)[kBlockSortItems], int rounds,
+                                                 uint32_t (*__restrict__ s_cnt)[256],
+                                                 uint32_t (&slot)[kBlockSortItems]) {
+  const int w = threadIdx.x >> 6;
+  for (int x = threadIdx.x; x < kBlockSortWaves * 256; x += kBlockSortThreads) (&s_cnt[0][0])[x] = 0u;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kBlockSortItems; ++r) {
+    if (r >= rounds) break;
+    const uint32_t d = digit[r];
+    const bool valid = d < 256u;
+    uint64_t m = __ballot(valid);
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+      const bool bit = (d >> b) & 1u;
+      const uint64_t bb = __ballot(bit);
+      m &= bit ? bb : ~bb;
+    }
+    const uint32_t rank = popc_below(m);
+    const uint32_t before = s_cnt[w][d & 255u];
+    if (valid && rank == 0) s_cnt[w][d] = before + static_cast<uint32_t>(__popcll(m));
+    slot[r] = before + rank;
+  }
+  __syncthreads();
+  uint32_t c[kBlockSortWaves], t = 0;
+#pragma unroll
+  for (int ww = 0; ww < kBlockSortWaves; ++ww) {
+    c[ww] = threadIdx.x < 256 ? s_cnt[ww][threadIdx.x] : 0u;
+    t += c[ww];
+  }
+  uint32_t total;
+  uint32_t run = block_excl_scan_n<kBlockSortThreads>(t, &total);
+  if (threadIdx.x < 256) {
+#pragma unroll
+    for (int ww = 0; ww < kBlockSortWaves; ++ww) {
+      s_cnt[ww][threadIdx.x] = run;
+      run += c[ww];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kBlockSortItems; ++r) {
+    if (r >= rounds) break;
+    slot[r] += s_cnt[w][digit[r] & 255u];
+  }
+  return total;
+}
+
+// kSparse: the depth sort (see radix_sort_sparse).  kPairs: the pair sort with what follows it, the
+// tiles' ranges (cleared beforehand), launch order and the caller's status.  The output may be the input.
+template <bool kSparse, bool kPairs>
+__global__ __launch_bounds__(kBlockSortThreads) void k_sort_block(const uint32_t* kin, const uint32_t* vin,
+                                                                  uint32_t* kout, uint32_t* vout, int64_t n_max,
+                                                                  const uint32_t* n_dev, int end_bit,
+                                                                  uint32_t* __restrict__ count_out, TileLists lists) {
+  __shared__ uint32_t s_key[kBlockSort];
+  __shared__ uint32_t s_val[kBlockSort];
+  __shared__ uint32_t s_cnt[kBlockSortWaves][256];   // per-wave digit counts, then per-wave digit bases
+  int n = static_cast<int>(active_count(n_max, n_dev));
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  uint32_t keys[kBlockSortItems], vals[kBlockSortItems], digit[kBlockSortItems], slot[kBlockSortItems];
+  int rounds = (n + kBlockSortThreads - 1) / kBlockSortThreads;   // wave w owns elements [64 rounds w, 64 rounds (w + 1))
+#pragma unroll
+  for (int r = 0; r < kBlockSortItems; ++r) {
+    const int i = (w * rounds + r) * 64 + lane;
+    const bool in = r < rounds && i < n;
+    keys[r] = in ? kin[i] : 0u;
+    vals[r] = kSparse ? static_cast<uint32_t>(i) : in ? vin[i] : 0u;
+  }
+  for (int shift = 0; shift < end_bit; shift += 8) {
+    const uint32_t mask = (1u << min(8, end_bit - shift)) - 1u;
+#pragma unroll
+    for (int r = 0; r < kBlockSortItems; ++r) {
+      const bool valid = (w * rounds + r) * 64 + lane < n && (!kSparse || keys[r] != 0u);
+      digit[r] = valid ? (keys[r] >> shift) & mask : 256u;
+    }
+    const int total = static_cast<int>(block_places(digit, rounds, s_cnt, slot));
+#pragma unroll
+    for (int r = 0; r < kBlockSortItems; ++r) {
+      if (r >= rounds) break;
+      if (digit[r] < 256u) {
+        s_key[slot[r]] = keys[r];
+        s_val[slot[r]] = vals[r];
+      }
+    }
+    __syncthreads();
+    n = total;   // (a sparse sort's first pass leaves the absent ones behind)
+    rounds = (n + kBlockSortThreads - 1) / kBlockSortThreads;
+#pragma unroll
+    for (int r = 0; r < kBlockSortItems; ++r) {
+      if (r >= rounds) break;
+      const int i = (w * rounds + r) * 64 + lane;
+      keys[r] = i < n ? s_key[i] : 0u;
+      vals[r] = i < n ? s_val[i] : 0u;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < kBlockSortItems; ++r) {
+    if (r >= rounds) break;
+    const int i = (w * rounds + r) * 64 + lane;
+    if (i >= n) continue;
+    kout[i] = keys[r];
+    vout[i] = vals[r];
+    if (kPairs) {   // (a batch of one tile has no digits and one run)
+      const uint32_t tile = keys[r];
+      if (i == 0 || (end_bit != 0 && s_key[i - 1] != tile)) lists.ranges[tile].x = static_cast<uint32_t>(i);
+      if (i + 1 == n || (end_bit != 0 && s_key[i + 1] != tile)) lists.ranges[tile].y = static_cast<uint32_t>(i + 1);
+    }
+  }
+  if (kSparse && threadIdx.x == 0) *count_out = static_cast<uint32_t>(n);
+  if (kPairs) {
+    __threadfence();
+    __syncthreads();
+    const int tiles = static_cast<int>(lists.n_tiles);
+    rounds = (tiles + kBlockSortThreads - 1) / kBlockSortThreads;
+#pragma unroll
+    for (int r = 0; r < kBlockSortItems; ++r) {
+      const int i = (w * rounds + r) * 64 + lane;
+      digit[r] = r < rounds && i < tiles ? length_key(lists.ranges[i]) : 256u;
+    }
+    block_places(digit, rounds, s_cnt, slot);
+#pragma unroll
+    for (int r = 0; r < kBlockSortItems; ++r)
+      if (r < rounds && digit[r] < 256u) lists.order[slot[r]] = static_cast<uint32_t>((w * rounds + r) * 64 + lane);
+    if (threadIdx.x == 0) write_status(lists.counters, lists.status);
+  }
+}
+
+// Tile order of larger batches: this kernel turns the last sort pass's (~first, last + 1) into ranges (an
+// untouched tile keeps (0, 0)), writes each tile's length key with bit 8 set and their counts, and clears the look-back
+// words of the sparse sort pass that follows; block 0 writes the caller's status.
+__global__ __launch_bounds__(256) void k_tile_keys(TileLists lists, int64_t capacity, int one_tile,
+                                                   uint32_t* __restrict__ keys, uint32_t* __restrict__ hist,
+                                                   uint32_t* __restrict__ clear, int64_t clear_n) {
+  __shared__ uint32_t s_hist[256];
+  s_hist[threadIdx.x] = 0u;
+  __syncthreads();
+  const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  for (int64_t i = t; i < clear_n; i += static_cast<int64_t>(gridDim.x) * 256) clear[i] = 0u;
+  if (t < lists.n_tiles) {
+    uint2 r = lists.ranges[t];
+    if (one_tile) {   // nothing was sorted
+      r = make_uint2(0u, static_cast<uint32_t>(min(static_cast<int64_t>(lists.counters[1]), capacity)));
+    } else {
+      r.x = r.y ? ~r.x : 0u;
+    }
+    lists.ranges[t] = r;
+    const uint32_t key = length_key(r);
+    keys[t] = key | 256u;
+    atomicAdd(&s_hist[key], 1u);
+  }
+  __syncthreads();
+  if (s_hist[threadIdx.x]) atomicAdd(&hist[threadIdx.x], s_hist[threadIdx.x]);
+  if (t == 0) write_status(lists.counters, lists.status);
 }
 
 }  // namespace
@@ -525,18 +711,26 @@ vbm_status check_digits(int end_bit, int digit_bits) {
   return VBM_OK;
 }
 
-// Passes first .. passes - 1 of a sort whose histogram has run, ping-ponging from (k0, v0).
+// Passes first .. passes - 1 of a sort whose histogram has run, ping-ponging from (k0, v0); with ranges, the
+// last one also records the runs of equal keys.
 vbm_status sweep(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, int64_t n_max, const uint32_t* n_dev,
-                 int end_bit, int digit_bits, int first, const RadixLayout& L, char* scratch, hipStream_t s) {
+                 int end_bit, int digit_bits, int first, const RadixLayout& L, char* scratch, uint2* ranges,
+                 hipStream_t s) {
   uint32_t* tot = reinterpret_cast<uint32_t*>(scratch + L.off_tot);
   uint32_t* status = reinterpret_cast<uint32_t*>(scratch + L.off_status);
   const int passes = static_cast<int>(ceil_div(end_bit, digit_bits));
+  const dim3 grid(static_cast<unsigned>(ceil_div(n_max, kSweepThreads * kItems)));
   for (int p = first; p < passes; ++p) {
     const int shift = p * digit_bits;
     const int bits = (end_bit - shift) < digit_bits ? (end_bit - shift) : digit_bits;
-    hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, false>), dim3(ceil_div(n_max, kSweepThreads * kItems)),
-                       dim3(kSweepThreads), 0, s, k0, v0, k1, v1, tot + p * 256, status + p * L.nb * L.radix, n_max,
-                       n_dev, shift, bits, static_cast<uint32_t*>(nullptr));
+    if (ranges && p == passes - 1)
+      hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, false, true>), grid, dim3(kSweepThreads), 0, s, k0, v0, k1,
+                         v1, tot + p * 256, status + p * L.nb * L.radix, n_max, n_dev, shift, bits,
+                         static_cast<uint32_t*>(nullptr), ranges);
+    else
+      hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, false, false>), grid, dim3(kSweepThreads), 0, s, k0, v0, k1,
+                         v1, tot + p * 256, status + p * L.nb * L.radix, n_max, n_dev, shift, bits,
+                         static_cast<uint32_t*>(nullptr), static_cast<uint2*>(nullptr));
     VBM_LAUNCH_CHECK("radix_onesweep");
     std::swap(k0, k1);
     std::swap(v0, v1);
@@ -554,38 +748,75 @@ uint32_t* radix_totals(int64_t n_max, int digit_bits, void* scratch) {
   return reinterpret_cast<uint32_t*>(static_cast<char*>(scratch) + radix_layout(n_max, digit_bits).off_tot);
 }
 
-vbm_status radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, int64_t n_max,
-                            const uint32_t* n_dev, int end_bit, int digit_bits, void* scratch, hipStream_t s) {
-  if (n_max <= 0 || end_bit <= 0) return VBM_OK;
-  VBM_TRY(check_digits(end_bit, digit_bits));
-  const RadixLayout L = radix_layout(n_max, digit_bits);
-  char* base = static_cast<char*>(scratch);
-  const int passes = static_cast<int>(ceil_div(end_bit, digit_bits));
-  hipLaunchKernelGGL(k_radix_upsweep<false>, dim3(L.G), dim3(kUpThreads), 0, s, k0, n_max, n_dev, end_bit, digit_bits,
-                     passes, reinterpret_cast<uint32_t*>(base + L.off_tot),
-                     reinterpret_cast<uint32_t*>(base + L.off_status), static_cast<int64_t>(passes) * L.nb * L.radix);
-  VBM_LAUNCH_CHECK("radix_upsweep");
-  return sweep(k0, v0, k1, v1, n_max, n_dev, end_bit, digit_bits, 0, L, base, s);
-}
-
 vbm_status radix_sort_sparse(const uint32_t* keys, int64_t n, uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1,
                              int end_bit, int digit_bits, uint32_t* count_dev, void* scratch, hipStream_t s) {
   if (n <= 0 || end_bit <= 0) return VBM_OK;
   VBM_TRY(check_digits(end_bit, digit_bits));
+  const int passes = static_cast<int>(ceil_div(end_bit, digit_bits));
+  if (n <= kBlockSort) {
+    hipLaunchKernelGGL((k_sort_block<true, false>), dim3(1), dim3(kBlockSortThreads), 0, s, keys,
+                       static_cast<const uint32_t*>(nullptr), passes % 2 ? k0 : k1, passes % 2 ? v0 : v1, n,
+                       static_cast<const uint32_t*>(nullptr), end_bit, count_dev, TileLists());
+    VBM_LAUNCH_CHECK("sort_block");
+    return VBM_OK;
+  }
   const RadixLayout L = radix_layout(n, digit_bits);
   char* base = static_cast<char*>(scratch);
   uint32_t* tot = reinterpret_cast<uint32_t*>(base + L.off_tot);
   uint32_t* status = reinterpret_cast<uint32_t*>(base + L.off_status);
-  const int passes = static_cast<int>(ceil_div(end_bit, digit_bits));
   hipLaunchKernelGGL(k_radix_upsweep<true>, dim3(L.G), dim3(kUpThreads), 0, s, keys, n,
                      static_cast<const uint32_t*>(nullptr), end_bit, digit_bits, passes, tot, status,
                      static_cast<int64_t>(passes) * L.nb * L.radix);
   VBM_LAUNCH_CHECK("radix_upsweep");
-  hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, true>), dim3(ceil_div(n, kSweepThreads * kItems)),
+  hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, true, false>), dim3(ceil_div(n, kSweepThreads * kItems)),
                      dim3(kSweepThreads), 0, s, keys, static_cast<const uint32_t*>(nullptr), k0, v0, tot, status, n,
-                     static_cast<const uint32_t*>(nullptr), 0, end_bit < digit_bits ? end_bit : digit_bits, count_dev);
+                     static_cast<const uint32_t*>(nullptr), 0, end_bit < digit_bits ? end_bit : digit_bits, count_dev,
+                     static_cast<uint2*>(nullptr));
   VBM_LAUNCH_CHECK("radix_onesweep");
-  return sweep(k0, v0, k1, v1, n, count_dev, end_bit, digit_bits, 1, L, base, s);
+  return sweep(k0, v0, k1, v1, n, count_dev, end_bit, digit_bits, 1, L, base, nullptr, s);
+}
+
+int sort_pairs_first(int64_t n_max, int64_t n_tiles, int end_bit, int digit_bits) {
+  if (n_max <= kBlockSort && n_tiles <= kBlockSort) return 0;
+  return static_cast<int>(ceil_div(end_bit, digit_bits)) % 2;
+}
+
+vbm_status sort_pairs_by_tile(uint32_t* const k[2], uint32_t* const v[2], int first, int64_t capacity, int64_t n_max,
+                              const uint32_t* n_dev, int end_bit, int digit_bits, const TileLists& lists,
+                              void* scratch, hipStream_t s) {
+  if (n_max > 0 && n_max <= kBlockSort && lists.n_tiles <= kBlockSort) {
+    hipLaunchKernelGGL((k_sort_block<false, true>), dim3(1), dim3(kBlockSortThreads), 0, s, k[first], v[first], k[0],
+                       v[0], n_max, n_dev, end_bit, static_cast<uint32_t*>(nullptr), lists);
+    VBM_LAUNCH_CHECK("sort_block");
+    return VBM_OK;
+  }
+  if (n_max > 0 && end_bit > 0) {
+    VBM_TRY(check_digits(end_bit, digit_bits));
+    const RadixLayout L = radix_layout(n_max, digit_bits);
+    char* base = static_cast<char*>(scratch);
+    const int passes = static_cast<int>(ceil_div(end_bit, digit_bits));
+    hipLaunchKernelGGL(k_radix_upsweep<false>, dim3(L.G), dim3(kUpThreads), 0, s, k[first], n_max, n_dev, end_bit,
+                       digit_bits, passes, reinterpret_cast<uint32_t*>(base + L.off_tot),
+                       reinterpret_cast<uint32_t*>(base + L.off_status),
+                       static_cast<int64_t>(passes) * L.nb * L.radix);
+    VBM_LAUNCH_CHECK("radix_upsweep");
+    VBM_TRY(sweep(k[first], v[first], k[1 - first], v[1 - first], n_max, n_dev, end_bit, digit_bits, 0, L, base,
+                  lists.ranges, s));
+  }
+  // The pair sort's scratch is free again: the order's look-back words take its place.
+  const int64_t NT = lists.n_tiles;
+  const RadixLayout L = radix_layout(NT, 8);
+  uint32_t* hist = tile_order_counts(scratch);
+  uint32_t* look = reinterpret_cast<uint32_t*>(static_cast<char*>(scratch) + L.off_status);
+  hipLaunchKernelGGL(k_tile_keys, dim3(static_cast<unsigned>(ceil_div(NT, 256))), dim3(256), 0, s, lists, capacity,
+                     end_bit == 0 ? 1 : 0, lists.keys, hist, look, L.nb * L.radix);
+  VBM_LAUNCH_CHECK("tile_keys");
+  hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, true, false>),
+                     dim3(static_cast<unsigned>(ceil_div(NT, kSweepThreads * kItems))), dim3(kSweepThreads), 0, s,
+                     lists.keys, static_cast<const uint32_t*>(nullptr), lists.keys + NT, lists.order, hist, look, NT,
+                     static_cast<const uint32_t*>(nullptr), 0, 8, hist + 256, static_cast<uint2*>(nullptr));
+  VBM_LAUNCH_CHECK("tile_order");
+  return VBM_OK;
 }
 
 }  // namespace vbm

@@ -50,32 +50,38 @@ def test_dwt_tile_edges(G, J, wav, with_tf, offset):
         assert err <= tol, ((j, o), err)
 
 
-# Item counts around the emission's 256-item blocks and the sorts' 4096- and 8192-key tiles; opacities with holes
-# in the depth keys, none visible at all (0), footprints on either side of the 32-tile rule.
-@pytest.mark.parametrize("n,tile,bits,opacity,log_scale", [
-    (1, 16, 8, (0.5, 0.9), -3.0), (255, 16, 8, (0.5, 0.9), -3.0), (256, 8, 8, (0.5, 0.9), -2.0),
-    (257, 16, 4, (0.5, 0.9), -1.6), (300, 16, 8, (0.001, 0.003), -3.0), (4097, 16, 8, (0.001, 0.007), -3.5),
-    (8192, 32, 8, (0.5, 0.9), -4.0), (8193, 16, 8, (0.001, 0.007), -3.5), (16500, 8, 5, (0.001, 0.02), -3.8)])
-def test_pair_lists_at_block_edges(n, tile, bits, opacity, log_scale):
+# Item counts around the emission's 256-item blocks, the sorts' 4096- and 8192-key tiles and the 16384 elements up
+# to which one block sorts; opacities with holes in the depth keys, none visible at all (0), footprints on either
+# side of the 32-tile rule; a batch of one tile (no digits to sort), short and long.
+@pytest.mark.parametrize("n,views,W,H,tile,bits,opacity,log_scale", [
+    (1, 2, 131, 77, 16, 8, (0.5, 0.9), -3.0), (255, 2, 131, 77, 16, 8, (0.5, 0.9), -3.0),
+    (256, 2, 131, 77, 8, 8, (0.5, 0.9), -2.0), (257, 2, 131, 77, 16, 4, (0.5, 0.9), -1.6),
+    (300, 2, 131, 77, 16, 8, (0.001, 0.003), -3.0), (4097, 2, 131, 77, 16, 8, (0.001, 0.007), -3.5),
+    (8192, 2, 131, 77, 32, 8, (0.5, 0.9), -4.0), (8193, 2, 131, 77, 16, 8, (0.001, 0.007), -3.5),
+    (16500, 2, 131, 77, 8, 5, (0.001, 0.02), -3.8), (300, 1, 16, 16, 16, 8, (0.5, 0.9), -3.0),
+    (20000, 1, 16, 15, 16, 8, (0.5, 0.9), -3.0), (700, 1, 640, 1100, 8, 8, (0.2, 0.9), -3.4)])
+def test_pair_lists_at_block_edges(n, views, W, H, tile, bits, opacity, log_scale):
     api = _api()
-    say(f"pair lists n={n} tile={tile} digits={bits} opacity {opacity} log scale {log_scale}")
+    say(f"pair lists n={n} {views} views {W}x{H} tile={tile} digits={bits} opacity {opacity} log scale {log_scale}")
     gs = vi.random_gaussians(n, 31 + n, log_scale_mean=log_scale, opacity_range=opacity)
-    cams = vi.orbit_cameras(2, 131, 77, azimuth0=0.2)
+    cams = vi.orbit_cameras(views, W, H, azimuth0=0.2)
     ref = binning.pair_lists(gs, cams, tile)
     total = ref["tile"].size
-    rp = api.plan_batch(cams, [0, n], tile=tile, sort_bits=bits, pair_capacity=max(total, 1))
-    for _ in range(2):      # the second pass finds the first one's counters, totals and look-back words
-        out = api.render_fwd(rp, to_dev(gs))
-    torch.cuda.synchronize()
-    assert out.status[:2].tolist() == [0, total]
-    assert int(out.status[2]) == sum(int((p["n_tiles"] > 0).sum()) for p in ref["proj"])
-    assert np.array_equal(rp.region("pair_tile", torch.int32).cpu().numpy()[:total], ref["tile"])
-    assert np.array_equal(rp.region("pair_item", torch.int32).cpu().numpy()[:total] & ITEM_MASK, ref["item"])
-    ranges = rp.region("ranges", torch.int32).cpu().numpy().reshape(-1, 2)
     full = ref["ranges"][:, 1] > ref["ranges"][:, 0]
-    assert np.array_equal(ranges[full], ref["ranges"][full])
-    assert np.all(ranges[~full, 0] == ranges[~full, 1])
-    if total > 1:           # one slot short: flagged, and the pairs that fit are the depth order's first
+    # the exact capacity, and one beyond the one-block sort
+    for capacity, mode in ((max(total, 1), "batched"), (total + 16385, "batched"), (total + 16385, "exact")):
+        rp = api.plan_batch(cams, [0, n], tile=tile, sort_bits=bits, pair_capacity=capacity, mode=mode)
+        for _ in range(2):      # the second pass finds the first one's counters, totals and look-back words
+            out = api.render_fwd(rp, to_dev(gs))
+        torch.cuda.synchronize()
+        assert out.status[:2].tolist() == [0, total]
+        assert int(out.status[2]) == sum(int((p["n_tiles"] > 0).sum()) for p in ref["proj"])
+        assert np.array_equal(rp.region("pair_tile", torch.int32).cpu().numpy()[:total], ref["tile"])
+        assert np.array_equal(rp.region("pair_item", torch.int32).cpu().numpy()[:total] & ITEM_MASK, ref["item"])
+        ranges = rp.region("ranges", torch.int32).cpu().numpy().reshape(-1, 2)
+        assert np.array_equal(ranges[full], ref["ranges"][full])
+        assert not ranges[~full].any()
+    if total > 1:           # one slot short: flagged
         rp = api.plan_batch(cams, [0, n], tile=tile, sort_bits=bits, pair_capacity=total - 1)
         out = api.render_fwd(rp, to_dev(gs))
         assert out.status.tolist()[:2] == [1, total]
