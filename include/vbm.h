@@ -240,11 +240,12 @@ typedef struct {
   int32_t sort_bits;     /* radix digit width for the tile sort: 4..8 */
   int64_t pair_capacity; /* pair slots reserved in the workspace, in [1, 2^30) */
   int32_t mode;          /* VBM_MODE_BATCHED or VBM_MODE_EXACT */
-  int32_t lds_batch;     /* record staging of the forward compositing: 0 = each record through the
+  int32_t lds_batch;     /* 0, or 32 or 64 with 8x8 or 16x16 tiles: the forward compositing stages its
+                          * lists in LDS whatever the value (it once chose between walks) */
+  int32_t lds_batch_bwd; /* record staging of the backward compositing: 0 = each record through the
                           * scalar cache into registers; 32 or 64 = the tile's list staged in LDS
                           * batches of that many entries (8x8 and 16x16 tiles only).  Results are
                           * identical. */
-  int32_t lds_batch_bwd; /* the same choice for the backward compositing */
   int32_t pad0;
 } vbm_schedule;
 
@@ -261,7 +262,9 @@ typedef struct {
 
 /* Workspace regions a test may read back after vbm_render_fwd (offsets into ws). */
 #define VBM_REGION_COUNTERS 0    /* uint32 [16]: [0] visible items, [1] pairs, [2] overflow, [4..5]
-                                  * uint64 ballot words taken by large footprints */
+                                  * uint64 ballot words taken by large footprints, [6] and [7] the
+                                  * tiles (the first of the launch order) whose lists four waves share
+                                  * in the forward and in the backward */
 #define VBM_REGION_ITEM_DEPTH 1  /* float32 [n_items] camera depth (0 when culled) */
 #define VBM_REGION_ITEM_RECT 2   /* uint32 [n_items][4], the binning entry of each item:
                                   * [0] x0 | x1 << 16 and [1] y0 | y1 << 16, the candidate
@@ -280,10 +283,10 @@ typedef struct {
 #define VBM_REGION_PAIR_ITEM 7   /* uint32 [pair_capacity]: sorted item of each pair in bits 0..26;
                                   * bit 27 + k is set when the footprint can reach lane group k of
                                   * the tile (with 16x16 tiles pixel rows 4k .. 4k + 3; every group
-                                  * with other tiles); bit 31 is 0.  With 8x8 and 16x16 tiles
-                                  * vbm_render_fwd keeps a copy elsewhere in ws with bit 27 + k set
-                                  * when it evaluated lane group k (pixel rows k*64/tile .. of the
-                                  * tile) of the pair, which vbm_render_bwd reads */
+                                  * with other tiles); bit 31 is 0.  With 16x16 tiles a copy
+                                  * is kept elsewhere in ws with bit 27 + k set when the pair can reach
+                                  * a pixel of lane group k (pixel rows 4k .. 4k + 3 of the tile), which
+                                  * vbm_render_bwd reads */
 #define VBM_REGION_RANGES 8      /* uint32 [n_tiles][2]: [start, end) of each tile's list */
 #define VBM_REGION_GRAD2D 9      /* float32 [n_items][16] after vbm_render_bwd: columns 0..5 hold the
                                   * sums over the item's pixels of dL/dpower times dx, dy, dx^2,

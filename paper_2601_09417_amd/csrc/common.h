@@ -68,8 +68,8 @@ struct DevScene {
 // ------------------------------------------------------------------ pair values
 // A pair value holds the item id in bits 0..26 (the plan keeps items below 2^27) and a 4-bit mask
 // of the tile's lane groups in bits 27..30.  With 16x16 tiles lane group k is pixel rows
-// 4k .. 4k + 3 of the tile.  The emission sets the groups the footprint can reach (all four with
-// other tiles), and the forward's marked copy the groups it evaluated.
+// 4k .. 4k + 3 of the tile.  The emission sets the groups whose rows the footprint can reach (all four
+// with other tiles), and the forward's marked copy the groups of which it can reach a pixel.
 constexpr int kItemBits = 27;
 constexpr uint32_t kItemMask = (1u << kItemBits) - 1u;
 
@@ -114,14 +114,30 @@ uint32_t* radix_totals(int64_t n_max, int digit_bits, void* scratch);
 vbm_status radix_sort_sparse(const uint32_t* keys, int64_t n, uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1,
                              int end_bit, int digit_bits, uint32_t* count_dev, void* scratch, hipStream_t s);
 
+// Tiles whose lists are composited by four waves each, a band of four pixel rows per wave (16x16 tiles, longest
+// lists first).  A launch takes at least as long as its longest list takes one wave, and a batch of few tiles does
+// not fill the chip with one wave each; in a batch of many tiles four waves only cost more (the list is staged and
+// read four times).
+//   Forward: every list in batches of up to kSplitAllTiles tiles, else lists of pairs / 8192 entries or more.
+//     us with a wave per list / every list shared (tiles, pairs): 600 / 270 (8,400, 3.4M), 437 / 203 (8,160, 2.4M),
+//     499 / 388 (16,320, 4.9M), 668 / 917 (32,640, 9.8M), 533 / 772 (40,000, 7.9M).
+//   Backward (its sums over a band cost as much as over a tile): lists of pairs / 2048 entries or more.  us with a wave
+//     per list / this rule / pairs / 4096: 773 / 695 / 882 (8,400 tiles, 3.4M pairs), 210 / 141 / 138 (2,400, 0.6M),
+//     829 / 751 / 887 (12,544, 4.0M), 115 / 69 / 69 (600, 0.1M).
+constexpr int kMaxSplit = 20480;        // at most
+constexpr int kSplitAllTiles = 20480;
+constexpr uint32_t kSplitForward = 8192, kSplitBackward = 2048;
+constexpr int kSplitCounter = 6;        // their numbers for the forward and the backward, among the forward's counters
+
 // The tiles' lists after the pair sort.
 struct TileLists {
   uint2* ranges;             // [n_tiles]: [start, end) of each tile's list
   int64_t n_tiles;
   uint32_t* order;           // [n_tiles]: tiles in launch order, the longest lists first (in steps of 8 entries, stable)
   uint32_t* keys;            // [2][n_tiles]: the order's sort keys
-  const uint32_t* counters;  // of the forward
+  uint32_t* counters;        // of the forward: the numbers of split tiles go to [6] and [7]
   int32_t* status;           // the caller's
+  uint32_t split_fwd, split_bwd;   // shares of split_key
 };
 // Sorts the pairs in (k[first], v[first]) by tile into (k[0], v[0]) (first as sort_pairs_first says; the count is
 // read from *n_dev when non-null, and is at most n_max), and writes the tiles' ranges (cleared beforehand),

@@ -4,13 +4,14 @@
 // Work decomposition: one wave64 per 256 pixels of a tile (a 16x16 tile is one wave, a 32x32 tile
 // four independent waves, an 8x8 tile one wave with one pixel per lane), each lane owning
 // PPL = 4 pixels of ONE pixel column (rows 64 / TILE apart), so the horizontal offset to a
-// Gaussian's centre is shared by a lane's pixels.  The tile's depth-sorted list is walked by every
-// wave in lockstep, with each Gaussian's 36-byte record wave-uniform, in one of two ways chosen by
-// the plan: through the scalar data cache into SGPRs, each record one list step ahead of its use
-// (no LDS, no barriers, no per-lane copies of a uniform value); or staged in LDS, where the first
-// LDSB lanes each gather one list entry's record with vector loads into a double-buffered batch
-// that the wave then reads entry by entry.  Either way the per-Gaussian load cost is amortised over
-// 256 pixels; a vector load of a uniform address instead would move 64 lanes' copies through the
+// Gaussian's centre is shared by a lane's pixels.  In a batch that does not fill the chip that way the
+// lists of 16x16 tiles are shared by four waves, a band of four rows and one pixel per lane each.  The tile's
+// depth-sorted list is walked by every wave in lockstep, with each Gaussian's 36-byte record wave-uniform.
+// The forward stages the list in LDS: lanes gather an entry's record each with vector loads into a batch
+// that the wave then reads entry by entry.  The backward reads each record through the scalar data
+// cache into SGPRs, one list step ahead of its use (no LDS, no barriers, no per-lane copies of a uniform
+// value), or from LDS batches as the plan chooses.  Either way the per-Gaussian load cost is amortised over
+// the wave's pixels; a vector load of a uniform address instead would move 64 lanes' copies through the
 // texture address and data units, which the list walk would saturate.
 //
 // The record holds the exponent in base 2 with the log-opacity folded in:
@@ -34,6 +35,7 @@
 #include <hip/hip_runtime.h>
 
 #include "common.h"
+#include "composite.h"
 
 namespace vbm {
 
@@ -64,26 +66,6 @@ __device__ __forceinline__ int find_view(const DevView* __restrict__ views, int 
 struct Rec {
   float mx, my, hA, hB, hC, lo, r, g, b;
 };
-
-// The forward reads pair values with vector buffer loads, three list steps ahead: they complete
-// in issue order (so each is waited for exactly, without waiting for the next record's scalar
-// loads) and a position past num_records reads zero instead of faulting.  num_records is a 32-bit
-// byte count; the plan bounds the pair capacity by 2^30.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t item_rsrc(const uint32_t* pair_item, int64_t n_pairs) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(pair_item), (short)0,
-                                           static_cast<int>(static_cast<uint32_t>(n_pairs * 4)), 0x00020000);
-}
-__device__ __forceinline__ uint32_t load_item(__amdgpu_buffer_rsrc_t items, int j) {
-  return static_cast<uint32_t>(__builtin_amdgcn_raw_buffer_load_b32(items, 0, 4 * j, 0));
-}
-
-// Rewrites the n <= 3 pair values j, j + 1, j + 2 (uniform v0, v1, v2) of the marked copy with
-// one vector store from lanes 0 .. n - 1.
-__device__ __forceinline__ void store_pair_values(uint32_t* __restrict__ marked, int lane, int j, int n, uint32_t v0,
-                                                  uint32_t v1, uint32_t v2) {
-  const uint32_t v = lane == 0 ? v0 : lane == 1 ? v1 : v2;
-  if (lane < n) marked[j + lane] = v;
-}
 
 __device__ __forceinline__ uint32_t uniform(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
 
@@ -239,6 +221,10 @@ constexpr float kDeadRow = 1e30f;
 constexpr float kE2Skip = -7.9953534f;
 constexpr float kLiveBound = 1e29f;
 
+// Transmittance behind a Gaussian: T - alpha T in one rounding, written out so that every walk takes the
+// same one.
+__device__ __forceinline__ float attenuate(float T, float alpha) { return fmaf(-T, alpha, T); }
+
 template <int PPL>
 __device__ __forceinline__ bool any_live(const float (&fy)[PPL]) {
   float m = fy[0];
@@ -251,38 +237,25 @@ __device__ __forceinline__ bool any_live(const float (&fy)[PPL]) {
 // alpha = min(0.99, 2^e2); a pixel takes the Gaussian when alpha >= 1/255, unless the new
 // transmittance would fall below 1e-4, in which case the pixel stops without it and records pos as
 // the number of list entries its compositing took into account.  Only the lane groups in `reach`
-// (the pair value's groups that the footprint can reach, uniform) are looked at.  Returns the mask
-// of lane groups k that were evaluated: every group with a pixel that took the Gaussian is among
-// them.
+// (uniform, every group with a pixel that passes the alpha test among them) are looked at.
 template <int PPL, bool STATS>
-__device__ __forceinline__ uint32_t fwd_step(const Rec& r, uint32_t reach, int pos, float fx, float (&fy)[PPL],
-                                             float (&T)[PPL], float (&cr)[PPL], float (&cg)[PPL], float (&cb)[PPL],
-                                             int (&nvis)[PPL], uint32_t& n_eval, uint32_t& n_used) {
-  uint32_t groups = 0;
+__device__ __forceinline__ void fwd_step(const Rec& r, uint32_t reach, int pos, float fx, float (&fy)[PPL],
+                                         float (&T)[PPL], float (&cr)[PPL], float (&cg)[PPL], float (&cb)[PPL],
+                                         int (&nvis)[PPL], uint32_t& n_used) {
   const float dx = r.mx - fx;
   const float u = fmaf(r.hA, dx * dx, r.lo);
   const float vb = r.hB * dx;
 #pragma unroll
   for (int k = 0; k < PPL; ++k) {
-    // a group out of the footprint's rows: nothing to evaluate (a scalar bit test)
-    if (!((reach >> k) & 1u)) {
-      if (STATS) n_eval += fy[k] < kLiveBound ? 1u : 0u;
-      continue;
-    }
+    // a group out of the footprint's reach: nothing to evaluate (a scalar bit test)
+    if (!((reach >> k) & 1u)) continue;
     const float dy = r.my - fy[k];
-    const float e2 = exponent2(r, u, vb, dy);
-    // A lane group where every pixel has 2^e2 clearly below 1/255 (or is terminated, e2 = -inf)
-    // takes nothing from this Gaussian: skip the exponential and the update with one uniform branch.
-    if (!wave_any(e2 >= kE2Skip)) {
-      if (STATS) n_eval += fy[k] < kLiveBound ? 1u : 0u;
-      continue;
-    }
-    groups |= 1u << k;
-    const float alpha = fminf(kAlphaMax, __builtin_amdgcn_exp2f(e2));
+    const float alpha = fminf(kAlphaMax, __builtin_amdgcn_exp2f(exponent2(r, u, vb, dy)));
     const bool ok = alpha >= kAlphaMin;
     // A pixel that fails the alpha test takes weight 0, which leaves T and its colour unchanged.
-    float w = (ok ? alpha : 0.0f) * T[k];
-    T[k] -= w;
+    const float a = ok ? alpha : 0.0f;
+    float w = a * T[k];
+    T[k] = attenuate(T[k], a);
     // A live pixel keeps T >= 1e-4, so only one that takes the Gaussian can fall below: it stops
     // without it (rare, so handled in a uniform branch), its transmittance going back to the value
     // before the Gaussian (T + w, within a unit in the last place of it).
@@ -293,17 +266,12 @@ __device__ __forceinline__ uint32_t fwd_step(const Rec& r, uint32_t reach, int p
       w = stop ? 0.0f : w;
       fy[k] = stop ? kDeadRow : fy[k];
       nvis[k] = stop ? pos : nvis[k];
-      if (STATS) n_eval += stop ? 1u : 0u;
     }
-    if (STATS) {
-      n_eval += fy[k] < kLiveBound ? 1u : 0u;
-      n_used += ok && fy[k] < kLiveBound ? 1u : 0u;
-    }
+    if (STATS) n_used += w > 0.0f ? 1u : 0u;
     cr[k] = fmaf(r.r, w, cr[k]);
     cg[k] = fmaf(r.g, w, cg[k]);
     cb[k] = fmaf(r.b, w, cb[k]);
   }
-  return groups;
 }
 
 // Records of an LDS batch (the optional staged list walk): B consecutive list entries, one per
@@ -349,45 +317,6 @@ __device__ __forceinline__ Rec lds_get(const LdsBatch<B>& L, int buf, int b) {
   return r;
 }
 
-// Lane-group marks of an LDS batch, one 4-bit nibble per list step, kept in wave-uniform 64-bit
-// words (scalar registers, so collecting them costs the vector pipes nothing).  A step ORs its
-// marks into the current word at bits 4 (b mod 16); every 16 steps the word is pushed onto a short
-// queue of filled words (most recent first), so the per-step cost does not grow with the batch and
-// no word is ever selected by a computed index (which would put them in scratch memory).
-template <int B>
-struct MarkWords {
-  static_assert(B == 32 || B == 64, "16 list steps per word, two or four words");
-  uint64_t cur = 0, w0 = 0, w1 = 0, w2 = 0, w3 = 0;
-  int filled = 0;
-  __device__ __forceinline__ void set(int b, uint32_t g) {
-    cur |= static_cast<uint64_t>(g) << (4 * (b & 15));
-    if ((b & 15) == 15) push();
-  }
-  // after the batch's n steps: pushes a partly filled last word
-  __device__ __forceinline__ void finish(int n) {
-    if (n & 15) push();
-  }
-  // The marks of step `lane` (lane < B).
-  __device__ __forceinline__ uint32_t of_lane(int lane) const {
-    const int q = filled - 1 - (lane >> 4);   // queue slot of the lane's word
-    uint64_t x = q == 0 ? w0 : w1;
-    if (B == 64) x = q == 2 ? w2 : (q == 3 ? w3 : x);
-    return static_cast<uint32_t>(x >> (4 * (lane & 15))) & 15u;
-  }
-
- private:
-  __device__ __forceinline__ void push() {
-    if (B == 64) {
-      w3 = w2;
-      w2 = w1;
-    }
-    w1 = w0;
-    w0 = cur;
-    cur = 0;
-    ++filled;
-  }
-};
-
 // Lane t's entry of the batch at list positions pos(t) (per-lane vector loads): its pair value and
 // record (the record of a clamped item when the position lies outside [lo, hi], never read).
 __device__ __forceinline__ void lds_fetch(const uint32_t* __restrict__ values, const float4* __restrict__ crec,
@@ -400,133 +329,283 @@ __device__ __forceinline__ void lds_fetch(const uint32_t* __restrict__ values, c
   bl = cblue[it];
 }
 
-// LDSB = 0: records through the scalar cache (the default); LDSB = 32 or 64: the list is staged in
-// LDS batches of that many entries (one wave per tile only), a tuning candidate.
-template <int TILE, bool STATS, int LDSB>
-__global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_composite_fwd(
-    const DevView* __restrict__ views, int n_views, const uint2* __restrict__ ranges,
-    const uint32_t* __restrict__ tile_order,
-    const uint32_t* __restrict__ pair_item, int64_t n_pairs, uint32_t* __restrict__ pair_marked,
+// A list staged for a wave whose lanes own one pixel each: up to 64 entries, and four of padding.
+struct LdsList {
+  float4 a[68], b[68];
+  float2 c[68];   // blue, the list position's bits
+};
+
+// False only when alpha < 1/255 at every pixel centre of a 16x4 band, [x0, x0 + 15] x [y0, y0 + 3]: the largest
+// e2 over that rectangle, at the mean if that is inside and else on one of the four edges, where e2 is a 1D quadratic
+// with a clamped maximum.  The bound is raised by well over the rounding of this evaluation and of exponent2.
+__device__ __forceinline__ bool band_reached(const float4& a, const float4& b, float x0, float y0) {
+  const float hA = a.z, hB = a.w, hC = b.x, lo = b.y;
+  const float dx0 = x0 - a.x, dx1 = dx0 + 15.0f, dy0 = y0 - a.y, dy1 = dy0 + 3.0f;
+  auto e2 = [&](float dx, float dy) { return fmaf(fmaf(hC, dy, hB * dx), dy, fmaf(hA, dx * dx, lo)); };
+  const float sx = -0.5f * hB * __builtin_amdgcn_rcpf(hA), sy = -0.5f * hB * __builtin_amdgcn_rcpf(hC);
+  const float m = fmaxf(fmaxf(e2(dx0, __builtin_amdgcn_fmed3f(sy * dx0, dy0, dy1)),
+                              e2(dx1, __builtin_amdgcn_fmed3f(sy * dx1, dy0, dy1))),
+                        fmaxf(e2(__builtin_amdgcn_fmed3f(sx * dy0, dx0, dx1), dy0),
+                              e2(__builtin_amdgcn_fmed3f(sx * dy1, dx0, dx1), dy1)));
+  const float ax = fmaxf(fabsf(dx0), fabsf(dx1)), ay = fmaxf(fabsf(dy0), fabsf(dy1));
+  const float terms = fmaf(fabsf(hA) * ax, ax, fmaf(fabsf(hB) * ax, ay, fabsf(hC) * ay * ay));
+  const bool inside = dx0 <= 0.0f && dx1 >= 0.0f && dy0 <= 0.0f && dy1 >= 0.0f;
+  return inside || !(m + fmaf(4e-6f, terms, 0.01f) < kE2Skip);
+}
+
+// The list walk of a wave with one pixel per lane (8x8 tiles, or one band of a 16x16 tile that four waves share):
+// the list goes through LDS in batches of 64 entries, with bands only those that can reach the band
+// (the pair value's mark of the band's rows, then band_reached, a lane per entry), closed up;
+// four entries are evaluated at a time, independently of each other up to the
+// transmittance, and the stop test is made once for the four (they are taken again one by one when a
+// pixel stops).  The arithmetic per entry is fwd_step's.  The next batch's records are requested while this one is
+// walked and its pair values one batch earlier, so that a lone wave waits for neither.
+template <bool STATS, bool kBand>
+__device__ __forceinline__ void fwd_walk_pixels(LdsList& L, const uint32_t* __restrict__ pair_item, int start, int end,
+                                                uint32_t group, float band_x0, float band_y0,
+                                                const float4* __restrict__ crec, const float* __restrict__ cblue,
+                                                uint32_t* __restrict__ planes, int lane, float fx, float& fy,
+                                                float& T, float& cr, float& cg, float& cb, int& nvis,
+                                                uint32_t& n_used) {
+  float4 ra, rb;
+  float bl = 0.0f;
+  auto fetch = [&](uint32_t pv, bool ok) {
+    if (ok) {
+      const uint32_t it = pv & kItemMask;
+      ra = crec[2 * it];
+      rb = crec[2 * it + 1];
+      bl = cblue[it];
+    }
+  };
+  uint32_t pv = start + lane < end ? pair_item[start + lane] : 0u;
+  uint32_t pv_next = start + 64 + lane < end ? pair_item[start + 64 + lane] : 0u;
+  fetch(pv, (pv & group) != 0u);
+  for (int base = start; base < end; base += 64) {
+    bool ok = (pv & group) != 0u;   // (0 past the end of the list)
+    if (kBand) ok = ok && band_reached(ra, rb, band_x0, band_y0);
+    const uint64_t m = __ballot(ok);
+    const int n = __popcll(m);
+    if (kBand && lane < 2) planes[(base - start) / 64 * 8 + lane] = static_cast<uint32_t>(m >> (32 * lane));
+    if (ok) {
+      const int at = static_cast<int>(popc_below(m));
+      L.a[at] = ra;
+      L.b[at] = rb;
+      L.c[at] = make_float2(bl, __int_as_float(base - start + lane));
+    }
+    if (lane < 4) {   // padding entries: alpha 0
+      L.a[n + lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      L.b[n + lane] = make_float4(0.0f, -__builtin_inff(), 0.0f, 0.0f);
+      L.c[n + lane] = make_float2(0.0f, 0.0f);
+    }
+    pv = pv_next;
+    fetch(pv, (pv & group) != 0u);
+    pv_next = base + 128 + lane < end ? pair_item[base + 128 + lane] : 0u;
+    for (int i = 0; i < n; i += 4) {
+      float alpha[4], w[4], red[4], green[4], blue[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float4 ra4 = L.a[i + k], rb4 = L.b[i + k];
+        const Rec r{ra4.x, ra4.y, ra4.z, ra4.w, rb4.x, rb4.y, rb4.z, rb4.w, L.c[i + k].x};
+        red[k] = r.r;
+        green[k] = r.g;
+        blue[k] = r.b;
+        const float dx = r.mx - fx;
+        const float e2 = exponent2(r, fmaf(r.hA, dx * dx, r.lo), r.hB * dx, r.my - fy);
+        const float al = fminf(kAlphaMax, __builtin_amdgcn_exp2f(e2));
+        alpha[k] = al >= kAlphaMin ? al : 0.0f;
+      }
+      const float T0 = T;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        w[k] = alpha[k] * T;
+        T = attenuate(T, alpha[k]);
+      }
+      if (wave_any(T < kTMin)) {
+        __asm__ volatile("" ::: "memory");   // keeps this a branch
+        T = T0;
+        bool stopped = false;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float a = stopped ? 0.0f : alpha[k];
+          w[k] = a * T;
+          T = attenuate(T, a);
+          const bool stop = T < kTMin;
+          T = stop ? T + w[k] : T;
+          w[k] = stop ? 0.0f : w[k];
+          fy = stop ? kDeadRow : fy;
+          nvis = stop ? __float_as_int(L.c[i + k].y) : nvis;
+          stopped |= stop;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (STATS) n_used += w[k] > 0.0f ? 1u : 0u;
+        cr = fmaf(red[k], w[k], cr);
+        cg = fmaf(green[k], w[k], cg);
+        cb = fmaf(blue[k], w[k], cb);
+      }
+    }
+    if (!wave_any(fy < kLiveBound)) {
+      if (kBand)   // the entries that no pixel of the band lived to see
+        for (int q = (base - start) / 64 + 1 + (lane >> 1); start + 64 * q < end; q += 32) planes[8 * q + (lane & 1)] = 0u;
+      break;
+    }
+  }
+}
+
+// Marks of a split tile, whose bands are walked by different waves: bit l of the 64-bit plane of band k and batch q
+// tells whether entry 64 q + l of the list can reach band k.  The planes lie in the idle tile-key buffer at
+// the list's own places, eight words per batch (a split list has 16 entries or more, so they fit).
+__device__ __forceinline__ uint32_t* mark_plane(uint32_t* planes, int start, int band) {
+  return planes + start + 2 * band;
+}
+
+// Work of one compositing wave: a tile, and with 16x16 tiles either all of it or one of its four bands
+// (band >= 0).  The first n_split tiles of the launch order, which have the longest lists, are taken by four waves
+// each, so that the longest list is no longer what the launch waits for (split_key in
+// scan_sort.hip says which).  tile < 0: nothing to do.
+struct WaveWork {
+  int tile, band;
+};
+template <int TILE>
+__device__ __forceinline__ WaveWork wave_work(const uint32_t* __restrict__ tile_order, int n_tiles,
+                                              const uint32_t* __restrict__ n_split) {
+  const int b = static_cast<int>(blockIdx.x);
+  if (TILE != 16) return {static_cast<int>(tile_order[b]), -1};
+  const int ns = static_cast<int>(*n_split);
+  if (b < 4 * ns) return {static_cast<int>(tile_order[b >> 2]), b & 3};
+  if (b - 3 * ns >= n_tiles) return {-1, -1};
+  return {static_cast<int>(tile_order[b - 3 * ns]), -1};
+}
+
+// Entries per LDS batch of the forward's walk with four pixels per lane: with 64 the walk took 0.99
+// against 0.90 ms (16M pairs, 1080p), and through the scalar cache 1.13 ms.  A test of each band by the wave (an exponent
+// and a ballot per step and band) instead of the staging lane's took 1.72 against 1.63 ms (27M pairs);
+// marks that tell whether a pixel passed the alpha test, collected in scalar registers, 1.82 ms for 2% of the backward.
+constexpr int kFwdBatch = 32;
+
+template <int TILE, bool STATS>
+__global__ __launch_bounds__(TileCfg<TILE>::kThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_composite_fwd(
+    const DevView* __restrict__ views, int n_views, int n_tiles, const uint2* __restrict__ ranges,
+    const uint32_t* __restrict__ tile_order, const uint32_t* __restrict__ n_split,
+    const uint32_t* __restrict__ pair_item, uint32_t* __restrict__ pair_marked, uint32_t* __restrict__ planes,
     const float* __restrict__ coef, const float* __restrict__ blue, int64_t n_items, float* __restrict__ image,
     float* __restrict__ final_T, int32_t* __restrict__ n_contrib, unsigned long long* __restrict__ stats) {
   using C = TileCfg<TILE>;
   constexpr int PPL = C::kPPL;
+  // one list buffer per wave; a wave's LDS operations complete in issue order, so no barrier separates its
+  // writes from its reads
+  union Lists {
+    LdsBatch<kFwdBatch> batch;
+    LdsList list;
+  };
+  __shared__ __align__(16) char lds[C::kWaves][sizeof(Lists)];
   const int lane = static_cast<int>(threadIdx.x) & 63;
   const int wave = static_cast<int>(threadIdx.x) >> 6;
-  const int tile = static_cast<int>(tile_order[blockIdx.x]);
+  const WaveWork work = wave_work<TILE>(tile_order, n_tiles, n_split);
+  if (work.tile < 0) return;
+  const int tile = work.tile;
   const DevView& v = views[find_view(views, n_views, tile)];
   const int local = tile - v.tile_offset;
   const int tx = local % v.tiles_x, ty = local / v.tiles_x;
-  float fy[PPL], T[PPL], cr[PPL], cg[PPL], cb[PPL];
-  int nvis[PPL];
-  bool inside[PPL];
-  int py[PPL];
-  const int q0 = wave * (C::kPix / C::kWaves) + lane;
-  const int px = tx * TILE + q0 % TILE;
-  const float fx = static_cast<float>(px) + 0.5f;
-#pragma unroll
-  for (int k = 0; k < PPL; ++k) {
-    py[k] = ty * TILE + (q0 + k * 64) / TILE;
-    inside[k] = px < v.width && py[k] < v.height;
-    fy[k] = inside[k] ? static_cast<float>(py[k]) + 0.5f : kDeadRow;
-    T[k] = 1.0f;
-    cr[k] = cg[k] = cb[k] = 0.0f;
-  }
   const uint2 rg = ranges[tile];
   // the range is the same for every lane: keep it (and the list walk's counters) in scalar registers
   const int start = static_cast<int>(uniform(rg.x)), end = static_cast<int>(uniform(rg.y));
-#pragma unroll
-  for (int k = 0; k < PPL; ++k) nvis[k] = end - start;
-  uint32_t n_eval = 0, n_used = 0;
-  const int lastj = end > start ? end - 1 : start;
-  // With one wave per tile, each processed pair value is copied to pair_marked with the mask of the
-  // lane groups that the step evaluated in bits kItemBits.. (see fwd_step): the backward visits
-  // only those, reading the copy through the scalar cache.
-  constexpr bool kMark = C::kWaves == 1;
   const float4* __restrict__ crec = reinterpret_cast<const float4*>(coef);
-  const uint32_t imax = n_items > 0 ? static_cast<uint32_t>(n_items - 1) : 0u;
-  if constexpr (LDSB > 0) {
-    static_assert(C::kWaves == 1, "LDS batches are wave-private");
-    // Double-buffered batches: the next batch's entries are loaded into registers (one per lane)
-    // while the current one is walked, then written to the other LDS buffer.  A single wave uses
-    // the LDS, whose operations it issues in order, so no barrier separates the writes from the
-    // reads.  The marks of a batch collect in uniform words and go out with one coalesced store
-    // (lane b: step b).
-    __shared__ LdsBatch<LDSB> L;
-    uint32_t pv, pvc;
-    float4 ra, rb;
-    float bl;
-    lds_fetch(pair_item, crec, blue, imax, start + lane, lane < LDSB && start + lane < end, pvc, ra, rb, bl);
-    lds_put<LDSB>(L, 0, lane, ra, rb, bl, pvc);
-    int buf = 0;
-    for (int base = start; base < end; base += LDSB) {
-      if (!any_live(fy)) break;
-      const int nb = base + LDSB;
-      lds_fetch(pair_item, crec, blue, imax, nb + lane, lane < LDSB && nb + lane < end, pv, ra, rb, bl);
-      // batch length and first list position, kept scalar so that the step loop runs on the SALU
-      const int n = static_cast<int>(uniform(static_cast<uint32_t>(min(LDSB, end - base))));
-      const int pos0 = static_cast<int>(uniform(static_cast<uint32_t>(base - start)));
-      MarkWords<LDSB> mw;
-      for (int b = 0; b < n; ++b) {
-        const Rec r = lds_get<LDSB>(L, buf, b);
-        const uint32_t reach = lds_pv<LDSB>(L, buf, b) >> kItemBits;
-        mw.set(b, fwd_step<PPL, STATS>(r, reach, pos0 + b, fx, fy, T, cr, cg, cb, nvis, n_eval, n_used));
-      }
-      mw.finish(n);
-      if (lane < n) pair_marked[base + lane] = (pvc & kItemMask) | (mw.of_lane(lane) << kItemBits);
-      buf ^= 1;
-      pvc = pv;
-      lds_put<LDSB>(L, buf, lane, ra, rb, bl, pv);
-    }
-  } else {
-  // Records through the scalar cache one list step ahead of their use, pair values by vector loads
-  // three steps ahead (measured faster here than scalar pair-value loads, which put a second
-  // scalar round trip in front of every record), unrolled by three so that the item slots rotate
-  // without copies.  All three steps of an iteration run; past the end of the list a record is a
-  // duplicate whose log-opacity is set to -inf, so alpha = 0 and it changes nothing.
-  const __amdgpu_buffer_rsrc_t irs = item_rsrc(pair_item, n_pairs);
-  uint32_t u0 = uniform(load_item(irs, start)), u1, u2;
-  Rec R0 = load_rec_s(crec, blue, u0, imax), R1, R2;
-  uint32_t L1 = load_item(irs, min(start + 1, lastj)), L2 = load_item(irs, min(start + 2, lastj)),
-           L0 = load_item(irs, min(start + 3, lastj));
-  for (int j = start; j < end; j += 3) {
-    if (!any_live(fy)) break;
-    wait_scalar_loads();
-    u1 = uniform(L1);
-    R1 = load_rec_s(crec, blue, u1, imax);
-    L1 = load_item(irs, min(j + 4, lastj));
-    const uint32_t m0 = (u0 & kItemMask) | (fwd_step<PPL, STATS>(R0, u0 >> kItemBits, j - start, fx, fy, T, cr, cg, cb, nvis,
-                                                                  n_eval, n_used) << kItemBits);
-    wait_scalar_loads();
-    R1.lo = j + 1 < end ? R1.lo : -__builtin_inff();
-    u2 = uniform(L2);
-    R2 = load_rec_s(crec, blue, u2, imax);
-    L2 = load_item(irs, min(j + 5, lastj));
-    const uint32_t un = uniform(L0);
-    const uint32_t m1 = (u1 & kItemMask) | (fwd_step<PPL, STATS>(R1, u1 >> kItemBits, j - start + 1, fx, fy, T, cr, cg, cb, nvis,
-                                                                  n_eval, n_used) << kItemBits);
-    wait_scalar_loads();
-    R2.lo = j + 2 < end ? R2.lo : -__builtin_inff();
-    R0 = load_rec_s(crec, blue, un, imax);
-    L0 = load_item(irs, min(j + 6, lastj));
-    const uint32_t m2 = (u2 & kItemMask) | (fwd_step<PPL, STATS>(R2, u2 >> kItemBits, j - start + 2, fx, fy, T, cr, cg, cb, nvis,
-                                                                  n_eval, n_used) << kItemBits);
-    if (kMark) store_pair_values(pair_marked, lane, j, min(end - j, 3), m0, m1, m2);
-    u0 = un;
-  }
-  }
-  if (STATS) add_stats(stats, n_eval, n_used);
+  uint32_t n_eval = 0, n_used = 0;
   const int64_t HW = static_cast<int64_t>(v.width) * v.height;
   float* img = image + 3 * static_cast<int64_t>(v.pixel_offset);
+  auto store = [&](int px, int py, float T, float cr, float cg, float cb, int nvis) {
+    const int64_t pix = static_cast<int64_t>(py) * v.width + px;
+    img[pix] = cr + T * v.bg[0];
+    img[HW + pix] = cg + T * v.bg[1];
+    img[2 * HW + pix] = cb + T * v.bg[2];
+    final_T[v.pixel_offset + pix] = T;
+    n_contrib[v.pixel_offset + pix] = nvis;
+  };
+  const int q0 = wave * (C::kPix / C::kWaves) + lane;
+  const int px = tx * TILE + q0 % TILE;
+  const float fx = static_cast<float>(px) + 0.5f;
+  if (PPL == 1 || work.band >= 0) {
+    const int band = PPL == 1 ? 0 : work.band;
+    const int py = ty * TILE + (q0 + 64 * band) / TILE;
+    const bool inside = px < v.width && py < v.height;
+    float fy = inside ? static_cast<float>(py) + 0.5f : kDeadRow, T = 1.0f, cr = 0.0f, cg = 0.0f, cb = 0.0f;
+    int nvis = end - start;
+    fwd_walk_pixels<STATS, PPL != 1>(*reinterpret_cast<LdsList*>(lds[wave]), pair_item, start, end,
+                                     1u << (kItemBits + band), static_cast<float>(tx * TILE) + 0.5f,
+                                     static_cast<float>(ty * TILE + 4 * band) + 0.5f, crec, blue,
+                                     mark_plane(planes, start, band), lane, fx, fy, T, cr, cg, cb, nvis, n_used);
+    if (STATS) {
+      // every list entry up to and with the one that stopped the pixel
+      n_eval = !inside ? 0u : static_cast<uint32_t>(nvis + (fy < kLiveBound ? 0 : 1));
+      add_stats(stats, n_eval, n_used);
+    }
+    if (inside) store(px, py, T, cr, cg, cb, nvis);
+    return;
+  }
+  if constexpr (PPL > 1) {
+    float fy[PPL], T[PPL], cr[PPL], cg[PPL], cb[PPL];
+    int nvis[PPL], py[PPL];
+    bool inside[PPL];
 #pragma unroll
-  for (int k = 0; k < PPL; ++k) {
-    if (!inside[k]) continue;
-    const int64_t pix = static_cast<int64_t>(py[k]) * v.width + px;
-    img[pix] = cr[k] + T[k] * v.bg[0];
-    img[HW + pix] = cg[k] + T[k] * v.bg[1];
-    img[2 * HW + pix] = cb[k] + T[k] * v.bg[2];
-    final_T[v.pixel_offset + pix] = T[k];
-    n_contrib[v.pixel_offset + pix] = nvis[k];
+    for (int k = 0; k < PPL; ++k) {
+      py[k] = ty * TILE + (q0 + k * 64) / TILE;
+      inside[k] = px < v.width && py[k] < v.height;
+      fy[k] = inside[k] ? static_cast<float>(py[k]) + 0.5f : kDeadRow;
+      T[k] = 1.0f;
+      cr[k] = cg[k] = cb[k] = 0.0f;
+      nvis[k] = end - start;
+    }
+    // Double-buffered batches: the next batch's entries are loaded into registers (one per lane)
+    // while the current one is walked, then written to the other LDS buffer.  With 16x16 tiles the lane that stages an
+    // entry also tests its four bands (32 tests of some 35 operations serve a batch, where a test by the wave
+    // costs every step an exponent and a ballot per band), and the pair value goes to pair_marked with
+    // the bands it found in bits kItemBits..: the backward visits only those.
+    constexpr bool kMark = TILE == 16;
+    const uint32_t imax = n_items > 0 ? static_cast<uint32_t>(n_items - 1) : 0u;
+    LdsBatch<kFwdBatch>& L = *reinterpret_cast<LdsBatch<kFwdBatch>*>(lds[wave]);
+    uint32_t pv;
+    float4 ra, rb;
+    float bl;
+    auto stage = [&](int buf, int base) {
+      if (kMark) {
+        uint32_t reach = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          reach |= (band_reached(ra, rb, static_cast<float>(tx * TILE) + 0.5f,
+                                 static_cast<float>(ty * TILE + 4 * k) + 0.5f) ? 1u : 0u) << (kItemBits + k);
+        pv &= kItemMask | reach;
+        if (lane < kFwdBatch && base + lane < end) pair_marked[base + lane] = pv;
+      }
+      lds_put<kFwdBatch>(L, buf, lane, ra, rb, bl, pv);
+    };
+    lds_fetch(pair_item, crec, blue, imax, start + lane, lane < kFwdBatch && start + lane < end, pv, ra, rb, bl);
+    stage(0, start);
+    int buf = 0;
+    for (int base = start; base < end; base += kFwdBatch) {
+      if (!any_live(fy)) break;
+      const int nb = base + kFwdBatch;
+      lds_fetch(pair_item, crec, blue, imax, nb + lane, lane < kFwdBatch && nb + lane < end, pv, ra, rb, bl);
+      // batch length and first list position, kept scalar so that the step loop runs on the SALU
+      const int n = static_cast<int>(uniform(static_cast<uint32_t>(min(kFwdBatch, end - base))));
+      const int pos0 = static_cast<int>(uniform(static_cast<uint32_t>(base - start)));
+      for (int b = 0; b < n; ++b) {
+        const Rec r = lds_get<kFwdBatch>(L, buf, b);
+        const uint32_t reach = lds_pv<kFwdBatch>(L, buf, b) >> kItemBits;
+        fwd_step<PPL, STATS>(r, reach, pos0 + b, fx, fy, T, cr, cg, cb, nvis, n_used);
+      }
+      buf ^= 1;
+      stage(buf, nb);
+    }
+    if (STATS)   // every list entry up to and with the one that stopped the pixel
+#pragma unroll
+      for (int k = 0; k < PPL; ++k)
+        n_eval += !inside[k] ? 0u : static_cast<uint32_t>(nvis[k] + (fy[k] < kLiveBound ? 0 : 1));
+    if (STATS) add_stats(stats, n_eval, n_used);
+#pragma unroll
+    for (int k = 0; k < PPL; ++k)
+      if (inside[k]) store(px, py[k], T[k], cr[k], cg[k], cb[k], nvis[k]);
   }
 }
 
@@ -544,17 +623,17 @@ struct BwdPix {
 // alpha c + (1 - alpha) acc.  Only the projection S = sum_c dL/dC_c acc_c enters, so that scalar is
 // what the pixel carries: dL/dalpha = T_before (D_c - S) with D_c = sum_c dL/dC_c c_c, and S moves
 // to S + alpha (D_c - S).  dL/dpower = alpha dL/dalpha unless alpha was clamped.
+// Returns the wave sum that the lane is left with (see reduce_cols9, reduce_scatter9), 0 when no group is marked.
 template <int PPL, bool MARKED, bool COLS, bool STATS>
-__device__ __forceinline__ void bwd_step(const Rec& r, uint32_t pv, int j, float fx, BwdPix<PPL>& P, int lane,
-                                         int out_k, bool out_lane, float* __restrict__ grad2d, uint32_t& n_eval,
-                                         uint32_t& n_used) {
+__device__ __forceinline__ float bwd_step(const Rec& r, uint32_t groups, int j, float fx, BwdPix<PPL>& P, int lane,
+                                          uint32_t& n_eval, uint32_t& n_used) {
   if (STATS)
 #pragma unroll
     for (int k = 0; k < PPL; ++k) n_eval += j < P.nc[k] ? 1u : 0u;
-  // MARKED: the forward left in the pair value the lane groups it evaluated, a superset of those
+  // MARKED: groups holds the lane groups that the forward left marked, a superset of those
   // with a contributing pixel; each is handled wholly inside its own uniform branch.
-  const uint32_t groups = MARKED ? pv >> kItemBits : (1u << PPL) - 1u;
-  if (groups == 0) return;
+  if (!MARKED) groups = (1u << PPL) - 1u;
+  if (groups == 0) return 0.0f;
   const float dx = r.mx - fx;
   const float dx2 = dx * dx;
   const float u = fmaf(r.hA, dx2, r.lo);
@@ -589,78 +668,184 @@ __device__ __forceinline__ void bwd_step(const Rec& r, uint32_t pv, int j, float
     }
   }
   // (with marks the superset is tight enough that the test does not pay for itself)
-  if (!MARKED && !wave_any(anyc)) return;
-  float sum;
+  if (!MARKED && !wave_any(anyc)) return 0.0f;
   if constexpr (COLS) {
-    sum = reduce_cols9(s0, s1, s2, wr, wg, wb, dx, dx2, lane);
+    return reduce_cols9(s0, s1, s2, wr, wg, wb, dx, dx2, lane);
   } else {
     const float g[9] = {dx * s0, s1, dx2 * s0, dx * s1, s2, s0, wr, wg, wb};
-    sum = reduce_scatter9(g, lane);
+    return reduce_scatter9(g, lane);
   }
-  if (out_lane && sum != 0.0f) unsafeAtomicAdd(&grad2d[16 * static_cast<size_t>(pv & kItemMask) + out_k], sum);
 }
 
+// A split tile in the backward: its four bands are walked by the four waves of a block, in batches of 64 list
+// entries whose records the block stages once.  Each wave takes the entries marked for its band and leaves their
+// nine sums in LDS; the block then adds the bands' sums in a fixed order, so that an item's row gets one addition
+// per tile and value, as from one wave (fewer atomics, and no more spread between two runs).
+struct BandLists {
+  float4 a[64], b[64];
+  float2 c[64];              // blue, the item's bits
+  float4 sum[64 * 9];        // entry, value: a lane of the vector per band
+  int maxn[4];
+};
+
+template <bool STATS>
+__device__ __forceinline__ void bwd_walk_bands(BandLists& L, const uint32_t* __restrict__ pair_values, int start,
+                                               const float4* __restrict__ crec, const float* __restrict__ cblue,
+                                               int wave, int lane, float fx, BwdPix<1>& P, int out_k, bool out_lane,
+                                               float* __restrict__ grad2d, uint32_t& n_used) {
+  const int tid = wave * 64 + lane;
+  int maxn = P.nc[0];
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) maxn = max(maxn, __shfl_xor(maxn, d, 64));
+  if (lane == 0) L.maxn[wave] = maxn;
+  for (int i = tid; i < 64 * 9; i += 256) L.sum[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  __syncthreads();
+  const int band_n = __builtin_amdgcn_readfirstlane(maxn);
+  maxn = __builtin_amdgcn_readfirstlane(max(max(L.maxn[0], L.maxn[1]), max(L.maxn[2], L.maxn[3])));
+  // entry e of the batch that ends at position hi is position hi - e; the wave's first 16 lanes fetch a quarter of the batch
+  float4 ra, rb;
+  float bl = 0.0f;
+  uint32_t item = 0;
+  auto value = [&](int pos) { return pos >= 0 ? pair_values[start + pos] : 0u; };
+  auto fetch = [&](int hi) {
+    const int pos = hi - 16 * wave - lane;
+    if (lane < 16 && pos >= 0) {
+      item = pair_values[start + pos] & kItemMask;
+      ra = crec[2 * item];
+      rb = crec[2 * item + 1];
+      bl = cblue[item];
+    }
+  };
+  fetch(maxn - 1);
+  uint32_t pv = value(maxn - 1 - lane);
+  for (int hi = maxn - 1; hi >= 0; hi -= 64) {
+    if (lane < 16) {
+      const int e = 16 * wave + lane;
+      L.a[e] = ra;
+      L.b[e] = rb;
+      L.c[e] = make_float2(bl, __uint_as_float(item));
+    }
+    // the band's entries, without those behind the last one that any of its pixels took into account
+    uint64_t m = __ballot((pv >> (kItemBits + wave)) & 1u && hi - lane < band_n);
+    fetch(hi - 64);
+    pv = value(hi - 64 - lane);
+    __syncthreads();
+    while (m) {
+      const int e = __builtin_ctzll(m);
+      m &= m - 1;
+      const float4 a = L.a[e], b = L.b[e];
+      const Rec r{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w, L.c[e].x};
+      uint32_t unused = 0;
+      const float sum = bwd_step<1, false, true, STATS>(r, 1u, hi - e, fx, P, lane, unused, n_used);
+      if (out_lane && sum != 0.0f) reinterpret_cast<float*>(&L.sum[9 * e + out_k])[wave] = sum;
+    }
+    __syncthreads();
+    for (int i = tid; i < 64 * 9; i += 256) {
+      const float4 v = L.sum[i];
+      const float s = (v.x + v.y) + (v.z + v.w);
+      if (s != 0.0f) {
+        const int e = i / 9;
+        unsafeAtomicAdd(&grad2d[16 * static_cast<size_t>(__float_as_uint(L.c[e].y)) + (i - 9 * e)], s);
+      }
+      L.sum[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+    __syncthreads();   // the sums and items are read: the next batch may be staged
+  }
+}
+
+// Threads of a backward block: with 16x16 tiles four waves, which share a split tile or take a tile each.
+template <int TILE>
+constexpr int kBwdThreads = TILE == 16 ? 256 : TileCfg<TILE>::kThreads;
+
 template <int TILE, bool STATS, int LDSB>
-__global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_composite_bwd(
-    const DevView* __restrict__ views, int n_views, const uint2* __restrict__ ranges,
-    const uint32_t* __restrict__ tile_order,
-    const uint32_t* __restrict__ pair_values, const float* __restrict__ coef,
+__global__ __launch_bounds__(kBwdThreads<TILE>) void k_composite_bwd(
+    const DevView* __restrict__ views, int n_views, int n_tiles, const uint2* __restrict__ ranges,
+    const uint32_t* __restrict__ tile_order, const uint32_t* __restrict__ n_split,
+    const uint32_t* __restrict__ pair_item, const uint32_t* __restrict__ pair_marked,
+    const float* __restrict__ coef,
     const float* __restrict__ blue, const float* __restrict__ final_T, const int32_t* __restrict__ n_contrib,
     const float* __restrict__ dL_dimg, float* __restrict__ grad2d, int64_t n_items,
     unsigned long long* __restrict__ stats) {
   using C = TileCfg<TILE>;
   constexpr int PPL = C::kPPL;
   const int lane = static_cast<int>(threadIdx.x) & 63;
-  const int wave = static_cast<int>(threadIdx.x) >> 6;
-  const int tile = static_cast<int>(tile_order[blockIdx.x]);
+  const int block_wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int wave = TILE == 16 ? 0 : block_wave;   // of the tile's
+  // 16x16 tiles: the first n_split[1] tiles take a block each, the others a wave each
+  const int ns = TILE == 16 ? static_cast<int>(n_split[1]) : 0;
+  const int b = static_cast<int>(blockIdx.x);
+  const bool split = TILE == 16 && b < ns;
+  const int place = TILE != 16 || split ? b : ns + 4 * (b - ns) + block_wave;
+  if (place >= n_tiles) return;
+  const int tile = static_cast<int>(tile_order[place]);
   const DevView& v = views[find_view(views, n_views, tile)];
   const int local = tile - v.tile_offset;
   const int tx = local % v.tiles_x, ty = local / v.tiles_x;
   const int64_t HW = static_cast<int64_t>(v.width) * v.height;
-  BwdPix<PPL> P;
-  int maxn = 0;
   const int q0 = wave * (C::kPix / C::kWaves) + lane;
   const int px = tx * TILE + q0 % TILE;
   const float fx = static_cast<float>(px) + 0.5f;
-#pragma unroll
-  for (int k = 0; k < PPL; ++k) {
-    const int py = ty * TILE + (q0 + k * 64) / TILE;
-    const bool inside = px < v.width && py < v.height;
-    P.fy[k] = static_cast<float>(py) + 0.5f;
-    P.T[k] = 1.0f;
-    P.nc[k] = 0;
-    P.dr[k] = P.dg[k] = P.db[k] = 0.0f;
-    if (inside) {
+  auto load_pixel = [&](int py, float& fy, float& T, int& nc, float& dr, float& dg, float& db, float& S) {
+    fy = static_cast<float>(py) + 0.5f;
+    T = 1.0f;
+    nc = 0;
+    dr = dg = db = 0.0f;
+    if (px < v.width && py < v.height) {
       const int64_t pix = static_cast<int64_t>(py) * v.width + px;
-      P.T[k] = final_T[v.pixel_offset + pix];
-      P.nc[k] = n_contrib[v.pixel_offset + pix];
+      T = final_T[v.pixel_offset + pix];
+      nc = n_contrib[v.pixel_offset + pix];
       const float* g = dL_dimg + 3 * static_cast<int64_t>(v.pixel_offset);
-      P.dr[k] = g[pix];
-      P.dg[k] = g[HW + pix];
-      P.db[k] = g[2 * HW + pix];
+      dr = g[pix];
+      dg = g[HW + pix];
+      db = g[2 * HW + pix];
     }
-    P.S[k] = fmaf(P.dr[k], v.bg[0], fmaf(P.dg[k], v.bg[1], P.db[k] * v.bg[2]));
-    maxn = max(maxn, P.nc[k]);
-  }
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) maxn = max(maxn, __shfl_xor(maxn, d, 64));
-  maxn = __builtin_amdgcn_readfirstlane(maxn);
+    S = fmaf(dr, v.bg[0], fmaf(dg, v.bg[1], db * v.bg[2]));
+  };
   const int start = static_cast<int>(uniform(ranges[tile].x));
   // Lanes l, l + 16, l + 32, l + 48 share a pixel column when the tile is at most 16 wide.
   constexpr bool kCols = 16 % TILE == 0;
   const int out_k = kCols ? col_index(lane) : rs_index(lane & 15);
   const bool out_lane = kCols ? out_k >= 0 : lane < 16 && ((lane & 1) == 0 || lane == 1);
-  uint32_t n_eval = 0, n_used = 0;
-  // pair_values: the forward's marked copy with one wave per tile (marks of the groups it
-  // evaluated), else the sorted pair values.
-  constexpr bool kMarked = C::kWaves == 1;
   const float4* __restrict__ crec = reinterpret_cast<const float4*>(coef);
+  if constexpr (TILE == 16) {
+    if (split) {   // uniform for the block
+      __shared__ BandLists bands;
+      BwdPix<1> P;
+      load_pixel(ty * TILE + (lane + 64 * block_wave) / TILE, P.fy[0], P.T[0], P.nc[0], P.dr[0], P.dg[0], P.db[0],
+                 P.S[0]);
+      uint32_t n_used = 0;
+      bwd_walk_bands<STATS>(bands, pair_marked, start, crec, blue, block_wave, lane, fx, P, out_k, out_lane, grad2d,
+                            n_used);
+      if (STATS) add_stats(stats, static_cast<uint32_t>(P.nc[0]), n_used);
+      return;
+    }
+  }
+  BwdPix<PPL> P;
+  int maxn = 0;
+#pragma unroll
+  for (int k = 0; k < PPL; ++k) {
+    load_pixel(ty * TILE + (q0 + k * 64) / TILE, P.fy[k], P.T[k], P.nc[k], P.dr[k], P.dg[k], P.db[k], P.S[k]);
+    maxn = max(maxn, P.nc[k]);
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) maxn = max(maxn, __shfl_xor(maxn, d, 64));
+  maxn = __builtin_amdgcn_readfirstlane(maxn);
+  uint32_t n_eval = 0, n_used = 0;
+  // With 16x16 tiles the forward's marked copy (marks of the groups it evaluated); else the sorted pair values (every group
+  // marked; an 8x8 tile has one, which the projection has found within reach).
+  constexpr bool kMarked = TILE <= 16;
+  const uint32_t* __restrict__ pair_values = TILE == 16 ? pair_marked : pair_item;
   const uint32_t imax = n_items > 0 ? static_cast<uint32_t>(n_items - 1) : 0u;
+  auto step = [&](const Rec& r, uint32_t pv, int j) __attribute__((always_inline)) {
+    const float sum = bwd_step<PPL, kMarked, kCols, STATS>(r, pv >> kItemBits, j, fx, P, lane, n_eval, n_used);
+    if (out_lane && sum != 0.0f) unsafeAtomicAdd(&grad2d[16 * static_cast<size_t>(pv & kItemMask) + out_k], sum);
+  };
   if constexpr (LDSB > 0) {
     static_assert(C::kWaves == 1, "LDS batches are wave-private");
-    // The forward's LDS batches walked in reverse: the batch ending at list position hi holds
+    // LDS batches walked in reverse: the batch ending at list position hi holds
     // positions hi, hi - 1, ... in lanes 0, 1, ...
-    __shared__ LdsBatch<LDSB> L;
+    __shared__ LdsBatch<LDSB> batches[kBwdThreads<TILE> / 64];
+    LdsBatch<LDSB>& L = batches[TILE == 16 ? block_wave : 0];
     uint32_t pv;
     float4 ra, rb;
     float bl;
@@ -674,8 +859,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_composite_bwd(
       const int n = min(LDSB, hi + 1);
       for (int b = 0; b < n; ++b) {
         const Rec r = lds_get<LDSB>(L, buf, b);
-        bwd_step<PPL, kMarked, kCols, STATS>(r, lds_pv<LDSB>(L, buf, b), hi - b, fx, P, lane, out_k, out_lane,
-                                             grad2d, n_eval, n_used);
+        step(r, lds_pv<LDSB>(L, buf, b), hi - b);
       }
       buf ^= 1;
       lds_put<LDSB>(L, buf, lane, ra, rb, bl, pv);
@@ -692,88 +876,113 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_composite_bwd(
     wait_scalar_loads();
     R1 = load_rec_s(crec, blue, u1, imax);
     u2 = pair_values[start + max(j - 2, 0)];
-    bwd_step<PPL, kMarked, kCols, STATS>(R0, u0, j, fx, P, lane, out_k, out_lane, grad2d, n_eval, n_used);
+    step(R0, u0, j);
     if (j == 0) break;
     wait_scalar_loads();
     R2 = load_rec_s(crec, blue, u2, imax);
     u0 = pair_values[start + max(j - 3, 0)];
-    bwd_step<PPL, kMarked, kCols, STATS>(R1, u1, j - 1, fx, P, lane, out_k, out_lane, grad2d, n_eval, n_used);
+    step(R1, u1, j - 1);
     if (j == 1) break;
     wait_scalar_loads();
     R0 = load_rec_s(crec, blue, u0, imax);
     u1 = pair_values[start + max(j - 4, 0)];
-    bwd_step<PPL, kMarked, kCols, STATS>(R2, u2, j - 2, fx, P, lane, out_k, out_lane, grad2d, n_eval, n_used);
+    step(R2, u2, j - 2);
   }
   }
   if (STATS) add_stats(stats, n_eval, n_used);
 }
 
-template <int TILE, int LDSB>
-static vbm_status launch_fwd_t(const DevView* views, int n_views, int64_t n_tiles, const uint2* ranges,
-                               const uint32_t* tile_order, const uint32_t* pair_item, int64_t n_pairs,
-                               uint32_t* pair_marked, const float* coef, const float* blue, int64_t n_items,
-                               float* image, float* final_T, int32_t* n_contrib, unsigned long long* stats,
+// Before the backward: clears the gradient rows (the first fill_blocks blocks, 16-byte stores), and writes the
+// marked copy of the tiles that the forward has split, a block each, from their mark planes.
+__global__ __launch_bounds__(256) void k_prepare_bwd(uint4* __restrict__ grad, int64_t n4, int fill_blocks,
+                                                     const uint32_t* __restrict__ n_split,
+                                                     const uint32_t* __restrict__ tile_order,
+                                                     const uint2* __restrict__ ranges,
+                                                     const uint32_t* __restrict__ pair_item,
+                                                     const uint32_t* __restrict__ planes,
+                                                     uint32_t* __restrict__ pair_marked) {
+  const int b = static_cast<int>(blockIdx.x);
+  if (b < fill_blocks) {
+    for (int64_t i = static_cast<int64_t>(b) * 256 + threadIdx.x; i < n4; i += static_cast<int64_t>(fill_blocks) * 256)
+      grad[i] = make_uint4(0u, 0u, 0u, 0u);
+    return;
+  }
+  if (b - fill_blocks >= static_cast<int>(*n_split)) return;
+  const uint2 r = ranges[tile_order[b - fill_blocks]];
+  for (uint32_t j = threadIdx.x; j < r.y - r.x; j += 256) {
+    const uint32_t* q = planes + r.x + 8u * (j >> 6) + ((j >> 5) & 1u);
+    uint32_t marks = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) marks |= ((q[2 * k] >> (j & 31u)) & 1u) << k;
+    pair_marked[r.x + j] = (pair_item[r.x + j] & kItemMask) | (marks << kItemBits);
+  }
+}
+
+vbm_status launch_prepare_bwd(int tile, const CompositeArgs& a, float* grad2d, hipStream_t s) {
+  const int64_t n4 = 4 * a.n_items;   // 16-float rows
+  const int64_t want = ceil_div(n4, 256);
+  const int fill_blocks = static_cast<int>(want < 8192 ? want : 8192);
+  const int tiles = tile == 16 ? static_cast<int>(a.n_tiles < kMaxSplit ? a.n_tiles : kMaxSplit) : 0;
+  if (fill_blocks + tiles == 0) return VBM_OK;
+  hipLaunchKernelGGL(k_prepare_bwd, dim3(static_cast<unsigned>(fill_blocks + tiles)), dim3(256), 0, s,
+                     reinterpret_cast<uint4*>(grad2d), n4, fill_blocks, a.n_split, a.tile_order, a.ranges,
+                     a.pair_item, a.planes, a.pair_marked);
+  VBM_LAUNCH_CHECK("prepare_bwd");
+  return VBM_OK;
+}
+
+template <int TILE>
+static unsigned wave_grid(const CompositeArgs& a) {
+  // with 16x16 tiles room for three more waves per tile that can be split (those left over do nothing)
+  return static_cast<unsigned>(a.n_tiles + (TILE == 16 ? 3 * (a.n_tiles < kMaxSplit ? a.n_tiles : kMaxSplit) : 0));
+}
+
+template <int TILE>
+static vbm_status launch_fwd_t(const CompositeArgs& a, float* image, float* final_T, int32_t* n_contrib,
                                hipStream_t s) {
-  const dim3 block(TileCfg<TILE>::kThreads);
-  if (stats)
-    hipLaunchKernelGGL((k_composite_fwd<TILE, true, LDSB>), dim3(n_tiles), block, 0, s, views, n_views, ranges,
-                       tile_order, pair_item, n_pairs, pair_marked, coef, blue, n_items, image, final_T, n_contrib,
-                       stats);
+  const dim3 grid(wave_grid<TILE>(a)), block(TileCfg<TILE>::kThreads);
+  if (a.stats)
+    hipLaunchKernelGGL((k_composite_fwd<TILE, true>), grid, block, 0, s, a.views, a.n_views,
+                       static_cast<int>(a.n_tiles), a.ranges, a.tile_order, a.n_split, a.pair_item, a.pair_marked,
+                       a.planes, a.coef, a.blue, a.n_items, image, final_T, n_contrib, a.stats);
   else
-    hipLaunchKernelGGL((k_composite_fwd<TILE, false, LDSB>), dim3(n_tiles), block, 0, s, views, n_views, ranges,
-                       tile_order, pair_item, n_pairs, pair_marked, coef, blue, n_items, image, final_T, n_contrib,
-                       stats);
+    hipLaunchKernelGGL((k_composite_fwd<TILE, false>), grid, block, 0, s, a.views, a.n_views,
+                       static_cast<int>(a.n_tiles), a.ranges, a.tile_order, a.n_split, a.pair_item, a.pair_marked,
+                       a.planes, a.coef, a.blue, a.n_items, image, final_T, n_contrib, a.stats);
   VBM_LAUNCH_CHECK("composite_fwd");
   return VBM_OK;
 }
 
 template <int TILE, int LDSB>
-static vbm_status launch_bwd_t(const DevView* views, int n_views, int64_t n_tiles, const uint2* ranges,
-                               const uint32_t* tile_order, const uint32_t* pair_item, const uint32_t* pair_marked,
-                               const float* coef, const float* blue, const float* final_T, const int32_t* n_contrib,
-                               const float* dL_dimg, float* grad2d, int64_t n_items, unsigned long long* stats,
-                               hipStream_t s) {
-  const dim3 block(TileCfg<TILE>::kThreads);
-  // one wave per tile: the forward's marked copy; otherwise the sorted pair values
-  const uint32_t* values = TileCfg<TILE>::kWaves == 1 ? pair_marked : pair_item;
-  if (stats)
-    hipLaunchKernelGGL((k_composite_bwd<TILE, true, LDSB>), dim3(n_tiles), block, 0, s, views, n_views, ranges,
-                       tile_order, values, coef, blue, final_T, n_contrib, dL_dimg, grad2d, n_items, stats);
+static vbm_status launch_bwd_t(const CompositeArgs& a, const float* final_T, const int32_t* n_contrib,
+                               const float* dL_dimg, float* grad2d, hipStream_t s) {
+  // with 16x16 tiles a block per split tile and a wave for each of the others (blocks left over do nothing)
+  const int64_t split = a.n_tiles < kMaxSplit ? a.n_tiles : kMaxSplit;
+  const dim3 grid(static_cast<unsigned>(TILE == 16 ? split + ceil_div(a.n_tiles, 4) : a.n_tiles)), block(kBwdThreads<TILE>);
+  if (a.stats)
+    hipLaunchKernelGGL((k_composite_bwd<TILE, true, LDSB>), grid, block, 0, s, a.views, a.n_views,
+                       static_cast<int>(a.n_tiles), a.ranges, a.tile_order, a.n_split, a.pair_item, a.pair_marked,
+                       a.coef, a.blue, final_T, n_contrib, dL_dimg, grad2d, a.n_items, a.stats);
   else
-    hipLaunchKernelGGL((k_composite_bwd<TILE, false, LDSB>), dim3(n_tiles), block, 0, s, views, n_views, ranges,
-                       tile_order, values, coef, blue, final_T, n_contrib, dL_dimg, grad2d, n_items, stats);
+    hipLaunchKernelGGL((k_composite_bwd<TILE, false, LDSB>), grid, block, 0, s, a.views, a.n_views,
+                       static_cast<int>(a.n_tiles), a.ranges, a.tile_order, a.n_split, a.pair_item, a.pair_marked,
+                       a.coef, a.blue, final_T, n_contrib, dL_dimg, grad2d, a.n_items, a.stats);
   VBM_LAUNCH_CHECK("composite_bwd");
   return VBM_OK;
 }
 
-vbm_status launch_composite_fwd(int tile, int lds_batch, const DevView* views, int n_views, int64_t n_tiles,
-                                const uint2* ranges, const uint32_t* tile_order, const uint32_t* pair_item,
-                                int64_t n_pairs, uint32_t* pair_marked, const float* coef, const float* blue,
-                                int64_t n_items, float* image, float* final_T, int32_t* n_contrib,
-                                unsigned long long* stats, hipStream_t s) {
-#define VBM_FWD(T, B)                                                                                              \
-  return launch_fwd_t<T, B>(views, n_views, n_tiles, ranges, tile_order, pair_item, n_pairs, pair_marked, coef,   \
-                            blue, n_items, image, final_T, n_contrib, stats, s)
-  if (tile == 8 && lds_batch == 0) VBM_FWD(8, 0);
-  if (tile == 8 && lds_batch == 32) VBM_FWD(8, 32);
-  if (tile == 8 && lds_batch == 64) VBM_FWD(8, 64);
-  if (tile == 16 && lds_batch == 0) VBM_FWD(16, 0);
-  if (tile == 16 && lds_batch == 32) VBM_FWD(16, 32);
-  if (tile == 16 && lds_batch == 64) VBM_FWD(16, 64);
-  if (tile == 32 && lds_batch == 0) VBM_FWD(32, 0);
-#undef VBM_FWD
-  set_error("unsupported tile size %d with LDS batch %d", tile, lds_batch);
+vbm_status launch_composite_fwd(int tile, const CompositeArgs& a, float* image, float* final_T, int32_t* n_contrib,
+                                hipStream_t s) {
+  if (tile == 8) return launch_fwd_t<8>(a, image, final_T, n_contrib, s);
+  if (tile == 16) return launch_fwd_t<16>(a, image, final_T, n_contrib, s);
+  if (tile == 32) return launch_fwd_t<32>(a, image, final_T, n_contrib, s);
+  set_error("unsupported tile size %d", tile);
   return VBM_ERR_UNSUPPORTED;
 }
 
-vbm_status launch_composite_bwd(int tile, int lds_batch, const DevView* views, int n_views, int64_t n_tiles,
-                                const uint2* ranges, const uint32_t* tile_order, const uint32_t* pair_item,
-                                const uint32_t* pair_marked, const float* coef, const float* blue,
-                                const float* final_T, const int32_t* n_contrib, const float* dL_dimg, float* grad2d,
-                                int64_t n_items, unsigned long long* stats, hipStream_t s) {
-#define VBM_BWD(T, B)                                                                                              \
-  return launch_bwd_t<T, B>(views, n_views, n_tiles, ranges, tile_order, pair_item, pair_marked, coef, blue,       \
-                            final_T, n_contrib, dL_dimg, grad2d, n_items, stats, s)
+vbm_status launch_composite_bwd(int tile, int lds_batch, const CompositeArgs& a, const float* final_T,
+                                const int32_t* n_contrib, const float* dL_dimg, float* grad2d, hipStream_t s) {
+#define VBM_BWD(T, B) return launch_bwd_t<T, B>(a, final_T, n_contrib, dL_dimg, grad2d, s)
   if (tile == 8 && lds_batch == 0) VBM_BWD(8, 0);
   if (tile == 8 && lds_batch == 32) VBM_BWD(8, 32);
   if (tile == 8 && lds_batch == 64) VBM_BWD(8, 64);

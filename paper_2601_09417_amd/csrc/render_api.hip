@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "common.h"
+#include "composite.h"
 
 namespace vbm {
 
@@ -26,16 +27,6 @@ __global__ void k_emit(const DevView*, int, const uint32_t*, const uint4*, const
                        uint32_t*, uint32_t*);
 __global__ void k_project_bwd(const DevView*, int, const DevScene*, int, vbm_gaussians_c, float*, const float4*,
                               int64_t, const uint32_t*, vbm_gaussians, int, int64_t);
-vbm_status launch_composite_fwd(int tile, int lds_batch, const DevView* views, int n_views, int64_t n_tiles,
-                                const uint2* ranges, const uint32_t* tile_order, const uint32_t* pair_item,
-                                int64_t n_pairs, uint32_t* pair_marked, const float* coef, const float* blue,
-                                int64_t n_items, float* image, float* final_T, int32_t* n_contrib,
-                                unsigned long long* stats, hipStream_t s);
-vbm_status launch_composite_bwd(int tile, int lds_batch, const DevView* views, int n_views, int64_t n_tiles,
-                                const uint2* ranges, const uint32_t* tile_order, const uint32_t* pair_item,
-                                const uint32_t* pair_marked, const float* coef, const float* blue,
-                                const float* final_T, const int32_t* n_contrib, const float* dL_dimg, float* grad2d,
-                                int64_t n_items, unsigned long long* stats, hipStream_t s);
 
 namespace {
 
@@ -175,6 +166,26 @@ unsigned long long* g_stats = nullptr;  // device [4]: fwd evaluated, fwd contri
 vbm_status record(int which, hipStream_t s) {
   if (!g_prof[which]) return VBM_OK;
   return hip_check(hipEventRecord(g_prof[which], s), "profile event record");
+}
+
+// The sorted pair values stay in slot 0; the forward's marked copy and mark planes go to the idle ping-pong
+// buffers.
+CompositeArgs composite_args(const vbm_plan* p, const void* view_table, void* ws, unsigned long long* stats) {
+  CompositeArgs a;
+  a.views = static_cast<const DevView*>(view_table);
+  a.n_views = p->n_views;
+  a.n_tiles = p->n_tiles;
+  a.ranges = region<uint2>(p, ws, R_RANGES);
+  a.tile_order = tile_order(p, ws);
+  a.n_split = region<uint32_t>(p, ws, R_COUNTERS) + kSplitCounter;
+  a.pair_item = region<uint32_t>(p, ws, R_PITEM);
+  a.pair_marked = region<uint32_t>(p, ws, R_PITEM_ALT);
+  a.planes = region<uint32_t>(p, ws, R_PTILE_ALT);
+  a.coef = region<float>(p, ws, R_COEF);
+  a.blue = region<float>(p, ws, R_BLUE);
+  a.n_items = p->n_items;
+  a.stats = stats;
+  return a;
 }
 
 }  // namespace
@@ -380,13 +391,12 @@ extern "C" vbm_status vbm_render_fwd(const vbm_plan* p, const void* view_table, 
   lists.keys = region<uint32_t>(p, ws, R_TORDER);
   lists.counters = counters;
   lists.status = status;
+  lists.split_fwd = p->n_tiles <= kSplitAllTiles ? 1u << 30 : kSplitForward;
+  lists.split_bwd = kSplitBackward;
   VBM_TRY(sort_pairs_by_tile(pt, pi, pfirst, cap, pair_n, pair_n_dev, p->tile_key_bits, p->sort_bits, lists, scratch,
                              s));
   VBM_TRY(record(0, s));
-  // the sorted pair values stay in pi[0]; the forward's marked copy goes to the idle ping-pong buffer
-  VBM_TRY(launch_composite_fwd(p->tile, p->lds_batch, views, p->n_views, p->n_tiles, ranges, tile_order(p, ws), pi[0],
-                               cap, pi[1],
-                               reinterpret_cast<const float*>(coef), blue, I, image, final_T, n_contrib, g_stats, s));
+  VBM_TRY(launch_composite_fwd(p->tile, composite_args(p, view_table, ws, g_stats), image, final_T, n_contrib, s));
   VBM_TRY(record(1, s));
   return VBM_OK;
 }
@@ -412,13 +422,10 @@ extern "C" vbm_status vbm_render_bwd(const vbm_plan* p, const void* view_table, 
       reinterpret_cast<const DevScene*>(static_cast<const char*>(view_table) + sizeof(DevView) * p->n_views);
   const int64_t I = p->n_items;
   float* grad2d = region<float>(p, ws, R_GRAD2D);
-  VBM_TRY(fill_u32(reinterpret_cast<uint32_t*>(grad2d), 0u, 16 * I, s));
+  const CompositeArgs args = composite_args(p, view_table, ws, g_stats ? g_stats + 2 : nullptr);
+  VBM_TRY(launch_prepare_bwd(p->tile, args, grad2d, s));
   VBM_TRY(record(2, s));
-  VBM_TRY(launch_composite_bwd(p->tile, p->lds_batch_bwd, views, p->n_views, p->n_tiles, region<uint2>(p, ws, R_RANGES),
-                               tile_order(p, ws),
-                               region<uint32_t>(p, ws, R_PITEM), region<uint32_t>(p, ws, R_PITEM_ALT),
-                               region<float>(p, ws, R_COEF), region<float>(p, ws, R_BLUE), final_T, n_contrib, dL_dimg,
-                               grad2d, I, g_stats ? g_stats + 2 : nullptr, s));
+  VBM_TRY(launch_composite_bwd(p->tile, p->lds_batch_bwd, args, final_T, n_contrib, dL_dimg, grad2d, s));
   VBM_TRY(record(3, s));
   if (p->n_gaussians > 0) {
     hipLaunchKernelGGL(k_project_bwd, dim3(ceil_div(p->n_gaussians, 256)), dim3(256), 0, s, views, p->n_views, scenes,

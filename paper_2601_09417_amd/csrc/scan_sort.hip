@@ -288,6 +288,18 @@ __global__ __launch_bounds__(kUpThreads) void k_radix_upsweep(const uint32_t* __
   }
 }
 
+// Coarse length key of a tile's list: the longest first, one step per 8 entries, lists of 2040 or more share
+// the first.
+__device__ __forceinline__ uint32_t length_key(uint2 r) { return 255u - min(255u, (r.y - r.x) >> 3); }
+
+// The length key below which a tile's list is composited by four waves: lists of kSplitLeast entries or more,
+// and of pairs / share or more (TileLists says which shares).
+constexpr uint32_t kSplitLeast = 16;
+__device__ __forceinline__ uint32_t split_key(uint32_t pairs, uint32_t share) {
+  const uint32_t steps = max(kSplitLeast, pairs / share) >> 3;   // lists of 8 steps entries or more
+  return steps > 255u ? 0u : 256u - steps;
+}
+
 // One stable pass over tiles of NT x 16 keys.  Wave w of a tile owns keys [1024 w, 1024 w + 1024)
 // and ranks them in 16 rounds of 64 against its own LDS digit counters: a lane's rank among the
 // round's equal digits comes from ballots, and the wave's LDS operations complete in issue order,
@@ -299,14 +311,18 @@ __global__ __launch_bounds__(kUpThreads) void k_radix_upsweep(const uint32_t* __
 // kRanges: the last pass of the pair sort.  Its input is in order of the lower digits, so the partitioned
 // tile is in order of the whole key and equal keys are neighbours; their first and last places go
 // to ranges[key] as (~first, last + 1), both by maximum from 0, since a key's run can span tiles.
-template <int NT, bool kSparse, bool kRanges>
+// kOrder: the tile order's pass (sparse); it also writes the number of split tiles.
+enum SweepKind { kPlainPass, kSparsePass, kRangesPass, kOrderPass };
+template <int NT, SweepKind kKind>
 __global__ __launch_bounds__(NT) void k_radix_onesweep(const uint32_t* __restrict__ kin,
                                                        const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
                                                        uint32_t* __restrict__ vout,
                                                        const uint32_t* __restrict__ totals,
                                                        uint32_t* __restrict__ status, int64_t n_max,
                                                        const uint32_t* n_dev, int shift, int bits,
-                                                       uint32_t* __restrict__ count_out, uint2* __restrict__ ranges) {
+                                                       uint32_t* __restrict__ count_out, uint2* __restrict__ ranges,
+                                                       TileLists lists) {
+  constexpr bool kSparse = kKind == kSparsePass || kKind == kOrderPass, kRanges = kKind == kRangesPass;
   constexpr int CH = NT * kItems;          // keys per tile
   constexpr int NW = NT / 64;
   constexpr int kPerWave = CH / NW;
@@ -375,7 +391,14 @@ __global__ __launch_bounds__(NT) void k_radix_onesweep(const uint32_t* __restric
     // keys of lower digits in the whole input: the exclusive scan of the digit totals
     uint32_t all;
     const uint32_t below = block_excl_scan_n<NT>(has ? totals[threadIdx.x] : 0u, &all);
-    if (kSparse && tile == 0 && threadIdx.x == 0) *count_out = all;
+    if (kKind == kSparsePass && tile == 0 && threadIdx.x == 0) *count_out = all;
+    if (kKind == kOrderPass && tile == 0) {
+      uint32_t* counters = lists.counters;
+      // tiles with a lower key are split
+      const uint32_t n_split = min(below, static_cast<uint32_t>(kMaxSplit));
+      if (threadIdx.x == split_key(counters[1], lists.split_fwd)) counters[kSplitCounter] = n_split;
+      if (threadIdx.x == split_key(counters[1], lists.split_bwd)) counters[kSplitCounter + 1] = n_split;
+    }
     if (has) {
       uint32_t* mine = status + tile * radix + threadIdx.x;
       uint32_t excl = 0;
@@ -461,10 +484,6 @@ __global__ __launch_bounds__(NT) void k_radix_onesweep(const uint32_t* __restric
 constexpr int kBlockSortThreads = 1024;
 constexpr int kBlockSortItems = static_cast<int>(kBlockSort / kBlockSortThreads);
 constexpr int kBlockSortWaves = kBlockSortThreads / 64;
-
-// Coarse length key of a tile's list: the longest first, one step per 8 entries, lists of 2040 or more share
-// the first.
-__device__ __forceinline__ uint32_t length_key(uint2 r) { return 255u - min(255u, (r.y - r.x) >> 3); }
 
 __device__ __forceinline__ void write_status(const uint32_t* __restrict__ counters, int32_t* __restrict__ status) {
   status[0] = static_cast<int32_t>(counters[2]);
@@ -599,7 +618,13 @@ __global__ __launch_bounds__(kBlockSortThreads) void k_sort_block(const uint32_t
 #pragma unroll
     for (int r = 0; r < kBlockSortItems; ++r)
       if (r < rounds && digit[r] < 256u) lists.order[slot[r]] = static_cast<uint32_t>((w * rounds + r) * 64 + lane);
-    if (threadIdx.x == 0) write_status(lists.counters, lists.status);
+    if (threadIdx.x == 0) {
+      // the first wave's base of a length key is the key's: the tiles with a lower one
+      const uint32_t pairs = lists.counters[1], most = kMaxSplit;
+      lists.counters[kSplitCounter] = min(s_cnt[0][split_key(pairs, lists.split_fwd)], most);
+      lists.counters[kSplitCounter + 1] = min(s_cnt[0][split_key(pairs, lists.split_bwd)], most);
+      write_status(lists.counters, lists.status);
+    }
   }
 }
 
@@ -724,13 +749,13 @@ vbm_status sweep(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, int64_t
     const int shift = p * digit_bits;
     const int bits = (end_bit - shift) < digit_bits ? (end_bit - shift) : digit_bits;
     if (ranges && p == passes - 1)
-      hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, false, true>), grid, dim3(kSweepThreads), 0, s, k0, v0, k1,
+      hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, kRangesPass>), grid, dim3(kSweepThreads), 0, s, k0, v0, k1,
                          v1, tot + p * 256, status + p * L.nb * L.radix, n_max, n_dev, shift, bits,
-                         static_cast<uint32_t*>(nullptr), ranges);
+                         static_cast<uint32_t*>(nullptr), ranges, TileLists());
     else
-      hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, false, false>), grid, dim3(kSweepThreads), 0, s, k0, v0, k1,
+      hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, kPlainPass>), grid, dim3(kSweepThreads), 0, s, k0, v0, k1,
                          v1, tot + p * 256, status + p * L.nb * L.radix, n_max, n_dev, shift, bits,
-                         static_cast<uint32_t*>(nullptr), static_cast<uint2*>(nullptr));
+                         static_cast<uint32_t*>(nullptr), static_cast<uint2*>(nullptr), TileLists());
     VBM_LAUNCH_CHECK("radix_onesweep");
     std::swap(k0, k1);
     std::swap(v0, v1);
@@ -768,10 +793,10 @@ vbm_status radix_sort_sparse(const uint32_t* keys, int64_t n, uint32_t* k0, uint
                      static_cast<const uint32_t*>(nullptr), end_bit, digit_bits, passes, tot, status,
                      static_cast<int64_t>(passes) * L.nb * L.radix);
   VBM_LAUNCH_CHECK("radix_upsweep");
-  hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, true, false>), dim3(ceil_div(n, kSweepThreads * kItems)),
+  hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, kSparsePass>), dim3(ceil_div(n, kSweepThreads * kItems)),
                      dim3(kSweepThreads), 0, s, keys, static_cast<const uint32_t*>(nullptr), k0, v0, tot, status, n,
                      static_cast<const uint32_t*>(nullptr), 0, end_bit < digit_bits ? end_bit : digit_bits, count_dev,
-                     static_cast<uint2*>(nullptr));
+                     static_cast<uint2*>(nullptr), TileLists());
   VBM_LAUNCH_CHECK("radix_onesweep");
   return sweep(k0, v0, k1, v1, n, count_dev, end_bit, digit_bits, 1, L, base, nullptr, s);
 }
@@ -811,10 +836,11 @@ vbm_status sort_pairs_by_tile(uint32_t* const k[2], uint32_t* const v[2], int fi
   hipLaunchKernelGGL(k_tile_keys, dim3(static_cast<unsigned>(ceil_div(NT, 256))), dim3(256), 0, s, lists, capacity,
                      end_bit == 0 ? 1 : 0, lists.keys, hist, look, L.nb * L.radix);
   VBM_LAUNCH_CHECK("tile_keys");
-  hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, true, false>),
+  hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, kOrderPass>),
                      dim3(static_cast<unsigned>(ceil_div(NT, kSweepThreads * kItems))), dim3(kSweepThreads), 0, s,
                      lists.keys, static_cast<const uint32_t*>(nullptr), lists.keys + NT, lists.order, hist, look, NT,
-                     static_cast<const uint32_t*>(nullptr), 0, 8, hist + 256, static_cast<uint2*>(nullptr));
+                     static_cast<const uint32_t*>(nullptr), 0, 8, static_cast<uint32_t*>(nullptr), static_cast<uint2*>(nullptr),
+                     lists);
   VBM_LAUNCH_CHECK("tile_order");
   return VBM_OK;
 }

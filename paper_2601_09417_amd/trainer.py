@@ -228,8 +228,8 @@ def render_images(P: torch.Tensor, cams, scene_offsets=None, view_scene=None, ti
 
 
 # (tile edge, tile-sort digit width, LDS batch depth of the forward and of the backward compositing
-# list walk; 0 = scalar cache), in order of preference: the tuner keeps the first one within
-# TUNE_MARGIN of the fastest
+# list walk; 0 = scalar cache, in the backward only: the forward stages its lists in LDS whatever the
+# value), in order of preference: the tuner keeps the first one within TUNE_MARGIN of the fastest
 TUNE_CANDIDATES = ((16, 8, 0, 0), (16, 4, 0, 0), (8, 8, 0, 0), (32, 8, 0, 0), (16, 8, 32, 0), (16, 8, 64, 0),
                    (16, 8, 32, 32))
 TUNE_MARGIN = 0.01

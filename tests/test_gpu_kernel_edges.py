@@ -5,10 +5,11 @@ import pytest
 import torch
 
 import vbm_inputs as vi
-from oracle import binning
+from oracle import binning, render
 from oracle import dwt as odwt
 from oracle import tf as otf
-from tests.gpu_common import ITEM_MASK, dev, say, to_dev
+from tests.gpu_common import (GRAD_TOL, IMG_TOL, ITEM_MASK, ROWS, dev, flat, group_error, image_error, masked_dL, say,
+                              to_dev)
 
 pytestmark = pytest.mark.gpu
 
@@ -85,3 +86,61 @@ def test_pair_lists_at_block_edges(n, views, W, H, tile, bits, opacity, log_scal
         rp = api.plan_batch(cams, [0, n], tile=tile, sort_bits=bits, pair_capacity=total - 1)
         out = api.render_fwd(rp, to_dev(gs))
         assert out.status.tolist()[:2] == [1, total]
+
+
+# List lengths around what the compositing walks count in: 16 entries (shorter lists are not shared by four waves),
+# batches of 64 and of 32, closed-up batches that are no multiple of four; faint lists that are walked to the end and dense
+# ones whose pixels stop inside a batch; an image that ends inside a band.
+@pytest.mark.parametrize("n,H,tile,opacity,log_scale", [
+    (15, 16, 16, (0.2, 0.6), -2.0), (16, 16, 16, (0.2, 0.6), -2.0), (17, 13, 16, (0.9, 1.0), -1.5),
+    (33, 16, 8, (0.2, 0.6), -2.0), (64, 16, 16, (0.2, 0.6), -2.0), (65, 10, 16, (0.02, 0.1), -2.0),
+    (130, 16, 16, (0.5, 1.0), -1.6), (200, 16, 32, (0.5, 1.0), -1.6), (400, 16, 16, (0.01, 0.05), -2.6),
+    (400, 16, 8, (0.5, 1.0), -2.0)])
+def test_compositing_walks_at_batch_edges(n, H, tile, opacity, log_scale):
+    api = _api()
+    say(f"walks n={n} 24x{H} tile={tile} opacity {opacity} log scale {log_scale}")
+    gs = vi.random_gaussians(n, 71 + n, log_scale_mean=log_scale, opacity_range=opacity)
+    cams = vi.orbit_cameras(1, 24, H, azimuth0=0.9)
+    P = to_dev(gs)
+    rp = api.plan_batch(cams, [0, n], tile=tile, pair_capacity=1 << 16)
+    batch = render.Batch(gs, cams, tile)
+    ref = render.render_forward(batch)
+    dL = masked_dL(cams, [r["flagged"] for r in ref], seed=n)
+    g_ref, _ = render.render_backward(batch, dL)
+    for _ in range(2):
+        out = api.render_fwd(rp, P)
+        assert image_error(api.split_views(out.image, cams)[0].cpu().numpy(), ref[0]["image"],
+                           ref[0]["flagged"]) <= IMG_TOL
+        ok = ~ref[0]["flagged"]
+        nc = out.n_contrib.cpu().numpy().reshape(H, 24)
+        assert np.array_equal(nc[ok], ref[0]["n_visited"][ok])
+        G = api.render_bwd(rp, P, flat(dL), out).cpu().numpy()
+        for name, rows in ROWS.items():
+            assert group_error(G[rows], g_ref[name].reshape(rows.stop - rows.start, -1)) <= GRAD_TOL, name
+
+
+def test_counters_agree_between_walks():
+    """The evaluation counters count list entries up to a pixel's stop and contributions; they do not depend on how
+    a list is walked: 16x16 tiles shared by four waves (few tiles), 8x8 and 32x32 tiles see the same contributions
+    (opacities up to 0.3: the reach of alpha >= 1/255 stays within three sigma, so the tilings list the same)."""
+    import ctypes
+
+    from paper_2601_09417_amd import _lib as L
+    api = _api()
+    gs = vi.random_gaussians(3000, 5, log_scale_mean=-2.6, opacity_range=(0.05, 0.3))
+    cams = vi.orbit_cameras(2, 131, 77)
+    used = []
+    for tile in (8, 16, 32):
+        rp = api.plan_batch(cams, [0, gs.n], tile=tile, pair_capacity=1 << 18)
+        c = torch.zeros(4, dtype=torch.int64, device=dev())
+        L.check(L.load().vbm_profile_counters(ctypes.c_void_p(c.data_ptr())), "vbm_profile_counters")
+        try:
+            out = api.render_fwd(rp, to_dev(gs))
+            api.render_bwd(rp, to_dev(gs), torch.ones_like(out.image), out)
+            torch.cuda.synchronize()
+        finally:
+            L.load().vbm_profile_counters(None)
+        ev_f, us_f, ev_b, us_b = c.tolist()
+        assert us_f == us_b and ev_b == int(out.n_contrib.sum()) and ev_f >= ev_b
+        used.append(us_f)
+    assert used[0] == used[1] == used[2] > 0
