@@ -7,6 +7,7 @@ import torch
 import vbm_inputs as vi
 from oracle import binning, render
 from oracle import dwt as odwt
+from oracle import select as oselect
 from oracle import tf as otf
 from tests.gpu_common import (GRAD_TOL, IMG_TOL, ITEM_MASK, ROWS, dev, flat, group_error, image_error, masked_dL, say,
                               to_dev)
@@ -144,3 +145,44 @@ def test_counters_agree_between_walks():
         assert us_f == us_b and ev_b == int(out.n_contrib.sum()) and ev_f >= ev_b
         used.append(us_f)
     assert used[0] == used[1] == used[2] > 0
+
+
+# The selection's candidate pass: grids below, at and above its 4096-location regions and the size from which a sample
+# bounds the candidates; K of 1, of everything and between; planes that start on a 4-byte boundary only; a sample that
+# misleads (only the sampled locations are large, so the bound leaves too few); ties at the K-th key; NaN and infinities.
+@pytest.mark.parametrize("G,K,kind", [
+    (4, 1, "plain"), (16, 4096, "plain"), (18, 1000, "odd"), (64, 5000, "plain"), (66, 1, "plain"), (66, 20000, "odd"),
+    (72, 72 ** 3, "plain"), (96, 50000, "mislead"), (96, 300000, "ties"), (96, 2000, "special")])
+def test_selection_candidates(G, K, kind):
+    api = _api()
+    say(f"selection G={G} K={K} {kind}")
+    M = G ** 3
+    rng = np.random.default_rng(G + K)
+    c = (rng.normal(size=(4, M)) * np.exp(rng.normal(size=M))).astype(np.float32)
+    if kind == "mislead":
+        c *= np.where(np.arange(M) % 2048 < 16, 100.0, 1.0).astype(np.float32)
+    if kind == "ties":
+        c = np.round(c).astype(np.float32)
+    if kind == "special":
+        c[0, 7::5000] = np.inf
+        c[2, 11::9000] = np.nan
+    flat_c = torch.empty(4 * M + 1, device=dev())
+    off = 1 if kind == "odd" else 0
+    x = flat_c[off:off + 4 * M].view(4, M)
+    x.copy_(torch.from_numpy(c))
+    bank = np.zeros((8, 12), np.float32)
+    bank[:, 0] = 1.0
+    bank[:, 4:8] = 1.0
+    P, kept = api.build_gaussians(x, G, 1, bank, K, s_mode="none")
+    kept = kept.cpu().numpy()
+    if kind == "special":
+        # key order of the bit patterns: NaN above infinity above the finite keys
+        with np.errstate(invalid="ignore"):
+            v = np.sqrt((((c[0] * c[0] + c[1] * c[1]) + c[2] * c[2]) + c[3] * c[3]).astype(np.float64)).astype(np.float32)
+        order = np.lexsort((np.arange(M), -np.nan_to_num(v, nan=np.inf).astype(np.float64), ~np.isnan(v)))
+        ref = np.sort(order[:K])
+    else:
+        ref = oselect.topk(c, K)
+    assert np.array_equal(kept, ref)
+    ok = np.isfinite(c[3][ref])
+    assert np.array_equal(P[10].cpu().numpy()[ok], np.clip(np.abs(c[3][ref][ok]), np.float32(1e-3), np.float32(0.99)))
