@@ -1,11 +1,14 @@
 """GPU parity of the kernels at the sizes where their tiles, chunks and dispatch rules change: edges and
 remainders of tiles, the smallest and largest sizes of a range."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
 
 import vbm_inputs as vi
 from oracle import binning, render
+from oracle import dvr as odvr
 from oracle import dwt as odwt
 from oracle import select as oselect
 from oracle import tf as otf
@@ -186,3 +189,25 @@ def test_selection_candidates(G, K, kind):
     assert np.array_equal(kept, ref)
     ok = np.isfinite(c[3][ref])
     assert np.array_equal(P[10].cpu().numpy()[ok], np.clip(np.abs(c[3][ref][ok]), np.float32(1e-3), np.float32(0.99)))
+
+
+# Views of several sizes in one call, more than one launch holds and none a multiple of the 16x16 blocks; the smallest
+# volume; steps other than half a voxel; a transfer function with a jump and values beyond both its ends.
+@pytest.mark.parametrize("G,step,n_views", [(2, 0.5, 1), (21, 0.5, 10), (21, 0.75, 2), (33, 1.0, 3)])
+def test_dvr_views_and_steps(G, step, n_views):
+    api = _api()
+    say(f"dvr G={G} step={step} views={n_views}")
+    rng = np.random.default_rng(G)
+    vol = rng.uniform(size=(G, G, G)).astype(np.float32)
+    xs = np.array([0.1, 0.4, 0.4, 0.7, 0.9], np.float32)
+    rgba = rng.uniform(size=(5, 4)).astype(np.float32)
+    rgba[:, 3] *= np.float32(0.2)
+    # intrinsics rounded to float32, the values the library receives
+    cams = [dataclasses.replace(c, fx=float(np.float32(c.fx)), fy=float(np.float32(c.fy)))
+            for v in range(n_views) for c in [vi.orbit_cameras(n_views, 17 + 3 * v, 33 - 2 * v, azimuth0=0.1)[v]]]
+    img = api.dvr_render(torch.from_numpy(vol).to(dev()), (xs, rgba), cams, step_vox=step)
+    for got, cam in zip(api.split_views(img, cams), cams):
+        ref, _, near = odvr.render(vol, xs, rgba, cam, step_vox=step, flag_rel=1e-6)
+        assert near.sum() <= 2
+        err = np.abs(got.cpu().numpy() - ref)[:, ~near].max()
+        assert err <= 1e-5 * max(float(np.abs(ref).max()), 1e-6)
