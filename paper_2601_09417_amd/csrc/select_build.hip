@@ -8,7 +8,7 @@
 // the candidates (12, 10 and 10 bits, most significant first) find the K-th largest key t; a last one
 // keeps every key > t plus the lowest-index keys == t until K are kept, in ascending index order, and builds
 // their Gaussians.
-// 512^3, K = 1M: 0.62 ms, where a key written per location and six passes over the keys took 1.93 ms (reading
+// 512^3, K = 1M: 0.59 ms, where a key written per location and six passes over the keys took 1.93 ms (reading
 // the coefficients takes 0.42 ms at the rate of a large copy).
 #include <hip/hip_runtime.h>
 
@@ -551,7 +551,8 @@ extern "C" vbm_status vbm_build_gaussians(const float* coeffs, int32_t G, int32_
   VBM_LAUNCH_CHECK("select_init");
   const uint32_t rank = sample_rank(M, K);
   if (rank) {
-    hipLaunchKernelGGL(k_select_sample, dim3(512), dim3(kT), 0, s, coeffs, M, rank, w.sc);
+    // (few blocks: each adds its counts to the same bins and releases them; 128, 512, 2048 blocks: 29, 69, 196 us)
+    hipLaunchKernelGGL(k_select_sample, dim3(128), dim3(kT), 0, s, coeffs, M, rank, w.sc);
     VBM_LAUNCH_CHECK("select_sample");
   }
   // 16-byte loads need every channel plane to start on a 16-byte boundary (M is a multiple of 8)
