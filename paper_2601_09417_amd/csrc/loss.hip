@@ -14,8 +14,8 @@
 //   B2 = sigma_x^2 + sigma_y^2 + C2.
 // Two LDS-tiled passes over 32x32 output tiles (256 threads, each filtering a 4-row strip of one
 // column vertically): (1) the four filtered maps (x, y, x^2 + y^2, x y) -> s and the three
-// partials, (2) the filtered partials -> dL/dx.  Partial sums go to per-block slots reduced in two
-// fixed-order stages (256 contiguous chunks, then one block), so the loss value is deterministic.
+// partials, (2) the filtered partials -> dL/dx.  Partial sums go to per-block slots, which one block adds up in
+// double in a fixed order (beside the tiles of the last gradient launch), so the loss value is deterministic.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -38,7 +38,6 @@ constexpr int RAD = 5;             // window radius
 constexpr int EX = TX + 2 * RAD;   // tile with halo
 constexpr int EY = TY + 2 * RAD;
 constexpr int RPT = 4;             // output rows per thread in the vertical pass (256 threads)
-constexpr int kRedBlocks = 256;    // first stage of the partial-sum reduction
 constexpr float kC1 = 0.01f * 0.01f;
 constexpr float kC2 = 0.03f * 0.03f;
 constexpr int kRowLoads = (EY + 3) / 4;        // halo rows per wave (a lane per halo column)
@@ -74,7 +73,7 @@ __device__ __forceinline__ float block_sum(float v, float* s_red) {
 
 // Block order of the SSIM passes.  A run of equal-size views has n_blocks = tiles x 3 channels x
 // views logical blocks (tile fastest).  Consecutive dispatches go to the 8 XCDs in turn and each XCD
-// has its own L2, so dispatch L takes logical block (L mod 8) * ceil(n_blocks / 8) + L / 8: every
+// has its own L2, so dispatch d takes logical block (d mod 8) * ceil(n_blocks / 8) + d / 8: every
 // XCD works through a contiguous run of tiles, and the halo rows and columns that neighbouring
 // tiles share are fetched once into that XCD's L2 instead of once per XCD.  Returns false for the
 // few padding dispatches past the end.
@@ -84,9 +83,8 @@ struct SsimBlock {
   int tile, c, z, bid;
 };
 
-__device__ __forceinline__ bool ssim_block(int tiles, int n_blocks, SsimBlock& b) {
+__device__ __forceinline__ bool ssim_block(int d, int tiles, int n_blocks, SsimBlock& b) {
   const int per = (n_blocks + kXcds - 1) / kXcds;
-  const int d = static_cast<int>(blockIdx.x);
   const int logical = (d % kXcds) * per + d / kXcds;
   if (logical >= n_blocks) return false;
   b.tile = logical % tiles;
@@ -94,6 +92,39 @@ __device__ __forceinline__ bool ssim_block(int tiles, int n_blocks, SsimBlock& b
   b.z = logical / (3 * tiles);
   b.bid = logical;
   return true;
+}
+
+// The loss from the partial sums: a sum(l1) + b sum(s) + c0, by one block of 256 threads in a fixed order.
+// Small images pay for launches (517 x 389: 41.4 us with two reduction launches after the gradient, 36.2 us with this
+// block inside it); with millions of pixels the block's chain of loads (2048 partials a step) hides behind the tiles.
+struct LossSum {
+  const float* l1;
+  const float* s;     // null: no SSIM term
+  int64_t n;
+  double a, b, c0;
+  float* loss;        // null: nothing to do
+};
+__device__ __forceinline__ void loss_sum(const LossSum& q, double* __restrict__ s_red) {
+  constexpr int kAhead = 8;   // loads in flight per thread
+  double acc = 0.0;
+  for (int64_t i0 = threadIdx.x; i0 < q.n; i0 += 256 * kAhead) {
+    float l[kAhead], s[kAhead];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) {
+      const int64_t i = i0 + 256 * k;
+      l[k] = i < q.n ? q.l1[i] : 0.0f;
+      s[k] = q.s && i < q.n ? q.s[i] : 0.0f;
+    }
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) acc += q.a * static_cast<double>(l[k]) + q.b * static_cast<double>(s[k]);
+  }
+  s_red[threadIdx.x] = acc;
+  __syncthreads();
+  for (int st = 128; st >= 1; st >>= 1) {
+    if (static_cast<int>(threadIdx.x) < st) s_red[threadIdx.x] += s_red[threadIdx.x + st];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) q.loss[0] = static_cast<float>(s_red[0] + q.c0);
 }
 
 // L1 only: dL/dx = scale * sign(x - y); per-block partial of |x - y|.
@@ -157,13 +188,13 @@ __global__ __launch_bounds__(256) void k_ssim_maps(const float* __restrict__ x, 
   // until every thread has read the halo.
   constexpr int kHalo = EY * (EX + 1), kMap = EY * TX;
   __shared__ float lds[2 * kMap + 2 * kHalo];
-  __shared__ float s_red[4];
+  __shared__ float2 s_red[4];
   auto sxy = reinterpret_cast<float(*)[EY][EX + 1]>(lds + 2 * kMap);
   auto hb = reinterpret_cast<float(*)[EY][TX]>(lds);
   auto sx = sxy[0];
   auto sy = sxy[1];
   SsimBlock blk;
-  if (!ssim_block(tiles, n_blocks, blk)) return;
+  if (!ssim_block(static_cast<int>(blockIdx.x), tiles, n_blocks, blk)) return;
   const int c = blk.c;
   const int bx = blk.tile % tiles_x, by = blk.tile / tiles_x;
   const int64_t HW = static_cast<int64_t>(W) * H;
@@ -275,11 +306,16 @@ __global__ __launch_bounds__(256) void k_ssim_maps(const float* __restrict__ x, 
     }
   }
   const int64_t bid = blk.bid;
-  const float ts = block_sum(sval, s_red);
-  if (threadIdx.x == 0) partial_s[bid] = ts;
+  for (int d = 32; d >= 1; d >>= 1) {
+    sval += __shfl_xor(sval, d, 64);
+    l1 += __shfl_xor(l1, d, 64);
+  }
+  if (lane_id() == 0) s_red[threadIdx.x >> 6] = make_float2(sval, l1);
   __syncthreads();
-  const float tl = block_sum(l1, s_red);
-  if (threadIdx.x == 0) partial_l1[bid] = tl;
+  if (threadIdx.x == 0) {
+    partial_s[bid] = ((s_red[0].x + s_red[1].x) + s_red[2].x) + s_red[3].x;
+    partial_l1[bid] = ((s_red[0].y + s_red[1].y) + s_red[2].y) + s_red[3].y;
+  }
 }
 
 // Pass 2: dL/dx = w_l1 sign(x - y) - w_ssim [w*p1 + 2 x (w*p2) + y (w*p3)], same tiling; the
@@ -288,14 +324,19 @@ __global__ __launch_bounds__(256) void k_ssim_grad(const float* __restrict__ x, 
                                                    int H, int tiles_x, int tiles, int n_blocks, Window win,
                                                    const float* __restrict__ p1,
                                                    const float* __restrict__ p2, const float* __restrict__ p3,
-                                                   float w_l1, float w_ssim, float* __restrict__ grad) {
+                                                   float w_l1, float w_ssim, float* __restrict__ grad, LossSum sum) {
   // Filtered maps 1 and 2 overlay the input halo (held in registers until it has been read).
   constexpr int kHalo = EY * (EX + 1), kMap = EY * TX;
-  __shared__ float lds[kMap + 3 * kHalo];
+  __shared__ __align__(16) float lds[kMap + 3 * kHalo];
   auto sp = reinterpret_cast<float(*)[EY][EX + 1]>(lds + kMap);
   auto hb = reinterpret_cast<float(*)[EY][TX]>(lds);
+  // the last launch's first block forms the loss while the others filter
+  if (sum.loss && blockIdx.x == 0) {
+    loss_sum(sum, reinterpret_cast<double*>(lds));
+    return;
+  }
   SsimBlock blk;
-  if (!ssim_block(tiles, n_blocks, blk)) return;
+  if (!ssim_block(static_cast<int>(blockIdx.x) - (sum.loss ? 1 : 0), tiles, n_blocks, blk)) return;
   const int c = blk.c;
   const int bx = blk.tile % tiles_x, by = blk.tile / tiles_x;
   const int64_t HW = static_cast<int64_t>(W) * H;
@@ -398,45 +439,9 @@ __global__ __launch_bounds__(256) void k_ssim_grad(const float* __restrict__ x, 
   }
 }
 
-// First stage of the deterministic reduction: block b sums the fixed chunk
-// [b * chunk, min((b + 1) * chunk, n)) of each partial array in double, in a fixed order.
-__global__ __launch_bounds__(256) void k_reduce_stage(const float* __restrict__ l1p, const float* __restrict__ sp,
-                                                      int64_t n, int64_t chunk, double* __restrict__ out) {
-  __shared__ double s_l[256], s_s[256];
-  const int64_t lo = static_cast<int64_t>(blockIdx.x) * chunk;
-  const int64_t hi = min(lo + chunk, n);
-  double al = 0.0, as = 0.0;
-  for (int64_t i = lo + threadIdx.x; i < hi; i += 256) {
-    al += l1p[i];
-    if (sp) as += sp[i];
-  }
-  s_l[threadIdx.x] = al;
-  s_s[threadIdx.x] = as;
-  __syncthreads();
-  for (int st = 128; st >= 1; st >>= 1) {
-    if (static_cast<int>(threadIdx.x) < st) {
-      s_l[threadIdx.x] += s_l[threadIdx.x + st];
-      s_s[threadIdx.x] += s_s[threadIdx.x + st];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    out[2 * blockIdx.x] = s_l[0];
-    out[2 * blockIdx.x + 1] = s_s[0];
-  }
-}
-
-// Second stage: loss = a * sum(l1 parts) + b * sum(ssim parts) + c, summed in a fixed order.
-__global__ void k_finalize(const double* __restrict__ parts, double a, double b, double c0,
-                           float* __restrict__ loss) {
-  __shared__ double s_red[kRedBlocks];
-  s_red[threadIdx.x] = a * parts[2 * threadIdx.x] + b * parts[2 * threadIdx.x + 1];
-  __syncthreads();
-  for (int st = kRedBlocks / 2; st >= 1; st >>= 1) {
-    if (static_cast<int>(threadIdx.x) < st) s_red[threadIdx.x] += s_red[threadIdx.x + st];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) loss[0] = static_cast<float>(s_red[0] + c0);
+__global__ __launch_bounds__(256) void k_l1_finalize(LossSum sum) {
+  __shared__ double s_red[256];
+  loss_sum(sum, s_red);
 }
 
 constexpr int kL1Blocks = 1024;
@@ -454,7 +459,7 @@ extern "C" size_t vbm_image_loss_workspace_size(const int32_t* dims, int32_t n_v
     px += W * H;
     blocks += ceil_div(W, TX) * ceil_div(H, TY) * 3;
   }
-  const size_t red = align_up(2 * kRedBlocks * sizeof(double), 256);
+  constexpr size_t red = 4096;   // not used since the loss is formed by one block; callers know the size
   if (kind == 0) return align_up(kL1Blocks * 4, 256) + red;
   return 3 * align_up(3 * px * 4, 256) + 2 * align_up(blocks * 4, 256) + red;
 }
@@ -517,14 +522,11 @@ extern "C" vbm_status vbm_image_loss(const float* image, const float* target, co
   Carver c(ws);
   if (kind == 0) {
     float* partial = c.take<float>(kL1Blocks);
-    double* parts = c.take<double>(2 * kRedBlocks);
     hipLaunchKernelGGL(k_l1, dim3(kL1Blocks), dim3(256), 0, s, image, target, n, 1.0f / static_cast<float>(n), grad,
                        partial);
     VBM_LAUNCH_CHECK("loss_l1");
-    hipLaunchKernelGGL(k_reduce_stage, dim3(kRedBlocks), dim3(256), 0, s, partial, static_cast<const float*>(nullptr),
-                       static_cast<int64_t>(kL1Blocks), ceil_div(kL1Blocks, kRedBlocks), parts);
-    VBM_LAUNCH_CHECK("loss_reduce");
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kRedBlocks), 0, s, parts, 1.0 / dn, 0.0, 0.0, loss);
+    hipLaunchKernelGGL(k_l1_finalize, dim3(1), dim3(256), 0, s,
+                       LossSum{partial, nullptr, kL1Blocks, 1.0 / dn, 0.0, 0.0, loss});
     VBM_LAUNCH_CHECK("loss_finalize");
     return VBM_OK;
   }
@@ -535,7 +537,6 @@ extern "C" vbm_status vbm_image_loss(const float* image, const float* target, co
   for (int v = 0; v < n_views; ++v) blocks += ceil_div(dims[2 * v], TX) * ceil_div(dims[2 * v + 1], TY) * 3;
   float* ps = c.take<float>(blocks);
   float* pl = c.take<float>(blocks);
-  double* parts = c.take<double>(2 * kRedBlocks);
   const Window win = make_window();
   const float w_l1 = (1.0f - lambda) / static_cast<float>(n);
   const float w_ss = lambda / static_cast<float>(n);
@@ -553,23 +554,20 @@ extern "C" vbm_status vbm_image_loss(const float* image, const float* target, co
       return VBM_ERR_UNSUPPORTED;
     }
     const int nb = static_cast<int>(nb64);
-    const dim3 grid(static_cast<unsigned>(kXcds * ceil_div(nb, kXcds)));
-    hipLaunchKernelGGL(k_ssim_maps, grid, dim3(256), 0, s, image + off, target + off, W, H, tx, tx * ty, nb, win,
-                       p1 + off, p2 + off, p3 + off, ps + boff, pl + boff);
+    const unsigned dispatches = static_cast<unsigned>(kXcds * ceil_div(nb, kXcds));
+    const bool last = v + nv == n_views;   // its gradient launch also forms the loss
+    const LossSum sum{pl, ps, blocks, (1.0 - lambda) / dn, -lambda / dn, static_cast<double>(lambda),
+                      last ? loss : nullptr};
+    hipLaunchKernelGGL(k_ssim_maps, dim3(dispatches), dim3(256), 0, s, image + off, target + off, W, H, tx, tx * ty,
+                       nb, win, p1 + off, p2 + off, p3 + off, ps + boff, pl + boff);
     VBM_LAUNCH_CHECK("ssim_maps");
-    hipLaunchKernelGGL(k_ssim_grad, grid, dim3(256), 0, s, image + off, target + off, W, H, tx, tx * ty, nb, win,
-                       p1 + off, p2 + off, p3 + off, w_l1, w_ss, grad + off);
+    hipLaunchKernelGGL(k_ssim_grad, dim3(dispatches + (last ? 1 : 0)), dim3(256), 0, s, image + off, target + off, W, H,
+                       tx, tx * ty, nb, win, p1 + off, p2 + off, p3 + off, w_l1, w_ss, grad + off, sum);
     VBM_LAUNCH_CHECK("ssim_grad");
     off += 3 * static_cast<int64_t>(W) * H * nv;
     boff += static_cast<int64_t>(tx) * ty * 3 * nv;
     v += nv;
   }
-  hipLaunchKernelGGL(k_reduce_stage, dim3(kRedBlocks), dim3(256), 0, s, pl, ps, blocks,
-                     ceil_div(blocks, kRedBlocks), parts);
-  VBM_LAUNCH_CHECK("loss_reduce");
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kRedBlocks), 0, s, parts, (1.0 - lambda) / dn, -lambda / dn,
-                     static_cast<double>(lambda), loss);
-  VBM_LAUNCH_CHECK("loss_finalize");
   return VBM_OK;
 }
 

@@ -211,3 +211,25 @@ def test_dvr_views_and_steps(G, step, n_views):
         assert near.sum() <= 2
         err = np.abs(got.cpu().numpy() - ref)[:, ~near].max()
         assert err <= 1e-5 * max(float(np.abs(ref).max()), 1e-6)
+
+
+# The loss value comes from one block that takes 2048 partial sums at a time: one partial, a single pass of the
+# block, a remainder after it, and view groups whose last one is a single tile.  The bounds are those of the
+# repository's loss comparison.
+@pytest.mark.parametrize("kind", ["l1", "l1_dssim"])
+@pytest.mark.parametrize("dims", [[(1, 1)], [(33, 31)], [(900, 905)], [(640, 512), (640, 512), (129, 500), (5, 3)]])
+def test_loss_partials(dims, kind):
+    from oracle import loss as oloss
+    api = _api()
+    say(f"loss partials {dims} {kind}")
+    rng = np.random.default_rng(len(dims))
+    imgs = [rng.uniform(size=(3, h, w)).astype(np.float32) for w, h in dims]
+    tgts = [np.clip(i + 0.1 * rng.normal(size=i.shape), 0, 1).astype(np.float32) for i in imgs]
+    x = torch.from_numpy(np.concatenate([i.reshape(-1) for i in imgs])).to(dev())
+    y = torch.from_numpy(np.concatenate([t.reshape(-1) for t in tgts])).to(dev())
+    g = torch.empty_like(x)
+    value = float(api.ImageLoss(dims, kind, 0.2)(x, y, g).item())
+    ref_loss, ref_g = oloss.loss_and_grad(imgs, tgts, kind)
+    assert abs(value - ref_loss) <= 1e-5 * abs(ref_loss)
+    rg = np.concatenate([a.reshape(-1) for a in ref_g])
+    assert np.abs(g.cpu().numpy() - rg).max() <= 1e-4 * np.abs(rg).max()
