@@ -233,3 +233,28 @@ def test_loss_partials(dims, kind):
     assert abs(value - ref_loss) <= 1e-5 * abs(ref_loss)
     rg = np.concatenate([a.reshape(-1) for a in ref_g])
     assert np.abs(g.cpu().numpy() - rg).max() <= 1e-4 * np.abs(rg).max()
+
+
+# Subbands of one part of a chunk, of one chunk and of a chunk and a short part; blocks without coefficients; many equal
+# norms (zeros, halves); infinities; budgets of 0 and of more than a subband holds.  The results match the oracle's.
+@pytest.mark.parametrize("G,J,values,K_tot,params", [
+    (8, 1, "normal", 100, dict(alpha=0.0, beta=0.0)), (16, 1, "normal", 7, dict(alpha=0.0, beta=0.0, min_band=0)),
+    (32, 1, "infinite", 2048, dict(alpha=0.0, beta=0.0)), (32, 1, "zeros", 512, dict(alpha=0.0, beta=0.0, lam=0.0)),
+    (52, 1, "sparse", 9001, dict(lam=0.5)), (52, 1, "halves", 20001, dict(lam=1.0)),
+    (64, 1, "normal", 4, dict(min_band=40000)), (66, 1, "normal", 30011, dict(lam=0.0))])
+def test_adaptive_parts(G, J, values, K_tot, params):
+    from tests.gpu_common import adaptive_check
+    api = _api()
+    say(f"adaptive parts G={G} J={J} {values} K_tot={K_tot} {params}")
+    rng = np.random.default_rng(G + K_tot)
+    c = rng.normal(size=(4, G ** 3)).astype(np.float32)
+    if values == "zeros":
+        c[:] = 0.0
+    elif values == "sparse":
+        c *= rng.uniform(size=(1, G ** 3)) < 0.03
+    elif values == "halves":
+        c = (np.round(2 * c) / 2).astype(np.float32)
+    elif values == "infinite":
+        c[rng.uniform(size=c.shape) < 0.01] = -np.inf
+    kept, stats = api.adaptive_select(torch.from_numpy(c).to(dev()), G, J, K_tot, **params)
+    adaptive_check(c, G, J, kept.cpu().numpy(), stats.cpu().numpy(), K_tot, **params)
