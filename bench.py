@@ -51,9 +51,9 @@ FLOPS_BWD_EVAL, FLOPS_BWD_USED = 17, 40
 # pixel.  (The lane-group marks the forward writes back into visited pair values are not counted.)
 BYTES_PER_PAIR_FWD, BYTES_PER_PIXEL_FWD = 40, 20
 BYTES_PER_PAIR_BWD, BYTES_PER_PIXEL_BWD = 76, 20
-# adaptive selection: 16 B read + 4 B key written, eight select passes (the median and the
-# K_band-th largest share four) and three count/flag/write passes over the 4-byte keys, per coefficient
-ADAPTIVE_BYTES_PER_COEF = 16 + 4 + 8 * 4 + 3 * 4
+# adaptive selection: 16 B read + 4 B key written, five select passes (the first digit is counted as the
+# keys are written) and the count and write passes over the 4-byte keys, per coefficient
+ADAPTIVE_BYTES_PER_COEF = 16 + 4 + 5 * 4 + 2 * 4
 
 WORKLOADS = {
     "c0": dict(config=0, G=32, J=1, wavelet="haar", K=2048, views=1, W=64, H=64, tile=16, loss="l1",

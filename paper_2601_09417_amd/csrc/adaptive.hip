@@ -615,7 +615,9 @@ extern "C" vbm_status vbm_adaptive_select(const float* coeffs, int32_t G, int32_
   const int64_t chunks = bt.chunk0[bt.nb];
   const dim3 cg(static_cast<unsigned>(chunks)), pg(static_cast<unsigned>(chunks << bt.part_shift)), blk(kT);
 
-  VBM_TRY(fill_u32(w.ghist, 0u, static_cast<int64_t>(bt.nb) * kHistWords, s));
+  ClearList cl;
+  cl.add(w.ghist, static_cast<int64_t>(bt.nb) * kHistWords);
+  VBM_TRY(clear_words(cl, s));
   hipLaunchKernelGGL(k_af_norm, cg, blk, 0, s, coeffs, M, bt, opts->ref_channel, w.keys, w.epart, w.ghist);
   VBM_LAUNCH_CHECK("adaptive_norm");
   hipLaunchKernelGGL(k_af_budget, dim3(1), dim3(kBudgetThreads), 0, s, bt, w.epart, w.st, opts->K_tot, opts->alpha,

@@ -92,13 +92,7 @@ __device__ __forceinline__ float sqrt_rn_f32(float x) {
   return static_cast<float>(__dsqrt_rn(static_cast<double>(x)));
 }
 
-// ------------------------------------------------------------------ scan / sort primitives (scan_sort.hip)
-// Exclusive prefix sum of n u32 values (n read from *n_dev when non-null, else n_max), with the
-// total written to *total_dev.  Scratch from scan_scratch_bytes(n_max).
-size_t scan_scratch_bytes(int64_t n_max);
-vbm_status scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n_max, const uint32_t* n_dev,
-                              uint32_t* total_dev, void* scratch, hipStream_t s);
-
+// ------------------------------------------------------------------ sort primitives (scan_sort.hip)
 // Stable LSD radix sorts of (key, value) pairs over key bits [0, end_bit) (end_bit <= 32), digit
 // width 4..8 bits.  The caller clears the kMaxRadixTotals words at radix_totals() beforehand.  The first
 // kRadixHead bytes of the scratch are not the sorts': tile_order_counts() lies there.
@@ -149,10 +143,8 @@ vbm_status sort_pairs_by_tile(uint32_t* const k[2], uint32_t* const v[2], int fi
                               const uint32_t* n_dev, int end_bit, int digit_bits, const TileLists& lists,
                               void* scratch, hipStream_t s);
 
-// Device fill (used instead of memset nodes so every step stays capturable).
-vbm_status fill_u32(uint32_t* p, uint32_t value, int64_t n, hipStream_t s);
-
-// Several short runs of 32-bit words cleared by one launch.
+// Several runs of 32-bit words cleared by one launch (used instead of memset nodes so that every step stays
+// capturable).
 struct ClearList {
   static constexpr int kMax = 6;
   uint32_t* p[kMax];

@@ -1,7 +1,6 @@
-// Device-wide exclusive scan and stable LSD radix sort (gfx950, wave64, 256-thread blocks).
+// Stable LSD radix sort (gfx950, wave64, 256-thread blocks).
 //
-// Scan: reduce -> single-workgroup scan of the block sums -> per-block scan with the block
-// offset added.  Sort: one histogram kernel counts the digits of every pass in one read of the
+// One histogram kernel counts the digits of every pass in one read of the
 // keys, then each pass is a single kernel over 8192-key tiles that ranks equal digits inside each
 // wave with ballots (a lane's rank = set bits of its digit-match mask below it) and across a
 // wave's rounds through per-wave LDS counters, learns the earlier tiles' digit counts by
@@ -31,131 +30,6 @@ __device__ __forceinline__ int64_t active_count(int64_t n_max, const uint32_t* n
   if (!n_dev) return n_max;
   int64_t n = static_cast<int64_t>(*n_dev);
   return n < n_max ? n : n_max;
-}
-
-template <class T>
-__global__ __launch_bounds__(kThreads) void k_scan_reduce(const T* __restrict__ in, T* __restrict__ block_sums,
-                                                          int64_t n_max, const uint32_t* n_dev) {
-  const int64_t n = active_count(n_max, n_dev);
-  const int64_t base = static_cast<int64_t>(blockIdx.x) * kChunk;
-  T acc = 0;
-  if (sizeof(T) == 4 && base + kChunk <= n && aligned16(in)) {
-    // a full block of 32-bit values: four 16-byte loads per thread, consecutive across the wave
-    const uint4* src = reinterpret_cast<const uint4*>(in + base);
-#pragma unroll
-    for (int r = 0; r < kItems / 4; ++r) {
-      const uint4 q = src[r * kThreads + threadIdx.x];
-      acc += static_cast<T>(q.x) + static_cast<T>(q.y) + static_cast<T>(q.z) + static_cast<T>(q.w);
-    }
-  } else if (base < n) {
-#pragma unroll
-    for (int r = 0; r < kItems; ++r) {
-      int64_t i = base + r * kThreads + threadIdx.x;
-      if (i < n) acc += in[i];
-    }
-  }
-  T tot;
-  block_excl_scan(acc, &tot);
-  if (threadIdx.x == 0) block_sums[blockIdx.x] = tot;
-}
-
-// One workgroup scans all block sums in place (exclusive), carrying across 4096-entry chunks.
-template <class T>
-__global__ __launch_bounds__(kThreads) void k_scan_top(T* __restrict__ sums, int64_t nb, T* __restrict__ total) {
-  T carry = 0;
-  for (int64_t base = 0; base < nb; base += kChunk) {
-    T items[kItems];
-    T acc = 0;
-#pragma unroll
-    for (int r = 0; r < kItems; ++r) {
-      int64_t i = base + static_cast<int64_t>(threadIdx.x) * kItems + r;
-      items[r] = i < nb ? sums[i] : T(0);
-      acc += items[r];
-    }
-    T tot;
-    T ex = block_excl_scan(acc, &tot) + carry;
-#pragma unroll
-    for (int r = 0; r < kItems; ++r) {
-      int64_t i = base + static_cast<int64_t>(threadIdx.x) * kItems + r;
-      if (i < nb) sums[i] = ex;
-      ex += items[r];
-    }
-    carry += tot;
-  }
-  if (total && threadIdx.x == 0) *total = carry;
-}
-
-template <class T>
-__global__ __launch_bounds__(kThreads) void k_scan_down(const T* __restrict__ in, T* __restrict__ out,
-                                                        const T* __restrict__ block_offsets, int64_t n_max,
-                                                        const uint32_t* n_dev) {
-  const int64_t n = active_count(n_max, n_dev);
-  const int64_t base = static_cast<int64_t>(blockIdx.x) * kChunk;
-  if (base >= n) return;  // uniform per block
-  // A full block of 32-bit values moves as four 16-byte vectors per thread (thread t owns
-  // elements [16 t, 16 t + 16) of the block, as in the general path).
-  const bool vec = sizeof(T) == 4 && base + kChunk <= n && aligned16(in) && aligned16(out);
-  T items[kItems];
-  T acc = 0;
-  if (vec) {
-    const uint4* src = reinterpret_cast<const uint4*>(in + base) + threadIdx.x * (kItems / 4);
-#pragma unroll
-    for (int r = 0; r < kItems / 4; ++r) {
-      const uint4 q = src[r];
-      items[4 * r] = static_cast<T>(q.x);
-      items[4 * r + 1] = static_cast<T>(q.y);
-      items[4 * r + 2] = static_cast<T>(q.z);
-      items[4 * r + 3] = static_cast<T>(q.w);
-    }
-  } else {
-#pragma unroll
-    for (int r = 0; r < kItems; ++r) {
-      int64_t i = base + static_cast<int64_t>(threadIdx.x) * kItems + r;
-      items[r] = i < n ? in[i] : T(0);
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < kItems; ++r) acc += items[r];
-  T tot;
-  T ex = block_excl_scan(acc, &tot) + block_offsets[blockIdx.x];
-  if (vec) {
-    uint4* dst = reinterpret_cast<uint4*>(out + base) + threadIdx.x * (kItems / 4);
-#pragma unroll
-    for (int r = 0; r < kItems / 4; ++r) {
-      uint4 q;
-      q.x = static_cast<uint32_t>(ex);
-      ex += items[4 * r];
-      q.y = static_cast<uint32_t>(ex);
-      ex += items[4 * r + 1];
-      q.z = static_cast<uint32_t>(ex);
-      ex += items[4 * r + 2];
-      q.w = static_cast<uint32_t>(ex);
-      ex += items[4 * r + 3];
-      dst[r] = q;
-    }
-  } else {
-#pragma unroll
-    for (int r = 0; r < kItems; ++r) {
-      int64_t i = base + static_cast<int64_t>(threadIdx.x) * kItems + r;
-      if (i < n) out[i] = ex;
-      ex += items[r];
-    }
-  }
-}
-
-// Fills n values; a 16-byte aligned buffer is written as 16-byte vectors plus a scalar tail.
-__global__ void k_fill_u32(uint32_t* p, uint32_t v, int64_t n) {
-  const int64_t first = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  if (aligned16(p)) {
-    const int64_t n4 = n >> 2;
-    uint4* q = reinterpret_cast<uint4*>(p);
-    const uint4 vv = make_uint4(v, v, v, v);
-    for (int64_t i = first; i < n4; i += stride) q[i] = vv;
-    for (int64_t i = 4 * n4 + first; i < n; i += stride) p[i] = v;
-  } else {
-    for (int64_t i = first; i < n; i += stride) p[i] = v;
-  }
 }
 
 __global__ __launch_bounds__(256) void k_clear_words(ClearList c) {
@@ -657,40 +531,6 @@ __global__ __launch_bounds__(256) void k_tile_keys(TileLists lists, int64_t capa
 }
 
 }  // namespace
-
-size_t scan_scratch_bytes(int64_t n_max) {
-  int64_t nb = ceil_div(n_max > 0 ? n_max : 1, kChunk);
-  return align_up(static_cast<size_t>(nb) * 8, 256) + 256;
-}
-
-template <class T>
-static vbm_status scan_impl(const T* in, T* out, int64_t n_max, const uint32_t* n_dev, T* total_dev, void* scratch,
-                            hipStream_t s) {
-  if (n_max <= 0) return VBM_OK;
-  const int64_t nb = ceil_div(n_max, kChunk);
-  T* sums = static_cast<T*>(scratch);
-  hipLaunchKernelGGL(k_scan_reduce<T>, dim3(nb), dim3(kThreads), 0, s, in, sums, n_max, n_dev);
-  VBM_LAUNCH_CHECK("scan_reduce");
-  hipLaunchKernelGGL(k_scan_top<T>, dim3(1), dim3(kThreads), 0, s, sums, nb, total_dev);
-  VBM_LAUNCH_CHECK("scan_top");
-  hipLaunchKernelGGL(k_scan_down<T>, dim3(nb), dim3(kThreads), 0, s, in, out, sums, n_max, n_dev);
-  VBM_LAUNCH_CHECK("scan_down");
-  return VBM_OK;
-}
-
-vbm_status scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n_max, const uint32_t* n_dev,
-                              uint32_t* total_dev, void* scratch, hipStream_t s) {
-  return scan_impl<uint32_t>(in, out, n_max, n_dev, total_dev, scratch, s);
-}
-
-vbm_status fill_u32(uint32_t* p, uint32_t value, int64_t n, hipStream_t s) {
-  if (n <= 0) return VBM_OK;
-  int64_t blocks = ceil_div(ceil_div(n, 4), 256);
-  if (blocks > 8192) blocks = 8192;
-  hipLaunchKernelGGL(k_fill_u32, dim3(blocks), dim3(256), 0, s, p, value, n);
-  VBM_LAUNCH_CHECK("fill_u32");
-  return VBM_OK;
-}
 
 vbm_status clear_words(const ClearList& c, hipStream_t s) {
   int64_t most = 1;
