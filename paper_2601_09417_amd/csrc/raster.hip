@@ -623,23 +623,26 @@ struct BwdPix {
 // alpha c + (1 - alpha) acc.  Only the projection S = sum_c dL/dC_c acc_c enters, so that scalar is
 // what the pixel carries: dL/dalpha = T_before (D_c - S) with D_c = sum_c dL/dC_c c_c, and S moves
 // to S + alpha (D_c - S).  dL/dpower = alpha dL/dalpha unless alpha was clamped.
-// Returns the wave sum that the lane is left with (see reduce_cols9, reduce_scatter9), 0 when no group is marked.
-template <int PPL, bool MARKED, bool COLS, bool STATS>
-__device__ __forceinline__ float bwd_step(const Rec& r, uint32_t groups, int j, float fx, BwdPix<PPL>& P, int lane,
-                                          uint32_t& n_eval, uint32_t& n_used) {
+// Leaves the lane's sums over its pixels: s0 = sum dp, s1 = sum dp dy, s2 = sum dp dy^2 (dp = dL/dpower), and the colour
+// weights alpha T_before dL/dC.  False (for the whole wave) when no group is marked or, without marks, no pixel
+// takes part.
+// RARE: a clamped alpha, of which there are few, is handled in uniform branches instead of by a minimum and a select for
+// every pixel: fewer instructions, but a lone wave waits for every branch (see kLdsSumTiles).
+struct BwdSums {
+  float s0, s1, s2, wr, wg, wb;
+};
+template <int PPL, bool MARKED, bool RARE, bool STATS>
+__device__ __forceinline__ bool bwd_step(const Rec& r, uint32_t groups, int j, float dx, float dx2, BwdPix<PPL>& P,
+                                         BwdSums& sums, uint32_t& n_eval, uint32_t& n_used) {
   if (STATS)
 #pragma unroll
     for (int k = 0; k < PPL; ++k) n_eval += j < P.nc[k] ? 1u : 0u;
   // MARKED: groups holds the lane groups that the forward left marked, a superset of those
   // with a contributing pixel; each is handled wholly inside its own uniform branch.
   if (!MARKED) groups = (1u << PPL) - 1u;
-  if (groups == 0) return 0.0f;
-  const float dx = r.mx - fx;
-  const float dx2 = dx * dx;
+  if (groups == 0) return false;
   const float u = fmaf(r.hA, dx2, r.lo);
   const float vb = r.hB * dx;
-  // Per-lane sums: s0 = sum dp, s1 = sum dp dy, s2 = sum dp dy^2 (dp = dL/dpower), and the colour
-  // weights alpha T_before dL/dC.
   float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, wr = 0.0f, wg = 0.0f, wb = 0.0f;
   bool anyc = false;
 #pragma unroll
@@ -647,11 +650,16 @@ __device__ __forceinline__ float bwd_step(const Rec& r, uint32_t groups, int j, 
     if (!((groups >> k) & 1u)) continue;
     const float dy = r.my - P.fy[k];
     const float G2 = __builtin_amdgcn_exp2f(exponent2(r, u, vb, dy));
-    const float alpha = fminf(kAlphaMax, G2);
-    const bool c = j < P.nc[k] && alpha >= kAlphaMin;
+    float alpha = RARE ? G2 : fminf(kAlphaMax, G2);
+    const bool c = j < P.nc[k] && !(alpha < kAlphaMin);
     if (STATS) n_used += c ? 1u : 0u;
     anyc |= c;
     if (c) {
+      const bool clamped = RARE && wave_any(!(G2 <= kAlphaMax));
+      if (clamped) {
+        __asm__ volatile("");   // keeps this a branch
+        alpha = fminf(kAlphaMax, G2);
+      }
       const float Tk = P.T[k] * __builtin_amdgcn_rcpf(1.0f - alpha);
       P.T[k] = Tk;
       const float D = fmaf(P.dr[k], r.r, fmaf(P.dg[k], r.g, P.db[k] * r.b)) - P.S[k];
@@ -660,21 +668,70 @@ __device__ __forceinline__ float bwd_step(const Rec& r, uint32_t groups, int j, 
       wr = fmaf(w, P.dr[k], wr);
       wg = fmaf(w, P.dg[k], wg);
       wb = fmaf(w, P.db[k], wb);
-      const float dp = G2 <= kAlphaMax ? w * D : 0.0f;     // alpha dL/dalpha
+      float dp = w * D;     // alpha dL/dalpha, unless alpha was clamped
+      if (!RARE || clamped) {
+        if (RARE) __asm__ volatile("");
+        dp = G2 <= kAlphaMax ? dp : 0.0f;
+      }
       const float t = dp * dy;
       s0 += dp;
       s1 += t;
       s2 = fmaf(t, dy, s2);
     }
   }
+  sums = BwdSums{s0, s1, s2, wr, wg, wb};
   // (with marks the superset is tight enough that the test does not pay for itself)
-  if (!MARKED && !wave_any(anyc)) return 0.0f;
-  if constexpr (COLS) {
-    return reduce_cols9(s0, s1, s2, wr, wg, wb, dx, dx2, lane);
-  } else {
-    const float g[9] = {dx * s0, s1, dx2 * s0, dx * s1, s2, s0, wr, wg, wb};
-    return reduce_scatter9(g, lane);
-  }
+  return MARKED || wave_any(anyc);
+}
+
+// The nine wave sums of two list entries at a time, through LDS (tiles at most 16 wide).  Every lane leaves its six
+// sums of an entry in six rows of 64; lane 4 (6 e + v) + q then takes the four words 16 r + 4 q .. + 3 of row v of entry
+// e, r = 0..3: four pixel columns.  It adds a column's pixels, weighs the columns with 1, dx and dx^2, and the quad
+// adds its four lanes' sums, of which lane q issues the q-th.
+// Why not in registers: a SIMD issues two vector instructions in four cycles, but only one of the two may be a lane
+// swap, a DPP or a select or read a scalar register (measured: 2.2 G wave instructions/s per CU of those, 1.2 of
+// swaps, against 4.0 of plain adds and fused multiply-adds), and 16 of the 24 that reduce_cols9 takes are of that kind (the swaps twice as slow).
+// Here about 7 of 26 per entry are.  27M pairs at 1080p: 4.03 -> 3.76 ms, with the branches of RARE 3.62 ms.
+constexpr int kSumRow = 80;                 // words between rows: a quarter wave's 16-byte reads touch every bank once
+constexpr int kSumWords = 12 * kSumRow;     // per wave
+__device__ __forceinline__ int sum_column(int lane) {   // the gradient column (0..8) that the lane issues, or -1
+  const int v = (lane >> 2) % 6, q = lane & 3;
+  if (lane >= 48) return -1;
+  if (v == 0) return q == 0 ? 5 : q == 1 ? 0 : q == 2 ? 2 : -1;   // s0, dx s0, dx^2 s0
+  if (v == 1) return q == 0 ? 1 : q == 1 ? 3 : -1;                // s1, dx s1
+  return q != 0 ? -1 : v == 2 ? 4 : v + 3;                        // s2, wr, wg, wb
+}
+
+// One entry's sums to slot e (0 or 1).
+__device__ __forceinline__ void sums_put(float* __restrict__ red, int e, int lane, const BwdSums& s) {
+  float* p = red + e * (6 * kSumRow) + lane;
+  p[0] = s.s0;
+  p[kSumRow] = s.s1;
+  p[2 * kSumRow] = s.s2;
+  p[3 * kSumRow] = s.wr;
+  p[4 * kSumRow] = s.wg;
+  p[5 * kSumRow] = s.wb;
+}
+
+// The wave sum of column sum_column(lane) of the lane's entry, 4 lanes of slots 0 and 1 each; mx: the entry's mean x,
+// fx0: the lane's first column.
+__device__ __forceinline__ float sums_total(const float* __restrict__ red, int lane, float mx, float fx0) {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  const float4* p = reinterpret_cast<const float4*>(red + min(lane >> 2, 11) * kSumRow + 4 * (lane & 3));
+  const float4 r0 = p[0], r1 = p[4], r2 = p[8], r3 = p[12];
+  const float c0 = (r0.x + r1.x) + (r2.x + r3.x), c1 = (r0.y + r1.y) + (r2.y + r3.y);
+  const float c2 = (r0.z + r1.z) + (r2.z + r3.z), c3 = (r0.w + r1.w) + (r2.w + r3.w);
+  const float d0 = mx - fx0, d1 = mx - (fx0 + 1.0f), d2 = mx - (fx0 + 2.0f), d3 = mx - (fx0 + 3.0f);
+  float a = (c0 + c1) + (c2 + c3);
+  float b = fmaf(c0, d0, c1 * d1) + fmaf(c2, d2, c3 * d3);
+  float c = fmaf(c0, d0 * d0, c1 * (d1 * d1)) + fmaf(c2, d2 * d2, c3 * (d3 * d3));
+  a = rs_single<kQuadXor1>(rs_single<kQuadXor2>(a));
+  b = rs_single<kQuadXor1>(rs_single<kQuadXor2>(b));
+  c = rs_single<kQuadXor1>(rs_single<kQuadXor2>(c));
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  return (lane & 2) ? c : (lane & 1) ? b : a;
 }
 
 // A split tile in the backward: its four bands are walked by the four waves of a block, in batches of 64 list
@@ -736,7 +793,10 @@ __device__ __forceinline__ void bwd_walk_bands(BandLists& L, const uint32_t* __r
       const float4 a = L.a[e], b = L.b[e];
       const Rec r{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w, L.c[e].x};
       uint32_t unused = 0;
-      const float sum = bwd_step<1, false, true, STATS>(r, 1u, hi - e, fx, P, lane, unused, n_used);
+      const float dx = r.mx - fx, dx2 = dx * dx;
+      BwdSums s;
+      if (!bwd_step<1, false, false, STATS>(r, 1u, hi - e, dx, dx2, P, s, unused, n_used)) continue;
+      const float sum = reduce_cols9(s.s0, s.s1, s.s2, s.wr, s.wg, s.wb, dx, dx2, lane);
       if (out_lane && sum != 0.0f) reinterpret_cast<float*>(&L.sum[9 * e + out_k])[wave] = sum;
     }
     __syncthreads();
@@ -757,7 +817,15 @@ __device__ __forceinline__ void bwd_walk_bands(BandLists& L, const uint32_t* __r
 template <int TILE>
 constexpr int kBwdThreads = TILE == 16 ? 256 : TileCfg<TILE>::kThreads;
 
-template <int TILE, bool STATS, int LDSB>
+// LDS of a backward block: a split tile's lists, or per wave the staged lists or the sums of two entries.
+template <int TILE, int LDSB, bool SUMS>
+constexpr size_t bwd_lds_bytes() {
+  const size_t wave = SUMS ? sizeof(float) * kSumWords : LDSB > 0 ? sizeof(LdsBatch<LDSB == 0 ? 1 : LDSB>) : 16;
+  const size_t waves = wave * (kBwdThreads<TILE> / 64);
+  return TILE == 16 && sizeof(BandLists) > waves ? sizeof(BandLists) : waves;
+}
+
+template <int TILE, bool STATS, int LDSB, bool SUMS>
 __global__ __launch_bounds__(kBwdThreads<TILE>) void k_composite_bwd(
     const DevView* __restrict__ views, int n_views, int n_tiles, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ tile_order, const uint32_t* __restrict__ n_split,
@@ -804,12 +872,15 @@ __global__ __launch_bounds__(kBwdThreads<TILE>) void k_composite_bwd(
   const int start = static_cast<int>(uniform(ranges[tile].x));
   // Lanes l, l + 16, l + 32, l + 48 share a pixel column when the tile is at most 16 wide.
   constexpr bool kCols = 16 % TILE == 0;
+  static_assert(!SUMS || (kCols && LDSB == 0), "sums through LDS: columns in rows of 16, no staged lists");
   const int out_k = kCols ? col_index(lane) : rs_index(lane & 15);
   const bool out_lane = kCols ? out_k >= 0 : lane < 16 && ((lane & 1) == 0 || lane == 1);
   const float4* __restrict__ crec = reinterpret_cast<const float4*>(coef);
+  __shared__ __align__(16) unsigned char lds[bwd_lds_bytes<TILE, LDSB, SUMS>()];
+  const int lds_wave = TILE == 16 ? block_wave : 0;
   if constexpr (TILE == 16) {
     if (split) {   // uniform for the block
-      __shared__ BandLists bands;
+      BandLists& bands = *reinterpret_cast<BandLists*>(lds);
       BwdPix<1> P;
       load_pixel(ty * TILE + (lane + 64 * block_wave) / TILE, P.fy[0], P.T[0], P.nc[0], P.dr[0], P.dg[0], P.db[0],
                  P.S[0]);
@@ -836,16 +907,49 @@ __global__ __launch_bounds__(kBwdThreads<TILE>) void k_composite_bwd(
   constexpr bool kMarked = TILE <= 16;
   const uint32_t* __restrict__ pair_values = TILE == 16 ? pair_marked : pair_item;
   const uint32_t imax = n_items > 0 ? static_cast<uint32_t>(n_items - 1) : 0u;
+  float* red = reinterpret_cast<float*>(lds) + (SUMS ? lds_wave * kSumWords : 0);
+  const float col0 = static_cast<float>(tx * TILE + (4 * (lane & 3)) % TILE) + 0.5f;   // of the lane's columns in red
+  const int sum_k = sum_column(lane);
+  int slot = 0;   // entries in red
+  float mx0 = 0.0f;
+  uint32_t item0 = 0;
+  auto flush = [&](int n, float mx1, uint32_t item1) __attribute__((always_inline)) {
+    const bool second = lane >= 24;
+    const float sum = sums_total(red, lane, second ? mx1 : mx0, col0);
+    if (sum_k >= 0 && lane < 24 * n && sum != 0.0f)
+      unsafeAtomicAdd(&grad2d[16 * static_cast<size_t>(second ? item1 : item0) + sum_k], sum);
+  };
   auto step = [&](const Rec& r, uint32_t pv, int j) __attribute__((always_inline)) {
-    const float sum = bwd_step<PPL, kMarked, kCols, STATS>(r, pv >> kItemBits, j, fx, P, lane, n_eval, n_used);
-    if (out_lane && sum != 0.0f) unsafeAtomicAdd(&grad2d[16 * static_cast<size_t>(pv & kItemMask) + out_k], sum);
+    const float dx = r.mx - fx, dx2 = dx * dx;
+    BwdSums s;
+    if (!bwd_step<PPL, kMarked, SUMS, STATS>(r, pv >> kItemBits, j, dx, dx2, P, s, n_eval, n_used)) return;
+    const uint32_t item = pv & kItemMask;
+    if constexpr (SUMS) {
+      sums_put(red, slot, lane, s);
+      if (slot == 0) {
+        mx0 = r.mx;
+        item0 = item;
+        slot = 1;
+        return;
+      }
+      flush(2, r.mx, item);
+      slot = 0;
+    } else {
+      float sum;
+      if constexpr (kCols) {
+        sum = reduce_cols9(s.s0, s.s1, s.s2, s.wr, s.wg, s.wb, dx, dx2, lane);
+      } else {
+        const float g[9] = {dx * s.s0, s.s1, dx2 * s.s0, dx * s.s1, s.s2, s.s0, s.wr, s.wg, s.wb};
+        sum = reduce_scatter9(g, lane);
+      }
+      if (out_lane && sum != 0.0f) unsafeAtomicAdd(&grad2d[16 * static_cast<size_t>(item) + out_k], sum);
+    }
   };
   if constexpr (LDSB > 0) {
     static_assert(C::kWaves == 1, "LDS batches are wave-private");
     // LDS batches walked in reverse: the batch ending at list position hi holds
     // positions hi, hi - 1, ... in lanes 0, 1, ...
-    __shared__ LdsBatch<LDSB> batches[kBwdThreads<TILE> / 64];
-    LdsBatch<LDSB>& L = batches[TILE == 16 ? block_wave : 0];
+    LdsBatch<LDSB>& L = reinterpret_cast<LdsBatch<LDSB>*>(lds)[lds_wave];
     uint32_t pv;
     float4 ra, rb;
     float bl;
@@ -889,6 +993,7 @@ __global__ __launch_bounds__(kBwdThreads<TILE>) void k_composite_bwd(
     step(R2, u2, j - 2);
   }
   }
+  if (SUMS && slot) flush(1, mx0, item0);
   if (STATS) add_stats(stats, n_eval, n_used);
 }
 
@@ -953,20 +1058,28 @@ static vbm_status launch_fwd_t(const CompositeArgs& a, float* image, float* fina
   return VBM_OK;
 }
 
+// Batches of so many tiles keep every SIMD supplied with waves, and the instructions that a SIMD can issue set the
+// backward's time: sums through LDS and branches around the rare cases save some.  With fewer, the time is that of the
+// longest lists, whose waves wait for each LDS round trip and branch.  us with sums in registers / this
+// form (tiles): 710 / 871 (11,340), 736 / 851 (12,544), 888 / 815 (16,320), 1248 / 1115 (24,480), 1559 / 1435 (32,640),
+// 1291 / 1151 (40,000), 4028 / 3617 (65,280); with 8x8 tiles 96 / 105 (7,600), 249 / 207 (24,000), 2177 / 2035 (160,000).
+constexpr int64_t kLdsSumTiles = 15000;
+
 template <int TILE, int LDSB>
 static vbm_status launch_bwd_t(const CompositeArgs& a, const float* final_T, const int32_t* n_contrib,
                                const float* dL_dimg, float* grad2d, hipStream_t s) {
   // with 16x16 tiles a block per split tile and a wave for each of the others (blocks left over do nothing)
   const int64_t split = a.n_tiles < kMaxSplit ? a.n_tiles : kMaxSplit;
   const dim3 grid(static_cast<unsigned>(TILE == 16 ? split + ceil_div(a.n_tiles, 4) : a.n_tiles)), block(kBwdThreads<TILE>);
-  if (a.stats)
-    hipLaunchKernelGGL((k_composite_bwd<TILE, true, LDSB>), grid, block, 0, s, a.views, a.n_views,
-                       static_cast<int>(a.n_tiles), a.ranges, a.tile_order, a.n_split, a.pair_item, a.pair_marked,
-                       a.coef, a.blue, final_T, n_contrib, dL_dimg, grad2d, a.n_items, a.stats);
-  else
-    hipLaunchKernelGGL((k_composite_bwd<TILE, false, LDSB>), grid, block, 0, s, a.views, a.n_views,
-                       static_cast<int>(a.n_tiles), a.ranges, a.tile_order, a.n_split, a.pair_item, a.pair_marked,
-                       a.coef, a.blue, final_T, n_contrib, dL_dimg, grad2d, a.n_items, a.stats);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, a.views, a.n_views, static_cast<int>(a.n_tiles), a.ranges,
+                       a.tile_order, a.n_split, a.pair_item, a.pair_marked, a.coef, a.blue, final_T, n_contrib, dL_dimg,
+                       grad2d, a.n_items, a.stats);
+  };
+  constexpr bool kSums = TILE <= 16 && LDSB == 0;   // has a form with sums through LDS
+  if (a.stats) launch(k_composite_bwd<TILE, true, LDSB, false>);
+  else if (kSums && a.n_tiles >= kLdsSumTiles) launch(k_composite_bwd<TILE, false, LDSB, kSums>);
+  else launch(k_composite_bwd<TILE, false, LDSB, false>);
   VBM_LAUNCH_CHECK("composite_bwd");
   return VBM_OK;
 }

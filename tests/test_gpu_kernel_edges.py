@@ -258,3 +258,33 @@ def test_adaptive_parts(G, J, values, K_tot, params):
         c[rng.uniform(size=c.shape) < 0.01] = -np.inf
     kept, stats = api.adaptive_select(torch.from_numpy(c).to(dev()), G, J, K_tot, **params)
     adaptive_check(c, G, J, kept.cpu().numpy(), stats.cpu().numpy(), K_tot, **params)
+
+
+# From 15,000 tiles on the backward adds up two list entries at a time through LDS.  A 24 x H view beside a large one of
+# another scene, whose one Gaussian is too faint to be listed: odd and even lists, a single entry, alphas beyond the clamp
+# (opacity 1), lists shared by four waves (400 entries: more than 1/2048 of the pairs).
+@pytest.mark.parametrize("n,H,tile,opacity,log_scale", [
+    (1, 16, 16, (0.5, 0.6), -1.5), (2, 16, 16, (0.5, 0.6), -1.5), (15, 13, 16, (0.2, 0.6), -2.0),
+    (15, 13, 8, (0.9, 1.0), -1.5), (64, 16, 8, (0.2, 0.6), -2.0), (400, 16, 16, (0.5, 1.0), -2.0),
+    (400, 16, 8, (0.01, 0.05), -2.6)])
+def test_backward_sums_of_many_tiles(n, H, tile, opacity, log_scale):
+    api = _api()
+    say(f"many tiles n={n} 24x{H} tile={tile} opacity {opacity} log scale {log_scale}")
+    gs = vi.random_gaussians(n, 171 + n, log_scale_mean=log_scale, opacity_range=opacity)
+    cams = vi.orbit_cameras(1, 24, H, azimuth0=0.9)
+    side = (2048, 1920) if tile == 16 else (1024, 960)     # 15,360 tiles
+    both = cams + vi.orbit_cameras(1, *side, azimuth0=0.9)
+    faint = vi.random_gaussians(1, 1, opacity_range=(0.001, 0.001))
+    P = torch.cat([to_dev(gs), to_dev(faint)], dim=1).contiguous()
+    rp = api.plan_batch(both, [0, n, n + 1], [0, 1], tile=tile, pair_capacity=1 << 16)
+    batch = render.Batch(gs, cams, tile)
+    ref = render.render_forward(batch)
+    dL = masked_dL(cams, [r["flagged"] for r in ref], seed=n)
+    g_ref, _ = render.render_backward(batch, dL)
+    out = api.render_fwd(rp, P)
+    grad = torch.zeros_like(out.image)
+    grad[:3 * 24 * H] = flat(dL)
+    G = api.render_bwd(rp, P, grad, out).cpu().numpy()
+    for name, rows in ROWS.items():
+        assert group_error(G[rows, :n], g_ref[name].reshape(rows.stop - rows.start, -1)) <= GRAD_TOL, name
+        assert not G[rows, n].any()
