@@ -48,6 +48,18 @@ struct Window {
   float w[2 * RAD + 1];
 };
 
+// The weights in vector registers: a SIMD issues a multiply-add with a scalar operand at half the rate (four views of
+// 517 x 389: 36.2 -> 33.1 us).
+struct LaneWindow {
+  float w[2 * RAD + 1];
+  __device__ __forceinline__ explicit LaneWindow(const Window& win) {
+#pragma unroll
+    for (int i = 0; i <= RAD; ++i) __asm__("v_mov_b32 %0, %1" : "=v"(w[i]) : "s"(win.w[i]));
+#pragma unroll
+    for (int i = 0; i < RAD; ++i) w[2 * RAD - i] = w[i];   // symmetric
+  }
+};
+
 Window make_window() {
   Window W;
   double s = 0, g[2 * RAD + 1];
@@ -180,7 +192,7 @@ __device__ __forceinline__ void load_halo(const float* const (&src)[NF], int W, 
 // x, y, x^2 + y^2 and x y.  Their horizontally filtered maps over the (TY + 10) x TX halo rows are
 // staged in LDS; each thread then filters a 4-row strip of one column vertically.
 __global__ __launch_bounds__(256) void k_ssim_maps(const float* __restrict__ x, const float* __restrict__ y, int W,
-                                                   int H, int tiles_x, int tiles, int n_blocks, Window win,
+                                                   int H, int tiles_x, int tiles, int n_blocks, Window window,
                                                    float* __restrict__ p1,
                                                    float* __restrict__ p2, float* __restrict__ p3,
                                                    float* __restrict__ partial_s, float* __restrict__ partial_l1) {
@@ -195,6 +207,7 @@ __global__ __launch_bounds__(256) void k_ssim_maps(const float* __restrict__ x, 
   auto sy = sxy[1];
   SsimBlock blk;
   if (!ssim_block(static_cast<int>(blockIdx.x), tiles, n_blocks, blk)) return;
+  const LaneWindow win(window);
   const int c = blk.c;
   const int bx = blk.tile % tiles_x, by = blk.tile / tiles_x;
   const int64_t HW = static_cast<int64_t>(W) * H;
@@ -321,7 +334,7 @@ __global__ __launch_bounds__(256) void k_ssim_maps(const float* __restrict__ x, 
 // Pass 2: dL/dx = w_l1 sign(x - y) - w_ssim [w*p1 + 2 x (w*p2) + y (w*p3)], same tiling; the
 // horizontal pass filters four adjacent columns per task, reading each input once for all four.
 __global__ __launch_bounds__(256) void k_ssim_grad(const float* __restrict__ x, const float* __restrict__ y, int W,
-                                                   int H, int tiles_x, int tiles, int n_blocks, Window win,
+                                                   int H, int tiles_x, int tiles, int n_blocks, Window window,
                                                    const float* __restrict__ p1,
                                                    const float* __restrict__ p2, const float* __restrict__ p3,
                                                    float w_l1, float w_ssim, float* __restrict__ grad, LossSum sum) {
@@ -337,6 +350,7 @@ __global__ __launch_bounds__(256) void k_ssim_grad(const float* __restrict__ x, 
   }
   SsimBlock blk;
   if (!ssim_block(static_cast<int>(blockIdx.x) - (sum.loss ? 1 : 0), tiles, n_blocks, blk)) return;
+  const LaneWindow win(window);
   const int c = blk.c;
   const int bx = blk.tile % tiles_x, by = blk.tile / tiles_x;
   const int64_t HW = static_cast<int64_t>(W) * H;
