@@ -10,6 +10,8 @@
 namespace vbm {
 namespace {
 
+constexpr int kRows = 14;   // parameters of a Gaussian
+
 struct AdamParams {
   float lr[5];
   float beta1, beta2, eps;
@@ -33,32 +35,42 @@ __global__ __launch_bounds__(256) void k_adam(int64_t n, int64_t stride, float* 
     p.bc2 = 1.0f - powf(p.beta2, t);
   }
   const int64_t GS = g.stride, AS = act.stride;
+  // every load before the first store: a small set's time is that of one round trip instead of one per row
+  float x[kRows], gr[kRows], mm[kRows], vv[kRows];
 #pragma unroll
-  for (int r = 0; r < 14; ++r) {
+  for (int r = 0; r < kRows; ++r) {
+    const int64_t o = r * stride + i;
+    x[r] = raw[o];
+    gr[r] = r < 3 ? g.means[r * GS + i]
+            : r < 6 ? g.scales[(r - 3) * GS + i]
+            : r < 10 ? g.quats[(r - 6) * GS + i]
+            : r == 10 ? g.opacity[i] : g.rgb[(r - 11) * GS + i];
+    mm[r] = m[o];
+    vv[r] = v[o];
+  }
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) {
     const int grp = r < 3 ? 0 : (r < 6 ? 1 : (r < 10 ? 2 : (r == 10 ? 3 : 4)));
     const int64_t o = r * stride + i;
-    float x = raw[o];
-    float gr;
-    if (grp == 0) gr = g.means[r * GS + i];
-    else if (grp == 1) gr = g.scales[(r - 3) * GS + i] * expf(x);
-    else if (grp == 2) gr = g.quats[(r - 6) * GS + i];
-    else if (grp == 3) {
-      const float sg = 1.0f / (1.0f + expf(-x));
-      gr = g.opacity[i] * sg * (1.0f - sg);
-    } else gr = g.rgb[(r - 11) * GS + i];
-    const float mm = p.beta1 * m[o] + (1.0f - p.beta1) * gr;
-    const float vv = p.beta2 * v[o] + (1.0f - p.beta2) * gr * gr;
-    m[o] = mm;
-    v[o] = vv;
-    const float mhat = mm / p.bc1;
-    const float vhat = vv / p.bc2;
-    x -= p.lr[grp] * mhat / (sqrtf(vhat) + p.eps);
-    raw[o] = x;
-    if (grp == 0) act.means[r * AS + i] = x;
-    else if (grp == 1) act.scales[(r - 3) * AS + i] = expf(x);
-    else if (grp == 2) act.quats[(r - 6) * AS + i] = x;
-    else if (grp == 3) act.opacity[i] = 1.0f / (1.0f + expf(-x));
-    else act.rgb[(r - 11) * AS + i] = x;
+    if (grp == 1) {
+      gr[r] = gr[r] * expf(x[r]);
+    } else if (grp == 3) {
+      const float sg = 1.0f / (1.0f + expf(-x[r]));
+      gr[r] = gr[r] * sg * (1.0f - sg);
+    }
+    mm[r] = p.beta1 * mm[r] + (1.0f - p.beta1) * gr[r];
+    vv[r] = p.beta2 * vv[r] + (1.0f - p.beta2) * gr[r] * gr[r];
+    m[o] = mm[r];
+    v[o] = vv[r];
+    const float mhat = mm[r] / p.bc1;
+    const float vhat = vv[r] / p.bc2;
+    x[r] -= p.lr[grp] * mhat / (sqrtf(vhat) + p.eps);
+    raw[o] = x[r];
+    if (grp == 0) act.means[r * AS + i] = x[r];
+    else if (grp == 1) act.scales[(r - 3) * AS + i] = expf(x[r]);
+    else if (grp == 2) act.quats[(r - 6) * AS + i] = x[r];
+    else if (grp == 3) act.opacity[i] = 1.0f / (1.0f + expf(-x[r]));
+    else act.rgb[(r - 11) * AS + i] = x[r];
   }
 }
 
