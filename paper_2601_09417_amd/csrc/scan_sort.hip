@@ -416,6 +416,16 @@ __device__ __forceinline__ uint32_t block_places(const uint32_t (&digit)[kBlockS
   return total;
 }
 
+// OR over the wave's lanes, by all of them.
+__device__ __forceinline__ uint32_t wave_or(uint32_t v) {
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);   // row_shr by 1, 2, 4, 8, then the rows' last lanes
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
+  return __builtin_amdgcn_readlane(v, 15) | __builtin_amdgcn_readlane(v, 31) | __builtin_amdgcn_readlane(v, 47) |
+         __builtin_amdgcn_readlane(v, 63);
+}
+
 // kSparse: the depth sort (see radix_sort_sparse).  kPairs: the pair sort with what follows it, the
 // tiles' ranges (cleared beforehand), launch order and the caller's status.  The output may be the input.
 template <bool kSparse, bool kPairs>
@@ -426,6 +436,7 @@ __global__ __launch_bounds__(kBlockSortThreads) void k_sort_block(const uint32_t
   __shared__ uint32_t s_key[kBlockSort];
   __shared__ uint32_t s_val[kBlockSort];
   __shared__ uint32_t s_cnt[kBlockSortWaves][256];   // per-wave digit counts, then per-wave digit bases
+  __shared__ uint2 s_bits[kBlockSortWaves];
   int n = static_cast<int>(active_count(n_max, n_dev));
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   uint32_t keys[kBlockSortItems], vals[kBlockSortItems], digit[kBlockSortItems], slot[kBlockSortItems];
@@ -437,7 +448,26 @@ __global__ __launch_bounds__(kBlockSortThreads) void k_sort_block(const uint32_t
     keys[r] = in ? kin[i] : 0u;
     vals[r] = kSparse ? static_cast<uint32_t>(i) : in ? vin[i] : 0u;
   }
-  for (int shift = 0; shift < end_bit; shift += 8) {
+  int shift0 = 0;
+  if (kSparse) {
+    // Only the bits in which the keys differ are sorted by: a scene's depths share most of their exponent, so that a
+    // pass of four is saved.  At least one pass leaves the absent ones behind.
+    uint32_t ones = 0, zeros = 0;
+#pragma unroll
+    for (int r = 0; r < kBlockSortItems; ++r) {
+      ones |= keys[r];
+      zeros |= keys[r] ? ~keys[r] : 0u;
+    }
+    ones = wave_or(ones);
+    zeros = wave_or(zeros);
+    if (lane == 0) s_bits[w] = make_uint2(ones, zeros);
+    __syncthreads();
+    const uint2 b = s_bits[lane % kBlockSortWaves];
+    const uint32_t differ = wave_or(b.x) & wave_or(b.y);
+    end_bit = min(end_bit, differ ? 32 - __builtin_clz(differ) : 1);
+    shift0 = min(differ ? __builtin_ctz(differ) : 0, end_bit - 1);
+  }
+  for (int shift = shift0; shift < end_bit; shift += 8) {
     const uint32_t mask = (1u << min(8, end_bit - shift)) - 1u;
 #pragma unroll
     for (int r = 0; r < kBlockSortItems; ++r) {
@@ -471,22 +501,39 @@ __global__ __launch_bounds__(kBlockSortThreads) void k_sort_block(const uint32_t
     if (i >= n) continue;
     kout[i] = keys[r];
     vout[i] = vals[r];
-    if (kPairs) {   // (a batch of one tile has no digits and one run)
-      const uint32_t tile = keys[r];
-      if (i == 0 || (end_bit != 0 && s_key[i - 1] != tile)) lists.ranges[tile].x = static_cast<uint32_t>(i);
-      if (i + 1 == n || (end_bit != 0 && s_key[i + 1] != tile)) lists.ranges[tile].y = static_cast<uint32_t>(i + 1);
-    }
   }
   if (kSparse && threadIdx.x == 0) *count_out = static_cast<uint32_t>(n);
   if (kPairs) {
-    __threadfence();
-    __syncthreads();
+    // The runs' ends through LDS, in the sorted keys' and values' place (there are at most as many tiles).
+    uint32_t first = 0, last = 0;   // a bit per round
+#pragma unroll
+    for (int r = 0; r < kBlockSortItems; ++r) {
+      const int i = (w * rounds + r) * 64 + lane;
+      if (r >= rounds || i >= n) continue;   // (a batch of one tile has no digits and one run)
+      first |= (i == 0 || (end_bit != 0 && s_key[i - 1] != keys[r]) ? 1u : 0u) << r;
+      last |= (i + 1 == n || (end_bit != 0 && s_key[i + 1] != keys[r]) ? 1u : 0u) << r;
+    }
     const int tiles = static_cast<int>(lists.n_tiles);
+    __syncthreads();
+    for (int t = threadIdx.x; t < tiles; t += kBlockSortThreads) s_key[t] = s_val[t] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kBlockSortItems; ++r) {
+      const uint32_t i = static_cast<uint32_t>((w * rounds + r) * 64 + lane);
+      if ((first >> r) & 1u) s_key[keys[r]] = i;
+      if ((last >> r) & 1u) s_val[keys[r]] = i + 1u;
+    }
+    __syncthreads();
     rounds = (tiles + kBlockSortThreads - 1) / kBlockSortThreads;
 #pragma unroll
     for (int r = 0; r < kBlockSortItems; ++r) {
       const int i = (w * rounds + r) * 64 + lane;
-      digit[r] = r < rounds && i < tiles ? length_key(lists.ranges[i]) : 256u;
+      digit[r] = 256u;
+      if (r < rounds && i < tiles) {
+        const uint2 range = make_uint2(s_key[i], s_val[i]);
+        lists.ranges[i] = range;
+        digit[r] = length_key(range);
+      }
     }
     block_places(digit, rounds, s_cnt, slot);
 #pragma unroll
