@@ -22,6 +22,18 @@ __device__ __forceinline__ T wave_incl_scan(T v) {
   return v;
 }
 
+// The same for 32-bit values in registers: shifts inside rows of 16, then each row's last lane to the rows after it.
+template <>
+__device__ __forceinline__ uint32_t wave_incl_scan<uint32_t>(uint32_t v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);   // row_shr 1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast 15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast 31 into rows 2 and 3
+  return v;
+}
+
 // Exclusive scan of one value per thread across a 256-thread block; block total in *total.
 // Every thread of the block must call it (it synchronises).
 template <class T>

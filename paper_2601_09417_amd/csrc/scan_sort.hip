@@ -372,8 +372,10 @@ __device__ __forceinline__ uint32_t block_places(const uint32_t (&digit)[kBlockS
                                                  uint32_t (*__restrict__ s_cnt)[256],
                                                  uint32_t (&slot)[kBlockSortItems]) {
   const int w = threadIdx.x >> 6;
-  for (int x = threadIdx.x; x < kBlockSortWaves * 256; x += kBlockSortThreads) (&s_cnt[0][0])[x] = 0u;
-  __syncthreads();
+  // a wave's own counts, which no other has touched since the last barrier
+  reinterpret_cast<uint4*>(s_cnt[w])[lane_id()] = make_uint4(0u, 0u, 0u, 0u);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 #pragma unroll
   for (int r = 0; r < kBlockSortItems; ++r) {
     if (r >= rounds) break;
