@@ -1,7 +1,7 @@
 // Stable LSD radix sort (gfx950, wave64, 256-thread blocks).
 //
 // One histogram kernel counts the digits of every pass in one read of the
-// keys, then each pass is a single kernel over 8192-key tiles that ranks equal digits inside each
+// keys, then each pass is a single kernel over tiles of 8192 keys (4096 or 2048 for few keys) that ranks equal digits inside each
 // wave with ballots (a lane's rank = set bits of its digit-match mask below it) and across a
 // wave's rounds through per-wave LDS counters, learns the earlier tiles' digit counts by
 // decoupled look-back, partitions the tile in LDS, and writes it out in digit order (coalesced
@@ -59,7 +59,7 @@ constexpr uint32_t kFlagInc = 2u << 30;   // status word: the count in this tile
 constexpr uint32_t kCountMask = kFlagAgg - 1u;
 constexpr int kFallbackRounds = 128;  // look-back rounds that find a tile unpublished before counting it directly
 constexpr int kLookback = 8;          // earlier tiles' status words read per look-back round
-// Threads of a one-sweep pass block (kItems keys each, so 8192-key tiles): at workload H the pass
+// Threads of a one-sweep pass block (kItems keys each in a large sort, so 8192-key tiles): at workload H the pass
 // time per step was 0.435 ms with 4096-key tiles, 0.404 ms with 8192 and 0.461 ms with 16384 (one
 // block per CU); fewer tiles shorten the look-back chain and lengthen each digit's output run.
 constexpr int kSweepThreads = 512;
@@ -174,8 +174,8 @@ __device__ __forceinline__ uint32_t split_key(uint32_t pairs, uint32_t share) {
   return steps > 255u ? 0u : 256u - steps;
 }
 
-// One stable pass over tiles of NT x 16 keys.  Wave w of a tile owns keys [1024 w, 1024 w + 1024)
-// and ranks them in 16 rounds of 64 against its own LDS digit counters: a lane's rank among the
+// One stable pass over tiles of NT x I keys.  Wave w of a tile owns keys [64 I w, 64 I (w + 1))
+// and ranks them in I rounds of 64 against its own LDS digit counters: a lane's rank among the
 // round's equal digits comes from ballots, and the wave's LDS operations complete in issue order,
 // so a round reads its digits' counters before its leaders advance them with no barrier in
 // between.  The per-wave counts give the tile's digit counts (published for the later tiles) and
@@ -187,7 +187,13 @@ __device__ __forceinline__ uint32_t split_key(uint32_t pairs, uint32_t share) {
 // to ranges[key] as (~first, last + 1), both by maximum from 0, since a key's run can span tiles.
 // kOrder: the tile order's pass (sparse); it also writes the number of split tiles.
 enum SweepKind { kPlainPass, kSparsePass, kRangesPass, kOrderPass };
-template <int NT, SweepKind kKind>
+// I: keys per thread.  16 move the most keys a second, but up to kSmallSweep keys such tiles are fewer than the CUs or
+// hardly more, and a pass takes as long as a tile: us a pass with 16 / 8 / 4 (keys): 14.5 / 10.5 / 9 (about 100,000),
+// 16.4 / 13.3 / 13.1 (360,000), 22 / 19.5 / 21.5 (1.1M), 25.3 / 25.3 / 28.6 (2.4M), 58 / 66 / 87 (7.9M).  The tile order's pass has
+// at most some ten thousand keys: 12.4 / 8.1 / 6.4 for 8,160 tiles, 14.7 / 10.5 / 9.1 for 65,280.
+constexpr int kSmallItems = 8, kOrderItems = 4;
+constexpr int64_t kSmallSweep = 2 << 20;
+template <int NT, int I, SweepKind kKind>
 __global__ __launch_bounds__(NT) void k_radix_onesweep(const uint32_t* __restrict__ kin,
                                                        const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
                                                        uint32_t* __restrict__ vout,
@@ -197,7 +203,7 @@ __global__ __launch_bounds__(NT) void k_radix_onesweep(const uint32_t* __restric
                                                        uint32_t* __restrict__ count_out, uint2* __restrict__ ranges,
                                                        TileLists lists) {
   constexpr bool kSparse = kKind == kSparsePass || kKind == kOrderPass, kRanges = kKind == kRangesPass;
-  constexpr int CH = NT * kItems;          // keys per tile
+  constexpr int CH = NT * I;          // keys per tile
   constexpr int NW = NT / 64;
   constexpr int kPerWave = CH / NW;
   __shared__ uint32_t s_key[CH];
@@ -216,18 +222,18 @@ __global__ __launch_bounds__(NT) void k_radix_onesweep(const uint32_t* __restric
   const uint32_t mask = static_cast<uint32_t>(radix - 1);
   const int w = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
-  uint32_t keys[kItems];
-  uint32_t vals[kItems];
+  uint32_t keys[I];
+  uint32_t vals[I];
 #pragma unroll
-  for (int r = 0; r < kItems; ++r) {
+  for (int r = 0; r < I; ++r) {
     const int li = w * kPerWave + r * 64 + lane;
     keys[r] = li < in_tile ? kin[base + li] : 0u;
     vals[r] = kSparse ? static_cast<uint32_t>(base + li) : li < in_tile ? vin[base + li] : 0u;
   }
   __syncthreads();
-  uint32_t slot[kItems];   // rank among the wave's keys of the same digit
+  uint32_t slot[I];   // rank among the wave's keys of the same digit
 #pragma unroll
-  for (int r = 0; r < kItems; ++r) {
+  for (int r = 0; r < I; ++r) {
     const bool valid = kSparse ? keys[r] != 0u : w * kPerWave + r * 64 + lane < in_tile;
     const uint32_t d = (keys[r] >> shift) & mask;
     uint64_t m = __ballot(valid);
@@ -323,7 +329,7 @@ __global__ __launch_bounds__(NT) void k_radix_onesweep(const uint32_t* __restric
   }
   __syncthreads();
 #pragma unroll
-  for (int r = 0; r < kItems; ++r) {
+  for (int r = 0; r < I; ++r) {
     if (kSparse ? keys[r] != 0u : w * kPerWave + r * 64 + lane < in_tile) {
       const uint32_t pos = s_cnt[w][(keys[r] >> shift) & mask] + slot[r];
       s_key[pos] = keys[r];
@@ -333,7 +339,7 @@ __global__ __launch_bounds__(NT) void k_radix_onesweep(const uint32_t* __restric
   __syncthreads();
   // write out in digit order
 #pragma unroll
-  for (int r = 0; r < kItems; ++r) {
+  for (int r = 0; r < I; ++r) {
     const int lp = r * NT + threadIdx.x;
     if (lp < count) {
       const uint32_t key = s_key[lp];
@@ -633,18 +639,22 @@ vbm_status sweep(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, int64_t
   uint32_t* tot = reinterpret_cast<uint32_t*>(scratch + L.off_tot);
   uint32_t* status = reinterpret_cast<uint32_t*>(scratch + L.off_status);
   const int passes = static_cast<int>(ceil_div(end_bit, digit_bits));
-  const dim3 grid(static_cast<unsigned>(ceil_div(n_max, kSweepThreads * kItems)));
+  const bool small = n_max <= kSmallSweep;
+  const dim3 grid(static_cast<unsigned>(ceil_div(n_max, kSweepThreads * (small ? kSmallItems : kItems))));
   for (int p = first; p < passes; ++p) {
     const int shift = p * digit_bits;
     const int bits = (end_bit - shift) < digit_bits ? (end_bit - shift) : digit_bits;
+    auto launch = [&](auto kernel, uint2* r) {
+      hipLaunchKernelGGL(kernel, grid, dim3(kSweepThreads), 0, s, k0, v0, k1, v1, tot + p * 256,
+                         status + p * L.nb * L.radix, n_max, n_dev, shift, bits, static_cast<uint32_t*>(nullptr), r,
+                         TileLists());
+    };
     if (ranges && p == passes - 1)
-      hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, kRangesPass>), grid, dim3(kSweepThreads), 0, s, k0, v0, k1,
-                         v1, tot + p * 256, status + p * L.nb * L.radix, n_max, n_dev, shift, bits,
-                         static_cast<uint32_t*>(nullptr), ranges, TileLists());
+      launch(small ? k_radix_onesweep<kSweepThreads, kSmallItems, kRangesPass>
+                   : k_radix_onesweep<kSweepThreads, kItems, kRangesPass>, ranges);
     else
-      hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, kPlainPass>), grid, dim3(kSweepThreads), 0, s, k0, v0, k1,
-                         v1, tot + p * 256, status + p * L.nb * L.radix, n_max, n_dev, shift, bits,
-                         static_cast<uint32_t*>(nullptr), static_cast<uint2*>(nullptr), TileLists());
+      launch(small ? k_radix_onesweep<kSweepThreads, kSmallItems, kPlainPass>
+                   : k_radix_onesweep<kSweepThreads, kItems, kPlainPass>, static_cast<uint2*>(nullptr));
     VBM_LAUNCH_CHECK("radix_onesweep");
     std::swap(k0, k1);
     std::swap(v0, v1);
@@ -682,8 +692,11 @@ vbm_status radix_sort_sparse(const uint32_t* keys, int64_t n, uint32_t* k0, uint
                      static_cast<const uint32_t*>(nullptr), end_bit, digit_bits, passes, tot, status,
                      static_cast<int64_t>(passes) * L.nb * L.radix);
   VBM_LAUNCH_CHECK("radix_upsweep");
-  hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, kSparsePass>), dim3(ceil_div(n, kSweepThreads * kItems)),
-                     dim3(kSweepThreads), 0, s, keys, static_cast<const uint32_t*>(nullptr), k0, v0, tot, status, n,
+  const bool small = n <= kSmallSweep;
+  hipLaunchKernelGGL((small ? k_radix_onesweep<kSweepThreads, kSmallItems, kSparsePass>
+                            : k_radix_onesweep<kSweepThreads, kItems, kSparsePass>),
+                     dim3(ceil_div(n, kSweepThreads * (small ? kSmallItems : kItems))), dim3(kSweepThreads), 0, s, keys,
+                     static_cast<const uint32_t*>(nullptr), k0, v0, tot, status, n,
                      static_cast<const uint32_t*>(nullptr), 0, end_bit < digit_bits ? end_bit : digit_bits, count_dev,
                      static_cast<uint2*>(nullptr), TileLists());
   VBM_LAUNCH_CHECK("radix_onesweep");
@@ -723,10 +736,10 @@ vbm_status sort_pairs_by_tile(uint32_t* const k[2], uint32_t* const v[2], int fi
   uint32_t* hist = tile_order_counts(scratch);
   uint32_t* look = reinterpret_cast<uint32_t*>(static_cast<char*>(scratch) + L.off_status);
   hipLaunchKernelGGL(k_tile_keys, dim3(static_cast<unsigned>(ceil_div(NT, 256))), dim3(256), 0, s, lists, capacity,
-                     end_bit == 0 ? 1 : 0, lists.keys, hist, look, L.nb * L.radix);
+                     end_bit == 0 ? 1 : 0, lists.keys, hist, look, ceil_div(NT, kSweepThreads * kOrderItems) * L.radix);
   VBM_LAUNCH_CHECK("tile_keys");
-  hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, kOrderPass>),
-                     dim3(static_cast<unsigned>(ceil_div(NT, kSweepThreads * kItems))), dim3(kSweepThreads), 0, s,
+  hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, kOrderItems, kOrderPass>),
+                     dim3(static_cast<unsigned>(ceil_div(NT, kSweepThreads * kOrderItems))), dim3(kSweepThreads), 0, s,
                      lists.keys, static_cast<const uint32_t*>(nullptr), lists.keys + NT, lists.order, hist, look, NT,
                      static_cast<const uint32_t*>(nullptr), 0, 8, static_cast<uint32_t*>(nullptr), static_cast<uint2*>(nullptr),
                      lists);
