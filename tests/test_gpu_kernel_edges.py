@@ -288,3 +288,20 @@ def test_backward_sums_of_many_tiles(n, H, tile, opacity, log_scale):
     for name, rows in ROWS.items():
         assert group_error(G[rows, :n], g_ref[name].reshape(rows.stop - rows.start, -1)) <= GRAD_TOL, name
         assert not G[rows, n].any()
+
+
+# Footprints from a pixel to the whole image and from round to thin (axes 10^4 apart), where the tile test's short form
+# meets its margin: the same pairs as the oracle's four-edge test.
+@pytest.mark.parametrize("tile", [8, 16, 32])
+def test_pair_lists_of_thin_footprints(tile):
+    api = _api()
+    say(f"thin footprints tile={tile}")
+    gs = vi.random_gaussians(1500, 77, log_scale_mean=-3.5, log_scale_std=2.5, opacity_range=(0.004, 0.99))
+    cams = vi.orbit_cameras(2, 301, 203)
+    ref = binning.pair_lists(gs, cams, tile)
+    total = ref["tile"].size
+    rp = api.plan_batch(cams, [0, gs.n], tile=tile, pair_capacity=total)
+    out = api.render_fwd(rp, to_dev(gs))
+    assert out.status[:2].tolist() == [0, total]
+    assert np.array_equal(rp.region("pair_tile", torch.int32).cpu().numpy()[:total], ref["tile"])
+    assert np.array_equal(rp.region("pair_item", torch.int32).cpu().numpy()[:total] & ITEM_MASK, ref["item"])
