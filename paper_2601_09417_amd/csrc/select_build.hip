@@ -8,7 +8,7 @@
 // the candidates (12, 10 and 10 bits, most significant first) find the K-th largest key t; a last one
 // keeps every key > t plus the lowest-index keys == t until K are kept, in ascending index order, and builds
 // their Gaussians.
-// 512^3, K = 1M: 0.59 ms, where a key written per location and six passes over the keys took 1.93 ms (reading
+// 512^3, K = 1M: 0.56 ms, where a key written per location and six passes over the keys took 1.93 ms (reading
 // the coefficients takes 0.42 ms at the rate of a large copy).
 #include <hip/hip_runtime.h>
 
@@ -28,6 +28,9 @@ constexpr int kRegion = kT * kPerThread;   // locations per region: its candidat
 constexpr int kBins[3] = {4096, 1024, 1024};
 constexpr int kShift[3] = {20, 10, 0};
 constexpr int kHistWords = 4096 + 1024 + 1024;
+// Blocks of the passes over the candidates.  Their counts meet at the same bins: 256 / 512 / 1024 blocks take 62 / 53 / 58 us in
+// the three digits and the count (512^3, K = 1M), 97 us with a region at a time per wave and 1024.
+constexpr int kHistBlocks = 512;
 constexpr int kTallies = 64;               // candidate totals, spread over as many words
 constexpr int kGroup = 256;                // regions per partial sum of kept keys
 constexpr int kGroupsMax = 1024;           // 1024^3 locations
@@ -254,22 +257,52 @@ __global__ __launch_bounds__(kT) void k_candidates_all(const float* __restrict__
     region_candidates<kVec>(coeffs, M, r, 0u, cand_key, cand_idx, cnt, sc->sample);   // (no one reads that tally)
 }
 
-// Calls fn with every candidate key of a region, by one wave: four keys a lane at a time.
-template <class F>
-__device__ __forceinline__ void for_region_keys(const uint32_t* __restrict__ cand_key,
-                                                const uint32_t* __restrict__ cnt, int64_t r, int lane, F&& fn) {
-  const uint32_t n = cnt[r];
-  const uint4* src = reinterpret_cast<const uint4*>(cand_key + r * kRegion);   // (256-byte aligned workspace)
-  for (uint32_t i = lane; 4 * i < n; i += 64) {
-    const uint4 q = src[i];
-    fn(q.x);
+// Calls fn with every candidate key of the wave's regions and done(region) after each: a wave per region, four keys a
+// lane at a time.  The regions go to the waves in turn (the coarse levels' are full, most others hold some 30 candidates),
+// and a wave asks for the counts and first 256 keys of four of them together, so that few blocks, whose counts then
+// meet at the same addresses, keep as much in flight as many.
+template <class F, class D>
+__device__ __forceinline__ void for_candidates(const uint32_t* __restrict__ cand_key, const uint32_t* __restrict__ cnt,
+                                               int64_t regions, F&& fn, D&& done) {
+  constexpr int kAhead = 4;
+  const int lane = threadIdx.x & 63;
+  const int64_t waves = static_cast<int64_t>(gridDim.x) * (kT / 64);
+  auto use = [&](const uint4& q, uint32_t i, uint32_t n) {
+    if (4 * i < n) fn(q.x);
     if (4 * i + 1 < n) fn(q.y);
     if (4 * i + 2 < n) fn(q.z);
     if (4 * i + 3 < n) fn(q.w);
+  };
+  for (int64_t r0 = static_cast<int64_t>(blockIdx.x) * (kT / 64) + (threadIdx.x >> 6); r0 < regions;
+       r0 += kAhead * waves) {
+    uint32_t n[kAhead];
+    uint4 q[kAhead];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) n[k] = r0 + k * waves < regions ? cnt[r0 + k * waves] : 0u;
+    auto keys = [&](int k) {   // (256-byte aligned workspace)
+      return reinterpret_cast<const uint4*>(cand_key + (r0 + k * waves) * kRegion);
+    };
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k)
+      if (4u * lane < n[k]) q[k] = keys(k)[lane];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) {
+      if (r0 + k * waves >= regions) break;
+      use(q[k], lane, n[k]);
+      for (uint32_t i = 64 + lane; 4 * (i - lane) < n[k]; i += 64 * kAhead) {
+        uint4 p[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+          if (4 * (i + 64 * u) < n[k]) p[u] = keys(k)[i + 64 * u];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) use(p[u], i + 64 * u, n[k]);
+      }
+      done(r0 + k * waves);
+    }
   }
 }
 
-// Digit D of the candidates whose higher digits are those picked so far, counted; a wave per region.
+// Digit D of the candidates whose higher digits are those picked so far, counted.
 template <int D>
 __global__ __launch_bounds__(kT) void k_select_hist(const uint32_t* __restrict__ cand_key,
                                                     const uint32_t* __restrict__ cnt, int64_t regions, uint32_t K,
@@ -288,13 +321,12 @@ __global__ __launch_bounds__(kT) void k_select_hist(const uint32_t* __restrict__
   }
   __syncthreads();
   constexpr uint32_t kHigh = D == 0 ? 0u : ~((1u << kShift[D > 0 ? D - 1 : 0]) - 1u);
-  const int lane = threadIdx.x & 63;
-  for (int64_t r = static_cast<int64_t>(blockIdx.x) * (kT / 64) + (threadIdx.x >> 6); r < regions;
-       r += static_cast<int64_t>(gridDim.x) * (kT / 64)) {
-    for_region_keys(cand_key, cnt, r, lane, [&](uint32_t k) {
-      if ((k & kHigh) == prefix) atomicAdd(&s_hist[(k >> kShift[D]) & (kBins[D] - 1)], 1u);
-    });
-  }
+  for_candidates(
+      cand_key, cnt, regions,
+      [&](uint32_t k) {
+        if ((k & kHigh) == prefix) atomicAdd(&s_hist[(k >> kShift[D]) & (kBins[D] - 1)], 1u);
+      },
+      [](int64_t) {});
   __syncthreads();
   uint32_t* h = sc->hist + (D == 0 ? 0 : D == 1 ? kBins[0] : kBins[0] + kBins[1]);
   for (int i = threadIdx.x; i < kBins[D]; i += kT)
@@ -305,7 +337,7 @@ __device__ __forceinline__ uint64_t select_flags(uint32_t key, uint32_t thr) {
   return (key > thr ? 1ull : 0ull) | (key == thr ? (1ull << 32) : 0ull);
 }
 
-// Keys above the K-th largest, and equal to it (high half), of each region and each group of regions; a wave per region.
+// Keys above the K-th largest, and equal to it (high half), of each region.
 __global__ __launch_bounds__(kT) void k_select_count(const uint32_t* __restrict__ cand_key,
                                                      const uint32_t* __restrict__ cnt, int64_t regions,
                                                      SelectScratch* __restrict__ sc, uint64_t* __restrict__ sums) {
@@ -316,17 +348,25 @@ __global__ __launch_bounds__(kT) void k_select_count(const uint32_t* __restrict_
     sc->st.prefix[2] = thr;
     sc->st.rest[2] = rest;
   }
-  const int lane = threadIdx.x & 63;
-  for (int64_t r = static_cast<int64_t>(blockIdx.x) * (kT / 64) + (threadIdx.x >> 6); r < regions;
-       r += static_cast<int64_t>(gridDim.x) * (kT / 64)) {
-    uint64_t acc = 0;
-    for_region_keys(cand_key, cnt, r, lane, [&](uint32_t k) { acc += select_flags(k, thr); });
-    for (int d = 32; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, 64);
-    if (lane == 0) {
-      sums[r] = acc;
-      if (acc) atomicAdd(&sc->group[r / kGroup], static_cast<unsigned long long>(acc));
-    }
-  }
+  uint64_t acc = 0;
+  for_candidates(
+      cand_key, cnt, regions, [&](uint32_t k) { acc += select_flags(k, thr); },
+      [&](int64_t r) {
+        for (int d = 32; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, 64);
+        if ((threadIdx.x & 63) == 0) sums[r] = acc;
+        acc = 0;
+      });
+}
+
+// The same of each group of regions, a block per group (added by k_select_count's waves as they went, the sums of 256
+// regions met at one address: 45 us for both against 18).
+__global__ __launch_bounds__(kT) void k_select_groups(const uint64_t* __restrict__ sums, int64_t regions,
+                                                      SelectScratch* __restrict__ sc) {
+  static_assert(kGroup == kT, "a thread per region");
+  const int64_t r = static_cast<int64_t>(blockIdx.x) * kGroup + threadIdx.x;
+  uint64_t total;
+  block_excl_scan(r < regions ? sums[r] : uint64_t{0}, &total);
+  if (threadIdx.x == 0) sc->group[blockIdx.x] = total;
 }
 
 struct BuildParams {
@@ -565,7 +605,7 @@ extern "C" vbm_status vbm_build_gaussians(const float* coeffs, int32_t G, int32_
                        0, s, coeffs, M, K, regions, w.sc, w.cand_key, w.cand_idx, w.cnt);
     VBM_LAUNCH_CHECK("candidates_all");
   }
-  const dim3 hist_grid(grid_cap(ceil_div(regions, kT / 64), 1024));
+  const dim3 hist_grid(grid_cap(ceil_div(regions, kT / 64), kHistBlocks));
   const uint32_t K32 = static_cast<uint32_t>(K);
   hipLaunchKernelGGL(k_select_hist<0>, hist_grid, dim3(kT), 0, s, w.cand_key, w.cnt, regions, K32, w.sc);
   VBM_LAUNCH_CHECK("select_hist");
@@ -575,6 +615,9 @@ extern "C" vbm_status vbm_build_gaussians(const float* coeffs, int32_t G, int32_
   VBM_LAUNCH_CHECK("select_hist");
   hipLaunchKernelGGL(k_select_count, hist_grid, dim3(kT), 0, s, w.cand_key, w.cnt, regions, w.sc, w.sums);
   VBM_LAUNCH_CHECK("select_count");
+  hipLaunchKernelGGL(k_select_groups, dim3(static_cast<unsigned>(ceil_div(regions, kGroup))), dim3(kT), 0, s, w.sums,
+                     regions, w.sc);
+  VBM_LAUNCH_CHECK("select_groups");
   hipLaunchKernelGGL(k_select_build, dim3(static_cast<unsigned>(regions)), dim3(kT), 0, s, coeffs, w.cand_key,
                      w.cand_idx, w.cnt, w.sc, w.sums, bank_dev, p, out, kept_index);
   VBM_LAUNCH_CHECK("select_build");
