@@ -632,7 +632,7 @@ struct BwdPix {
 // weights alpha T_before dL/dC.  False (for the whole wave) when no group is marked or, without marks, no pixel
 // takes part.
 // RARE: a clamped alpha, of which there are few, is handled in uniform branches instead of by a minimum and a select for
-// every pixel: fewer instructions, but a lone wave waits for every branch (see kLdsSumTiles).
+// every pixel: fewer instructions, but a lone wave waits for every branch (see kLdsSumShare).
 struct BwdSums {
   float s0, s1, s2, wr, wg, wb;
 };
@@ -822,20 +822,161 @@ __device__ __forceinline__ void bwd_walk_bands(BandLists& L, const uint32_t* __r
 template <int TILE>
 constexpr int kBwdThreads = TILE == 16 ? 256 : TileCfg<TILE>::kThreads;
 
+// Batches whose pairs are kLdsSumShare longest lists or more keep every SIMD supplied with waves, and the instructions
+// that a SIMD can issue set the backward's time: sums through LDS and branches around the rare cases save some.
+// With fewer, the time is that of the longest lists, whose waves wait for each LDS round trip and branch.  us with
+// sums in registers / this form (pairs over the longest list; the launch order's first tile has it, to a few entries):
+// 710 / 871 (1,800), 736 / 851 (2,400), 888 / 815 (3,700), 1248 / 1115 (4,700), 1559 / 1435 (7,400), 4028 / 3617 (11,000),
+// 1291 / 1151 (12,500); with 8x8 tiles 96 / 105 (2,200), 249 / 207 (6,000), 2177 / 2035 (50,000).
+constexpr uint32_t kLdsSumShare = 3000;
+template <int TILE, bool STATS, int LDSB>
+constexpr bool kBwdSums = TILE <= 16 && !STATS && LDSB == 0;   // the kernel has both forms
+
 // LDS of a backward block: a split tile's lists, or per wave the staged lists or the sums of two entries.
-template <int TILE, int LDSB, bool SUMS>
+template <int TILE, bool STATS, int LDSB>
+constexpr size_t bwd_wave_bytes() {
+  return kBwdSums<TILE, STATS, LDSB> ? sizeof(float) * kSumWords : LDSB > 0 ? sizeof(LdsBatch<LDSB == 0 ? 1 : LDSB>) : 16;
+}
+template <int TILE, bool STATS, int LDSB>
 constexpr size_t bwd_lds_bytes() {
-  const size_t wave = SUMS ? sizeof(float) * kSumWords : LDSB > 0 ? sizeof(LdsBatch<LDSB == 0 ? 1 : LDSB>) : 16;
-  const size_t waves = wave * (kBwdThreads<TILE> / 64);
+  const size_t waves = bwd_wave_bytes<TILE, STATS, LDSB>() * (kBwdThreads<TILE> / 64);
   return TILE == 16 && sizeof(BandLists) > waves ? sizeof(BandLists) : waves;
 }
 
-template <int TILE, bool STATS, int LDSB, bool SUMS>
+// A tile's list for the backward wave that walks it.
+struct BwdTile {
+  const uint32_t* __restrict__ values;   // pair values, from the list's first
+  const float4* __restrict__ crec;
+  const float* __restrict__ blue;
+  uint32_t imax;
+  int lane;
+  float fx;
+  float col0;      // the first of the lane's four columns in the sums through LDS
+  float* __restrict__ grad2d;
+};
+template <int TILE, int LDSB, bool SUMS, bool STATS, class F>
+__device__ __forceinline__ void bwd_walk_tile(const BwdTile& t, unsigned char* __restrict__ lds, F&& load_pixel,
+                                              uint32_t& n_eval, uint32_t& n_used) {
+  using C = TileCfg<TILE>;
+  constexpr int PPL = C::kPPL;
+  constexpr bool kCols = 16 % TILE == 0;   // lanes l, l + 16, l + 32, l + 48 share a pixel column
+  static_assert(!SUMS || (kCols && LDSB == 0), "sums through LDS: columns in rows of 16, no staged lists");
+  // 16x16 tiles walk the forward's marked copy; the sorted pair values of the others mark every group (an 8x8
+  // tile has one, which the projection has found within reach)
+  constexpr bool kMarked = TILE <= 16;
+  const int lane = t.lane;
+  BwdPix<PPL> P;
+  int maxn = 0;
+#pragma unroll
+  for (int k = 0; k < PPL; ++k) {
+    load_pixel(k, P.fy[k], P.T[k], P.nc[k], P.dr[k], P.dg[k], P.db[k], P.S[k]);
+    maxn = max(maxn, P.nc[k]);
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) maxn = max(maxn, __shfl_xor(maxn, d, 64));
+  maxn = __builtin_amdgcn_readfirstlane(maxn);
+  const float fx = t.fx;
+  const uint32_t imax = t.imax;
+  const uint32_t* __restrict__ values = t.values;
+  const float4* __restrict__ crec = t.crec;
+  const float* __restrict__ blue = t.blue;
+  float* __restrict__ grad2d = t.grad2d;
+  const int out_k = kCols ? col_index(lane) : rs_index(lane & 15);
+  const bool out_lane = kCols ? out_k >= 0 : lane < 16 && ((lane & 1) == 0 || lane == 1);
+  float* red = reinterpret_cast<float*>(lds);   // with SUMS
+  const int sum_k = sum_column(lane);
+  int slot = 0;   // entries in red
+  float mx0 = 0.0f;
+  uint32_t item0 = 0;
+  auto flush = [&](int n, float mx1, uint32_t item1) __attribute__((always_inline)) {
+    const bool second = lane >= 24;
+    const float sum = sums_total(red, lane, second ? mx1 : mx0, t.col0);
+    if (sum_k >= 0 && lane < 24 * n && sum != 0.0f)
+      unsafeAtomicAdd(&grad2d[16 * static_cast<size_t>(second ? item1 : item0) + sum_k], sum);
+  };
+  auto step = [&](const Rec& r, uint32_t pv, int j) __attribute__((always_inline)) {
+    const float dx = r.mx - fx, dx2 = dx * dx;
+    BwdSums s;
+    if (!bwd_step<PPL, kMarked, SUMS, STATS>(r, pv >> kItemBits, j, dx, dx2, P, s, n_eval, n_used)) return;
+    const uint32_t item = pv & kItemMask;
+    if constexpr (SUMS) {
+      sums_put(red, slot, lane, s);
+      if (slot == 0) {
+        mx0 = r.mx;
+        item0 = item;
+        slot = 1;
+        return;
+      }
+      flush(2, r.mx, item);
+      slot = 0;
+    } else {
+      float sum;
+      if constexpr (kCols) {
+        sum = reduce_cols9(s.s0, s.s1, s.s2, s.wr, s.wg, s.wb, dx, dx2, lane);
+      } else {
+        const float g[9] = {dx * s.s0, s.s1, dx2 * s.s0, dx * s.s1, s.s2, s.s0, s.wr, s.wg, s.wb};
+        sum = reduce_scatter9(g, lane);
+      }
+      if (out_lane && sum != 0.0f) unsafeAtomicAdd(&grad2d[16 * static_cast<size_t>(item) + out_k], sum);
+    }
+  };
+  if constexpr (LDSB > 0) {
+    static_assert(C::kWaves == 1, "LDS batches are wave-private");
+    // LDS batches walked in reverse: the batch ending at list position hi holds
+    // positions hi, hi - 1, ... in lanes 0, 1, ...
+    LdsBatch<LDSB>& L = *reinterpret_cast<LdsBatch<LDSB>*>(lds);
+    uint32_t pv;
+    float4 ra, rb;
+    float bl;
+    int hi = maxn - 1;
+    lds_fetch(values, crec, blue, imax, hi - lane, lane < LDSB && hi - lane >= 0, pv, ra, rb, bl);
+    lds_put<LDSB>(L, 0, lane, ra, rb, bl, pv);
+    int buf = 0;
+    for (; hi >= 0; hi -= LDSB) {
+      const int nh = hi - LDSB;
+      lds_fetch(values, crec, blue, imax, nh - lane, lane < LDSB && nh - lane >= 0, pv, ra, rb, bl);
+      const int n = min(LDSB, hi + 1);
+      for (int b = 0; b < n; ++b) {
+        const Rec r = lds_get<LDSB>(L, buf, b);
+        step(r, lds_pv<LDSB>(L, buf, b), hi - b);
+      }
+      buf ^= 1;
+      lds_put<LDSB>(L, buf, lane, ra, rb, bl, pv);
+    }
+  } else {
+  // Records through the scalar cache one step ahead of their use, pair values through the scalar
+  // cache one step before the record they address, walking positions maxn - 1 .. 0 (positions
+  // below 0 are clamped to 0 and their loads never used).
+  const int top = max(maxn - 1, 0);
+  uint32_t u0 = values[top];
+  Rec R0 = load_rec_s(crec, blue, u0, imax), R1, R2;
+  uint32_t u1 = values[max(top - 1, 0)], u2;
+  for (int j = maxn - 1; j >= 0; j -= 3) {
+    wait_scalar_loads();
+    R1 = load_rec_s(crec, blue, u1, imax);
+    u2 = values[max(j - 2, 0)];
+    step(R0, u0, j);
+    if (j == 0) break;
+    wait_scalar_loads();
+    R2 = load_rec_s(crec, blue, u2, imax);
+    u0 = values[max(j - 3, 0)];
+    step(R1, u1, j - 1);
+    if (j == 1) break;
+    wait_scalar_loads();
+    R0 = load_rec_s(crec, blue, u0, imax);
+    u1 = values[max(j - 4, 0)];
+    step(R2, u2, j - 2);
+  }
+  }
+  if (SUMS && slot) flush(1, mx0, item0);
+}
+
+template <int TILE, bool STATS, int LDSB>
 __global__ __launch_bounds__(kBwdThreads<TILE>) void k_composite_bwd(
     const DevView* __restrict__ views, int n_views, int n_tiles, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ tile_order, const uint32_t* __restrict__ n_split,
-    const uint32_t* __restrict__ pair_item, const uint32_t* __restrict__ pair_marked,
-    const float* __restrict__ coef,
+    const uint32_t* __restrict__ n_pairs, const uint32_t* __restrict__ pair_item,
+    const uint32_t* __restrict__ pair_marked, const float* __restrict__ coef,
     const float* __restrict__ blue, const float* __restrict__ final_T, const int32_t* __restrict__ n_contrib,
     const float* __restrict__ dL_dimg, float* __restrict__ grad2d, int64_t n_items,
     unsigned long long* __restrict__ stats) {
@@ -877,12 +1018,8 @@ __global__ __launch_bounds__(kBwdThreads<TILE>) void k_composite_bwd(
   const int start = static_cast<int>(uniform(ranges[tile].x));
   // Lanes l, l + 16, l + 32, l + 48 share a pixel column when the tile is at most 16 wide.
   constexpr bool kCols = 16 % TILE == 0;
-  static_assert(!SUMS || (kCols && LDSB == 0), "sums through LDS: columns in rows of 16, no staged lists");
-  const int out_k = kCols ? col_index(lane) : rs_index(lane & 15);
-  const bool out_lane = kCols ? out_k >= 0 : lane < 16 && ((lane & 1) == 0 || lane == 1);
   const float4* __restrict__ crec = reinterpret_cast<const float4*>(coef);
-  __shared__ __align__(16) unsigned char lds[bwd_lds_bytes<TILE, LDSB, SUMS>()];
-  const int lds_wave = TILE == 16 ? block_wave : 0;
+  __shared__ __align__(16) unsigned char lds[bwd_lds_bytes<TILE, STATS, LDSB>()];
   if constexpr (TILE == 16) {
     if (split) {   // uniform for the block
       BandLists& bands = *reinterpret_cast<BandLists*>(lds);
@@ -890,115 +1027,30 @@ __global__ __launch_bounds__(kBwdThreads<TILE>) void k_composite_bwd(
       load_pixel(ty * TILE + (lane + 64 * block_wave) / TILE, P.fy[0], P.T[0], P.nc[0], P.dr[0], P.dg[0], P.db[0],
                  P.S[0]);
       uint32_t n_used = 0;
-      bwd_walk_bands<STATS>(bands, pair_marked, start, crec, blue, block_wave, lane, fx, P, out_k, out_lane, grad2d,
+      const int out_k = col_index(lane);
+      bwd_walk_bands<STATS>(bands, pair_marked, start, crec, blue, block_wave, lane, fx, P, out_k, out_k >= 0, grad2d,
                             n_used);
       if (STATS) add_stats(stats, static_cast<uint32_t>(P.nc[0]), n_used);
       return;
     }
   }
-  BwdPix<PPL> P;
-  int maxn = 0;
-#pragma unroll
-  for (int k = 0; k < PPL; ++k) {
-    load_pixel(ty * TILE + (q0 + k * 64) / TILE, P.fy[k], P.T[k], P.nc[k], P.dr[k], P.dg[k], P.db[k], P.S[k]);
-    maxn = max(maxn, P.nc[k]);
-  }
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) maxn = max(maxn, __shfl_xor(maxn, d, 64));
-  maxn = __builtin_amdgcn_readfirstlane(maxn);
-  uint32_t n_eval = 0, n_used = 0;
-  // With 16x16 tiles the forward's marked copy (marks of the groups it evaluated); else the sorted pair values (every group
-  // marked; an 8x8 tile has one, which the projection has found within reach).
-  constexpr bool kMarked = TILE <= 16;
   const uint32_t* __restrict__ pair_values = TILE == 16 ? pair_marked : pair_item;
   const uint32_t imax = n_items > 0 ? static_cast<uint32_t>(n_items - 1) : 0u;
-  float* red = reinterpret_cast<float*>(lds) + (SUMS ? lds_wave * kSumWords : 0);
-  const float col0 = static_cast<float>(tx * TILE + (4 * (lane & 3)) % TILE) + 0.5f;   // of the lane's columns in red
-  const int sum_k = sum_column(lane);
-  int slot = 0;   // entries in red
-  float mx0 = 0.0f;
-  uint32_t item0 = 0;
-  auto flush = [&](int n, float mx1, uint32_t item1) __attribute__((always_inline)) {
-    const bool second = lane >= 24;
-    const float sum = sums_total(red, lane, second ? mx1 : mx0, col0);
-    if (sum_k >= 0 && lane < 24 * n && sum != 0.0f)
-      unsafeAtomicAdd(&grad2d[16 * static_cast<size_t>(second ? item1 : item0) + sum_k], sum);
-  };
-  auto step = [&](const Rec& r, uint32_t pv, int j) __attribute__((always_inline)) {
-    const float dx = r.mx - fx, dx2 = dx * dx;
-    BwdSums s;
-    if (!bwd_step<PPL, kMarked, SUMS, STATS>(r, pv >> kItemBits, j, dx, dx2, P, s, n_eval, n_used)) return;
-    const uint32_t item = pv & kItemMask;
-    if constexpr (SUMS) {
-      sums_put(red, slot, lane, s);
-      if (slot == 0) {
-        mx0 = r.mx;
-        item0 = item;
-        slot = 1;
-        return;
-      }
-      flush(2, r.mx, item);
-      slot = 0;
-    } else {
-      float sum;
-      if constexpr (kCols) {
-        sum = reduce_cols9(s.s0, s.s1, s.s2, s.wr, s.wg, s.wb, dx, dx2, lane);
-      } else {
-        const float g[9] = {dx * s.s0, s.s1, dx2 * s.s0, dx * s.s1, s.s2, s.s0, s.wr, s.wg, s.wb};
-        sum = reduce_scatter9(g, lane);
-      }
-      if (out_lane && sum != 0.0f) unsafeAtomicAdd(&grad2d[16 * static_cast<size_t>(item) + out_k], sum);
+  const uint32_t* __restrict__ values = pair_values + start;
+  uint32_t n_eval = 0, n_used = 0;
+  auto load = [&](int k, float& fy, float& T, int& nc, float& dr, float& dg, float& db, float& S)
+                  __attribute__((always_inline)) { load_pixel(ty * TILE + (q0 + k * 64) / TILE, fy, T, nc, dr, dg, db, S); };
+  unsigned char* wave_lds = lds + (TILE == 16 ? block_wave : 0) * bwd_wave_bytes<TILE, STATS, LDSB>();
+  const BwdTile tile_data{values, crec, blue, imax, lane, fx,
+                          static_cast<float>(tx * TILE + (4 * (lane & 3)) % TILE) + 0.5f, grad2d};
+  if constexpr (kBwdSums<TILE, STATS, LDSB>) {
+    const uint2 longest = ranges[tile_order[0]];
+    if (*n_pairs / kLdsSumShare >= longest.y - longest.x) {
+      bwd_walk_tile<TILE, LDSB, true, STATS>(tile_data, wave_lds, load, n_eval, n_used);
+      return;
     }
-  };
-  if constexpr (LDSB > 0) {
-    static_assert(C::kWaves == 1, "LDS batches are wave-private");
-    // LDS batches walked in reverse: the batch ending at list position hi holds
-    // positions hi, hi - 1, ... in lanes 0, 1, ...
-    LdsBatch<LDSB>& L = reinterpret_cast<LdsBatch<LDSB>*>(lds)[lds_wave];
-    uint32_t pv;
-    float4 ra, rb;
-    float bl;
-    int hi = maxn - 1;
-    lds_fetch(pair_values, crec, blue, imax, start + hi - lane, lane < LDSB && hi - lane >= 0, pv, ra, rb, bl);
-    lds_put<LDSB>(L, 0, lane, ra, rb, bl, pv);
-    int buf = 0;
-    for (; hi >= 0; hi -= LDSB) {
-      const int nh = hi - LDSB;
-      lds_fetch(pair_values, crec, blue, imax, start + nh - lane, lane < LDSB && nh - lane >= 0, pv, ra, rb, bl);
-      const int n = min(LDSB, hi + 1);
-      for (int b = 0; b < n; ++b) {
-        const Rec r = lds_get<LDSB>(L, buf, b);
-        step(r, lds_pv<LDSB>(L, buf, b), hi - b);
-      }
-      buf ^= 1;
-      lds_put<LDSB>(L, buf, lane, ra, rb, bl, pv);
-    }
-  } else {
-  // Records through the scalar cache one step ahead of their use, pair values through the scalar
-  // cache one step before the record they address, walking positions maxn - 1 .. 0 (positions
-  // below 0 are clamped to 0 and their loads never used).
-  const int top = max(maxn - 1, 0);
-  uint32_t u0 = pair_values[start + top];
-  Rec R0 = load_rec_s(crec, blue, u0, imax), R1, R2;
-  uint32_t u1 = pair_values[start + max(top - 1, 0)], u2;
-  for (int j = maxn - 1; j >= 0; j -= 3) {
-    wait_scalar_loads();
-    R1 = load_rec_s(crec, blue, u1, imax);
-    u2 = pair_values[start + max(j - 2, 0)];
-    step(R0, u0, j);
-    if (j == 0) break;
-    wait_scalar_loads();
-    R2 = load_rec_s(crec, blue, u2, imax);
-    u0 = pair_values[start + max(j - 3, 0)];
-    step(R1, u1, j - 1);
-    if (j == 1) break;
-    wait_scalar_loads();
-    R0 = load_rec_s(crec, blue, u0, imax);
-    u1 = pair_values[start + max(j - 4, 0)];
-    step(R2, u2, j - 2);
   }
-  }
-  if (SUMS && slot) flush(1, mx0, item0);
+  bwd_walk_tile<TILE, LDSB, false, STATS>(tile_data, wave_lds, load, n_eval, n_used);
   if (STATS) add_stats(stats, n_eval, n_used);
 }
 
@@ -1063,13 +1115,6 @@ static vbm_status launch_fwd_t(const CompositeArgs& a, float* image, float* fina
   return VBM_OK;
 }
 
-// Batches of so many tiles keep every SIMD supplied with waves, and the instructions that a SIMD can issue set the
-// backward's time: sums through LDS and branches around the rare cases save some.  With fewer, the time is that of the
-// longest lists, whose waves wait for each LDS round trip and branch.  us with sums in registers / this
-// form (tiles): 710 / 871 (11,340), 736 / 851 (12,544), 888 / 815 (16,320), 1248 / 1115 (24,480), 1559 / 1435 (32,640),
-// 1291 / 1151 (40,000), 4028 / 3617 (65,280); with 8x8 tiles 96 / 105 (7,600), 249 / 207 (24,000), 2177 / 2035 (160,000).
-constexpr int64_t kLdsSumTiles = 15000;
-
 template <int TILE, int LDSB>
 static vbm_status launch_bwd_t(const CompositeArgs& a, const float* final_T, const int32_t* n_contrib,
                                const float* dL_dimg, float* grad2d, hipStream_t s) {
@@ -1078,13 +1123,10 @@ static vbm_status launch_bwd_t(const CompositeArgs& a, const float* final_T, con
   const dim3 grid(static_cast<unsigned>(TILE == 16 ? split + ceil_div(a.n_tiles, 4) : a.n_tiles)), block(kBwdThreads<TILE>);
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, block, 0, s, a.views, a.n_views, static_cast<int>(a.n_tiles), a.ranges,
-                       a.tile_order, a.n_split, a.pair_item, a.pair_marked, a.coef, a.blue, final_T, n_contrib, dL_dimg,
-                       grad2d, a.n_items, a.stats);
+                       a.tile_order, a.n_split, a.n_pairs, a.pair_item, a.pair_marked, a.coef, a.blue, final_T,
+                       n_contrib, dL_dimg, grad2d, a.n_items, a.stats);
   };
-  constexpr bool kSums = TILE <= 16 && LDSB == 0;   // has a form with sums through LDS
-  if (a.stats) launch(k_composite_bwd<TILE, true, LDSB, false>);
-  else if (kSums && a.n_tiles >= kLdsSumTiles) launch(k_composite_bwd<TILE, false, LDSB, kSums>);
-  else launch(k_composite_bwd<TILE, false, LDSB, false>);
+  launch(a.stats ? k_composite_bwd<TILE, true, LDSB> : k_composite_bwd<TILE, false, LDSB>);
   VBM_LAUNCH_CHECK("composite_bwd");
   return VBM_OK;
 }
