@@ -99,7 +99,7 @@ __device__ __forceinline__ float sqrt_rn_f32(float x) {
 constexpr size_t kRadixHead = 4096;
 constexpr int kMaxRadixTotals = 8 * 256;    // any sort
 constexpr int kMaxDepthTotals = 4 * 256;    // 8-bit digits
-constexpr int64_t kBlockSort = 16384;       // elements that one block sorts in LDS
+constexpr int64_t kBlockSort = 8192;        // elements that one block sorts in LDS
 size_t radix_scratch_bytes(int64_t n_max, int digit_bits);
 uint32_t* radix_totals(int64_t n_max, int digit_bits, void* scratch);
 // The elements i in [0, n) with keys[i] != 0, each with value i; ceil(end_bit / width) passes write (k0, v0) and

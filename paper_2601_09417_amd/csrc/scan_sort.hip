@@ -357,10 +357,10 @@ __global__ __launch_bounds__(NT) void k_radix_onesweep(const uint32_t* __restric
 
 // ------------------------------------------------------------------ one-block sort
 // Up to kBlockSort elements are sorted by one block in LDS, all passes in one launch: at these sizes a pass of the
-// one-sweep sort is its launch and the latency of one tile (about 10 us), however few keys there are.
-// 2,048 items and 2,079 pairs (64 tiles): sorts, ranges and tile order 75 us in 13 launches before, 33 us in two
-// now; 5,000 items and 7,749 pairs: 85 and 46 us.  The bound is what LDS holds (two words per element
-// and the per-wave counters, 144 KB); at it the passes take about as long as the larger sort's launches.
+// one-sweep sort is its launch and the latency of one tile (about 8 us), however few keys there are.
+// 2,048 items and 2,079 pairs (64 tiles): sorts, ranges and tile order 75 us in 13 launches before, 24 us in two
+// now.  The line: a render of 4,000 items and 6,787 pairs with room for 8,192 / 12,288 / 16,384 elements in the block takes 74 /
+// 76 / 76 us, 8,000 and 13,625: 91 / 94 / 106, 10,000 and 16,968: 106 / 101 / 117, 16,384 and 27,803: 108 / 107 / 131.
 constexpr int kBlockSortThreads = 1024;
 constexpr int kBlockSortItems = static_cast<int>(kBlockSort / kBlockSortThreads);
 constexpr int kBlockSortWaves = kBlockSortThreads / 64;

@@ -55,12 +55,13 @@ def test_dwt_tile_edges(G, J, wav, with_tf, offset):
         assert err <= tol, ((j, o), err)
 
 
-# Item counts around the emission's 256-item blocks, the sorts' 4096- and 8192-key tiles and the 16384 elements up
+# Item counts around the emission's 256-item blocks, the sorts' 4096- and 8192-key tiles and the 8192 elements up
 # to which one block sorts; opacities with holes in the depth keys, none visible at all (0), footprints on either
 # side of the 32-tile rule; a batch of one tile (no digits to sort), short and long.
 @pytest.mark.parametrize("n,views,W,H,tile,bits,opacity,log_scale", [
     (1, 2, 131, 77, 16, 8, (0.5, 0.9), -3.0), (255, 2, 131, 77, 16, 8, (0.5, 0.9), -3.0),
     (256, 2, 131, 77, 8, 8, (0.5, 0.9), -2.0), (257, 2, 131, 77, 16, 4, (0.5, 0.9), -1.6),
+    (4096, 2, 131, 77, 16, 8, (0.001, 0.007), -3.5),
     (300, 2, 131, 77, 16, 8, (0.001, 0.003), -3.0), (4097, 2, 131, 77, 16, 8, (0.001, 0.007), -3.5),
     (8192, 2, 131, 77, 32, 8, (0.5, 0.9), -4.0), (8193, 2, 131, 77, 16, 8, (0.001, 0.007), -3.5),
     (16500, 2, 131, 77, 8, 5, (0.001, 0.02), -3.8), (300, 1, 16, 16, 16, 8, (0.5, 0.9), -3.0),
