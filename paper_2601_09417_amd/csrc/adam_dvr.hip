@@ -169,8 +169,9 @@ struct DvrViews {
 // Bound by VALU issue: the position along an axis is one multiply-add from the entry point's (in voxels), the
 // transfer function has no division, and the next sample's eight voxels (four pair loads) are requested before
 // this one is composited.  A 1080p view of a 512^3 volume: 0.86 -> 0.43 ms (with a transfer function whose rays end
-// late 1.46 -> 0.77 ms), against a kernel with two f64 divisions and a library square root per sample and 64 pixels of one row per wave.
-// kSmall: the volume's byte offsets fit 32 bits.  kHalf: half-voxel steps, whose opacity correction is a square root.
+// late 1.46 -> 0.77 ms), against a kernel with two f64 divisions and a library square root per sample and 64 pixels of
+// one row per wave. kSmall: the volume's byte offsets fit 32 bits.  kHalf: half-voxel steps, whose opacity correction
+// is a square root.
 template <bool kSmall, bool kHalf>
 __global__ __launch_bounds__(256) void k_dvr(const float* __restrict__ vol, int G, DevTF tf, DvrViews views,
                                              double step_vox, float* __restrict__ images) {
@@ -285,8 +286,8 @@ extern "C" vbm_status vbm_adam_step(int64_t n, int64_t stride, float* raw, float
     set_error("vbm_adam_step: null argument");
     return VBM_ERR_INVALID;
   }
-  if (n < 0 || stride < n || g.stride < n || act.stride < n || (!step_dev && o->step < 1) || !(o->beta1 >= 0.0f && o->beta1 < 1.0f) ||
-      !(o->beta2 >= 0.0f && o->beta2 < 1.0f) || !(o->eps >= 0.0f)) {
+  if (n < 0 || stride < n || g.stride < n || act.stride < n || (!step_dev && o->step < 1) ||
+      !(o->beta1 >= 0.0f && o->beta1 < 1.0f) || !(o->beta2 >= 0.0f && o->beta2 < 1.0f) || !(o->eps >= 0.0f)) {
     set_error("vbm_adam_step: bad sizes or hyper-parameters");
     return VBM_ERR_INVALID;
   }

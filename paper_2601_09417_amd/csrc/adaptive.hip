@@ -190,8 +190,8 @@ __global__ __launch_bounds__(kT) void k_af_norm(const float* __restrict__ coeffs
     if (h[x]) atomicAdd(&g[x], h[x]);
 }
 
-// E per subband and the budgets K_{j,o} = max(min_band, floor(K_tot S / sum S)), S = E^alpha N^beta, in one block.  A wave
-// sums a subband's chunks in a fixed order: 256 partial sums (four per lane), added in four groups of 64.
+// E per subband and the budgets K_{j,o} = max(min_band, floor(K_tot S / sum S)), S = E^alpha N^beta, in one block.  A
+// wave sums a subband's chunks in a fixed order: 256 partial sums (four per lane), added in four groups of 64.
 constexpr int kBudgetThreads = 1024;
 __global__ __launch_bounds__(kBudgetThreads) void k_af_budget(BandTable bt, const double* __restrict__ epart,
                                                              BandState* __restrict__ st, int64_t K_tot, double alpha,

@@ -127,7 +127,7 @@ constexpr int kSplitCounter = 6;        // their numbers for the forward and the
 struct TileLists {
   uint2* ranges;             // [n_tiles]: [start, end) of each tile's list
   int64_t n_tiles;
-  uint32_t* order;           // [n_tiles]: tiles in launch order, the longest lists first (in steps of 8 entries, stable)
+  uint32_t* order;           // [n_tiles]: tiles in launch order, longest lists first (in steps of 8 entries, stable)
   uint32_t* keys;            // [2][n_tiles]: the order's sort keys
   uint32_t* counters;        // of the forward: the numbers of split tiles go to [6] and [7]
   int32_t* status;           // the caller's
@@ -135,7 +135,8 @@ struct TileLists {
 };
 // Sorts the pairs in (k[first], v[first]) by tile into (k[0], v[0]) (first as sort_pairs_first says; the count is
 // read from *n_dev when non-null, and is at most n_max), and writes the tiles' ranges (cleared beforehand),
-// launch order and the status (scratch: radix_scratch_bytes of n_max and of the tiles).  The kTileOrderCounts words at tile_order_counts() are cleared beforehand.
+// launch order and the status (scratch: radix_scratch_bytes of n_max and of the tiles).  The kTileOrderCounts words at
+// tile_order_counts() are cleared beforehand.
 constexpr int kTileOrderCounts = 2 * 256;
 inline uint32_t* tile_order_counts(void* scratch) { return static_cast<uint32_t*>(scratch); }
 int sort_pairs_first(int64_t n_max, int64_t n_tiles, int end_bit, int digit_bits);

@@ -11,8 +11,8 @@ struct CompositeArgs {
   int64_t n_tiles;
   const uint2* ranges;          // each tile's list
   const uint32_t* tile_order;   // longest lists first
-  const uint32_t* n_split;      // device: the first n_split[0] tiles of the order are shared by four waves in the forward,
-                                // the first n_split[1] <= n_split[0] in the backward (16x16 tiles)
+  const uint32_t* n_split;      // device: the first n_split[0] tiles of the order are shared by four waves in the
+                                // forward, the first n_split[1] <= n_split[0] in the backward (16x16 tiles)
   const uint32_t* n_pairs;      // device: pairs of the batch
   const uint32_t* pair_item;    // sorted pair values
   uint32_t* pair_marked;        // the forward's marked copy

@@ -23,8 +23,8 @@ namespace {
 
 // ------------------------------------------------------------------ transfer function in LDS
 // RGBA by linear interpolation between ascending control points, constant beyond the end points
-// (Sec. 3, Transfer Function).  Segment table: entry 0 is the constant before the first control point, entry i the segment
-// between points i - 1 and i, entry n the constant from the last point on.  A lane's segment index varies, so
+// (Sec. 3, Transfer Function).  Segment table: entry 0 is the constant before the first control point, entry i the
+// segment between points i - 1 and i, entry n the constant from the last point on.  A lane's segment index varies, so
 // the table is read from LDS (three 16-byte reads) rather than from the kernel arguments.
 constexpr int kTfEntries = VBM_TF_MAX_POINTS + 1;
 struct TfSegment {
@@ -43,7 +43,8 @@ __device__ __forceinline__ void tf_load(const DevTF& tf, TfSegment* __restrict__
     q.inv_w = q.w > 0.0f ? fminf(__fdiv_rn(1.0f, q.w), 3.402823466e38f) : 0.0f;   // (finite for a subnormal width)
     q.pad = 0.0f;
     for (int c = 0; c < 4; ++c) {
-      // t = 1 in an entry without a position: a constant entry keeps its point (delta 0), a segment of no width takes its end
+      // t = 1 in an entry without a position: a constant entry keeps its point (delta 0), a segment of no width takes
+      // its end
       q.base[c] = tf.rgba[a][c];
       q.delta[c] = tf.rgba[b][c] - tf.rgba[a][c];
     }

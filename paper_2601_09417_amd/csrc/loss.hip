@@ -175,7 +175,8 @@ __device__ __forceinline__ void load_halo(const float* const (&src)[NF], int W, 
     const bool in = lane < EX && r < EY && gx >= 0 && gx < W && gy >= 0 && gy < H;
     const int off = in ? 4 * (gy * W + gx) : plane_bytes;
 #pragma unroll
-    for (int f = 0; f < NF; ++f) v[f][k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs[f], off, 0, 0));
+    for (int f = 0; f < NF; ++f)
+      v[f][k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs[f], off, 0, 0));
   }
 #pragma unroll
   for (int k = 0; k < kRowLoads; ++k) {
@@ -311,8 +312,8 @@ __global__ __launch_bounds__(256) void k_ssim_maps(const float* __restrict__ x, 
       const float iA1 = A2 * iA, iA2 = A1 * iA, iB1 = B2 * iB, iB2 = B1 * iB;
       const float sv = AA * iB;
       const int off = 4 * (gy * W + gx);
-      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, 2.0f * sv * (my * (iA1 - iA2) + mx * (iB2 - iB1))),
-                                            r1, off, 0, 0);
+      const float v1 = 2.0f * sv * (my * (iA1 - iA2) + mx * (iB2 - iB1));
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v1), r1, off, 0, 0);
       __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, -sv * iB2), r2, off, 0, 0);
       __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, 2.0f * sv * iA2), r3, off, 0, 0);
       sval += sv;

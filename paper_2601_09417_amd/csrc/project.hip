@@ -90,10 +90,10 @@ __device__ __forceinline__ bool tile_reached(float mx, float my, float A, float 
 
 // The same in two thirds of the instructions where rounding cannot matter, which is nearly everywhere.  Of the
 // footprint's q the minimum over the rectangle lies on an edge that faces the mean, so two candidates do: the
-// nearest column dx, |dx| least, with its stationary dy clamped, and the nearest row (both inside: q = 0).  They and the
-// four edges' q differ by rounding only, a few units of 2^-24 of the terms' magnitude; `margin` is 64 of them for the
-// largest terms in the item's tile rectangle.  Tiles closer to tau than that take the four edges (one in 2,000 of the
-// tiles of random ellipses, axes up to 10^4 apart).  8M items: 388 us with the four edges only, 342 us.
+// nearest column dx, |dx| least, with its stationary dy clamped, and the nearest row (both inside: q = 0).  They and
+// the four edges' q differ by rounding only, a few units of 2^-24 of the terms' magnitude; `margin` is 64 of them for
+// the largest terms in the item's tile rectangle.  Tiles closer to tau than that take the four edges (one in 2,000 of
+// the tiles of random ellipses, axes up to 10^4 apart).  8M items: 388 us with the four edges only, 342 us.
 __device__ __forceinline__ bool tile_reached_near(float mx, float my, float A, float B, float C, float nBA, float nBC,
                                                   float tau, float margin, int tx, int ty, int tile, int W, int H) {
   // (exact, like tile_reached's: halves of integers below 2^16)
@@ -242,9 +242,9 @@ __device__ __forceinline__ ProjResult project_one(const DevView& v, int tile, fl
 }
 
 // grid: x over Gaussians of the view's scene, y over views.  Writes the per-item records and the depth
-// sort's key: the bits of the (positive) depth of an item that reaches a tile, 0 for the others.  Each thread projects one item; the reached tiles
-// are then counted block-wide so that the footprint tests do not diverge with the rectangle sizes:
-// the tiles of all rectangles of at most 32 tiles are numbered consecutively (a block prefix sum of
+// sort's key: the bits of the (positive) depth of an item that reaches a tile, 0 for the others.  Each thread projects
+// one item; the reached tiles are then counted block-wide so that the footprint tests do not diverge with the
+// rectangle sizes: the tiles of all rectangles of at most 32 tiles are numbered consecutively (a block prefix sum of
 // their areas, an LDS map from test number to item) and shared round-robin by the block's threads,
 // which set the reached bits of the items' row-major masks; larger rectangles are tested by whole
 // waves, 64 tiles per round.
@@ -404,7 +404,8 @@ __device__ __forceinline__ int view_of_item(const DevView* __restrict__ views, i
 constexpr unsigned long long kEmitAgg = 1ull << 62;
 constexpr unsigned long long kEmitInc = 2ull << 62;
 constexpr unsigned long long kEmitCount = kEmitAgg - 1ull;
-constexpr int kEmitRounds = 128;   // look-back rounds that find a block unpublished before its items are counted directly
+// Look-back rounds that find a block unpublished before its items are counted directly.
+constexpr int kEmitRounds = 128;
 
 __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
   for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
@@ -470,7 +471,8 @@ __global__ __launch_bounds__(256) void k_emit(const DevView* __restrict__ views,
   __shared__ uint32_t s_x[256], s_y[256], s_z[256];   // the items' bin entries
   __shared__ uint32_t s_base[256];   // global tile of the rectangle's first tile
   __shared__ uint32_t s_row[256];    // tiles per row of the item's view
-  __shared__ uint32_t s_dst[256];    // small: a pair's place among the block's pairs minus its place in s_pair; large: the first one's place
+  // small: a pair's place among the block's pairs minus its place in s_pair; large: the first one's place
+  __shared__ uint32_t s_dst[256];
   __shared__ uint32_t s_q[256];      // threads with a large rectangle
   __shared__ uint32_t s_n;
   __shared__ unsigned long long s_first;

@@ -27,7 +27,8 @@
 // behind the current Gaussian (see bwd_step).  The geometric gradient is accumulated as three
 // per-lane moments of dL/dpower (sum, first and second moment in dy); the lane's column offset dx
 // turns them into the five sums the 2D parameters need.  Nine per-wave sums are then formed by
-// cross-row lane swaps and a DPP reduction inside 16-lane rows (one value per lane), and nine lanes
+// cross-row lane swaps and a DPP reduction inside 16-lane rows (one value per lane; in large batches through
+// LDS, two entries at a time: see kSumRow), and nine lanes
 // issue one float atomic each into the item's 64-byte accumulator row (one cache segment per pair
 // instead of nine lines) -- only when some pixel contributed.  The atomics add those raw moments;
 // the projection backward turns them into mean/conic/opacity gradients with the item's conic,
@@ -447,7 +448,8 @@ __device__ __forceinline__ void fwd_walk_pixels(LdsList& L, const uint32_t* __re
     }
     if (!wave_any(fy < kLiveBound)) {
       if (kBand)   // the entries that no pixel of the band lived to see
-        for (int q = (base - start) / 64 + 1 + (lane >> 1); start + 64 * q < end; q += 32) planes[8 * q + (lane & 1)] = 0u;
+        for (int q = (base - start) / 64 + 1 + (lane >> 1); start + 64 * q < end; q += 32)
+          planes[8 * q + (lane & 1)] = 0u;
       break;
     }
   }
@@ -479,8 +481,8 @@ __device__ __forceinline__ WaveWork wave_work(const uint32_t* __restrict__ tile_
 }
 
 // Entries per LDS batch of the forward's walk with four pixels per lane: with 64 the walk took 0.99
-// against 0.90 ms (16M pairs, 1080p), and through the scalar cache 1.13 ms.  A test of each band by the wave (an exponent
-// and a ballot per step and band) instead of the staging lane's took 1.72 against 1.63 ms (27M pairs);
+// against 0.90 ms (16M pairs, 1080p), and through the scalar cache 1.13 ms.  A test of each band by the wave (an
+// exponent and a ballot per step and band) instead of the staging lane's took 1.72 against 1.63 ms (27M pairs);
 // marks that tell whether a pixel passed the alpha test, collected in scalar registers, 1.82 ms for 2% of the backward.
 constexpr int kFwdBatch = 32;
 
@@ -628,11 +630,11 @@ struct BwdPix {
 // alpha c + (1 - alpha) acc.  Only the projection S = sum_c dL/dC_c acc_c enters, so that scalar is
 // what the pixel carries: dL/dalpha = T_before (D_c - S) with D_c = sum_c dL/dC_c c_c, and S moves
 // to S + alpha (D_c - S).  dL/dpower = alpha dL/dalpha unless alpha was clamped.
-// Leaves the lane's sums over its pixels: s0 = sum dp, s1 = sum dp dy, s2 = sum dp dy^2 (dp = dL/dpower), and the colour
-// weights alpha T_before dL/dC.  False (for the whole wave) when no group is marked or, without marks, no pixel
+// Leaves the lane's sums over its pixels: s0 = sum dp, s1 = sum dp dy, s2 = sum dp dy^2 (dp = dL/dpower), and the
+// colour weights alpha T_before dL/dC.  False (for the whole wave) when no group is marked or, without marks, no pixel
 // takes part.
-// RARE: a clamped alpha, of which there are few, is handled in uniform branches instead of by a minimum and a select for
-// every pixel: fewer instructions, but a lone wave waits for every branch (see kLdsSumShare).
+// RARE: a clamped alpha, of which there are few, is handled in uniform branches instead of by a minimum and a select
+// for every pixel: fewer instructions, but a lone wave waits for every branch (see kLdsSumShare).
 struct BwdSums {
   float s0, s1, s2, wr, wg, wb;
 };
@@ -690,13 +692,14 @@ __device__ __forceinline__ bool bwd_step(const Rec& r, uint32_t groups, int j, f
 }
 
 // The nine wave sums of two list entries at a time, through LDS (tiles at most 16 wide).  Every lane leaves its six
-// sums of an entry in six rows of 64; lane 4 (6 e + v) + q then takes the four words 16 r + 4 q .. + 3 of row v of entry
-// e, r = 0..3: four pixel columns.  It adds a column's pixels, weighs the columns with 1, dx and dx^2, and the quad
-// adds its four lanes' sums, of which lane q issues the q-th.
+// sums of an entry in six rows of 64; lane 4 (6 e + v) + q then takes the four words 16 r + 4 q .. + 3 of row v of
+// entry e, r = 0..3: four pixel columns.  It adds a column's pixels, weighs the columns with 1, dx and dx^2, and the
+// quad adds its four lanes' sums, of which lane q issues the q-th.
 // Why not in registers: a SIMD issues two vector instructions in four cycles, but only one of the two may be a lane
 // swap, a DPP or a select or read a scalar register (measured: 2.2 G wave instructions/s per CU of those, 1.2 of
-// swaps, against 4.0 of plain adds and fused multiply-adds), and 16 of the 24 that reduce_cols9 takes are of that kind (the swaps twice as slow).
-// Here about 7 of 26 per entry are.  27M pairs at 1080p: 4.03 -> 3.76 ms, with the branches of RARE 3.62 ms.
+// swaps, against 4.0 of plain adds and fused multiply-adds), and 16 of the 24 that reduce_cols9 takes are of that kind
+// (the swaps twice as slow). Here about 7 of 26 per entry are.  27M pairs at 1080p: 4.03 -> 3.76 ms, with the branches
+// of RARE 3.62 ms.
 constexpr int kSumRow = 80;                 // words between rows: a quarter wave's 16-byte reads touch every bank once
 constexpr int kSumWords = 12 * kSumRow;     // per wave
 __device__ __forceinline__ int sum_column(int lane) {   // the gradient column (0..8) that the lane issues, or -1
@@ -764,7 +767,8 @@ __device__ __forceinline__ void bwd_walk_bands(BandLists& L, const uint32_t* __r
   __syncthreads();
   const int band_n = __builtin_amdgcn_readfirstlane(maxn);
   maxn = __builtin_amdgcn_readfirstlane(max(max(L.maxn[0], L.maxn[1]), max(L.maxn[2], L.maxn[3])));
-  // entry e of the batch that ends at position hi is position hi - e; the wave's first 16 lanes fetch a quarter of the batch
+  // entry e of the batch that ends at position hi is position hi - e; the wave's first 16 lanes fetch a quarter of the
+  // batch
   float4 ra, rb;
   float bl = 0.0f;
   uint32_t item = 0;
@@ -826,8 +830,8 @@ constexpr int kBwdThreads = TILE == 16 ? 256 : TileCfg<TILE>::kThreads;
 // that a SIMD can issue set the backward's time: sums through LDS and branches around the rare cases save some.
 // With fewer, the time is that of the longest lists, whose waves wait for each LDS round trip and branch.  us with
 // sums in registers / this form (pairs over the longest list; the launch order's first tile has it, to a few entries):
-// 710 / 871 (1,800), 736 / 851 (2,400), 888 / 815 (3,700), 1248 / 1115 (4,700), 1559 / 1435 (7,400), 4028 / 3617 (11,000),
-// 1291 / 1151 (12,500); with 8x8 tiles 96 / 105 (2,200), 249 / 207 (6,000), 2177 / 2035 (50,000).
+// 710 / 871 (1,800), 736 / 851 (2,400), 888 / 815 (3,700), 1248 / 1115 (4,700), 1559 / 1435 (7,400), 4028 / 3617
+// (11,000), 1291 / 1151 (12,500); with 8x8 tiles 96 / 105 (2,200), 249 / 207 (6,000), 2177 / 2035 (50,000).
 constexpr uint32_t kLdsSumShare = 3000;
 template <int TILE, bool STATS, int LDSB>
 constexpr bool kBwdSums = TILE <= 16 && !STATS && LDSB == 0;   // the kernel has both forms
@@ -835,7 +839,8 @@ constexpr bool kBwdSums = TILE <= 16 && !STATS && LDSB == 0;   // the kernel has
 // LDS of a backward block: a split tile's lists, or per wave the staged lists or the sums of two entries.
 template <int TILE, bool STATS, int LDSB>
 constexpr size_t bwd_wave_bytes() {
-  return kBwdSums<TILE, STATS, LDSB> ? sizeof(float) * kSumWords : LDSB > 0 ? sizeof(LdsBatch<LDSB == 0 ? 1 : LDSB>) : 16;
+  return kBwdSums<TILE, STATS, LDSB> ? sizeof(float) * kSumWords
+         : LDSB > 0 ? sizeof(LdsBatch<LDSB == 0 ? 1 : LDSB>) : 16;
 }
 template <int TILE, bool STATS, int LDSB>
 constexpr size_t bwd_lds_bytes() {
@@ -1039,7 +1044,9 @@ __global__ __launch_bounds__(kBwdThreads<TILE>) void k_composite_bwd(
   const uint32_t* __restrict__ values = pair_values + start;
   uint32_t n_eval = 0, n_used = 0;
   auto load = [&](int k, float& fy, float& T, int& nc, float& dr, float& dg, float& db, float& S)
-                  __attribute__((always_inline)) { load_pixel(ty * TILE + (q0 + k * 64) / TILE, fy, T, nc, dr, dg, db, S); };
+                  __attribute__((always_inline)) {
+    load_pixel(ty * TILE + (q0 + k * 64) / TILE, fy, T, nc, dr, dg, db, S);
+  };
   unsigned char* wave_lds = lds + (TILE == 16 ? block_wave : 0) * bwd_wave_bytes<TILE, STATS, LDSB>();
   const BwdTile tile_data{values, crec, blue, imax, lane, fx,
                           static_cast<float>(tx * TILE + (4 * (lane & 3)) % TILE) + 0.5f, grad2d};
@@ -1120,7 +1127,8 @@ static vbm_status launch_bwd_t(const CompositeArgs& a, const float* final_T, con
                                const float* dL_dimg, float* grad2d, hipStream_t s) {
   // with 16x16 tiles a block per split tile and a wave for each of the others (blocks left over do nothing)
   const int64_t split = a.n_tiles < kMaxSplit ? a.n_tiles : kMaxSplit;
-  const dim3 grid(static_cast<unsigned>(TILE == 16 ? split + ceil_div(a.n_tiles, 4) : a.n_tiles)), block(kBwdThreads<TILE>);
+  const dim3 grid(static_cast<unsigned>(TILE == 16 ? split + ceil_div(a.n_tiles, 4) : a.n_tiles));
+  const dim3 block(kBwdThreads<TILE>);
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, block, 0, s, a.views, a.n_views, static_cast<int>(a.n_tiles), a.ranges,
                        a.tile_order, a.n_split, a.n_pairs, a.pair_item, a.pair_marked, a.coef, a.blue, final_T,

@@ -1,8 +1,8 @@
 // Stable LSD radix sort (gfx950, wave64, 256-thread blocks).
 //
 // One histogram kernel counts the digits of every pass in one read of the
-// keys, then each pass is a single kernel over tiles of 8192 keys (4096 or 2048 for few keys) that ranks equal digits inside each
-// wave with ballots (a lane's rank = set bits of its digit-match mask below it) and across a
+// keys, then each pass is a single kernel over tiles of 8192 keys (4096 or 2048 for few keys) that ranks equal digits
+// inside each wave with ballots (a lane's rank = set bits of its digit-match mask below it) and across a
 // wave's rounds through per-wave LDS counters, learns the earlier tiles' digit counts by
 // decoupled look-back, partitions the tile in LDS, and writes it out in digit order (coalesced
 // runs).
@@ -189,8 +189,8 @@ __device__ __forceinline__ uint32_t split_key(uint32_t pairs, uint32_t share) {
 enum SweepKind { kPlainPass, kSparsePass, kRangesPass, kOrderPass };
 // I: keys per thread.  16 move the most keys a second, but up to kSmallSweep keys such tiles are fewer than the CUs or
 // hardly more, and a pass takes as long as a tile: us a pass with 16 / 8 / 4 (keys): 14.5 / 10.5 / 9 (about 100,000),
-// 16.4 / 13.3 / 13.1 (360,000), 22 / 19.5 / 21.5 (1.1M), 25.3 / 25.3 / 28.6 (2.4M), 58 / 66 / 87 (7.9M).  The tile order's pass has
-// at most some ten thousand keys: 12.4 / 8.1 / 6.4 for 8,160 tiles, 14.7 / 10.5 / 9.1 for 65,280.
+// 16.4 / 13.3 / 13.1 (360,000), 22 / 19.5 / 21.5 (1.1M), 25.3 / 25.3 / 28.6 (2.4M), 58 / 66 / 87 (7.9M).  The tile
+// order's pass has at most some ten thousand keys: 12.4 / 8.1 / 6.4 for 8,160 tiles, 14.7 / 10.5 / 9.1 for 65,280.
 constexpr int kSmallItems = 8, kOrderItems = 4;
 constexpr int64_t kSmallSweep = 2 << 20;
 template <int NT, int I, SweepKind kKind>
@@ -359,8 +359,9 @@ __global__ __launch_bounds__(NT) void k_radix_onesweep(const uint32_t* __restric
 // Up to kBlockSort elements are sorted by one block in LDS, all passes in one launch: at these sizes a pass of the
 // one-sweep sort is its launch and the latency of one tile (about 8 us), however few keys there are.
 // 2,048 items and 2,079 pairs (64 tiles): sorts, ranges and tile order 75 us in 13 launches before, 24 us in two
-// now.  The line: a render of 4,000 items and 6,787 pairs with room for 8,192 / 12,288 / 16,384 elements in the block takes 74 /
-// 76 / 76 us, 8,000 and 13,625: 91 / 94 / 106, 10,000 and 16,968: 106 / 101 / 117, 16,384 and 27,803: 108 / 107 / 131.
+// now.  The line: a render of 4,000 items and 6,787 pairs with room for 8,192 / 12,288 / 16,384 elements in the block
+// takes 74 / 76 / 76 us, 8,000 and 13,625: 91 / 94 / 106, 10,000 and 16,968: 106 / 101 / 117, 16,384 and 27,803: 108 /
+// 107 / 131.
 constexpr int kBlockSortThreads = 1024;
 constexpr int kBlockSortItems = static_cast<int>(kBlockSort / kBlockSortThreads);
 constexpr int kBlockSortWaves = kBlockSortThreads / 64;
@@ -448,7 +449,8 @@ __global__ __launch_bounds__(kBlockSortThreads) void k_sort_block(const uint32_t
   int n = static_cast<int>(active_count(n_max, n_dev));
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   uint32_t keys[kBlockSortItems], vals[kBlockSortItems], digit[kBlockSortItems], slot[kBlockSortItems];
-  int rounds = (n + kBlockSortThreads - 1) / kBlockSortThreads;   // wave w owns elements [64 rounds w, 64 rounds (w + 1))
+  // wave w owns elements [64 rounds w, 64 rounds (w + 1))
+  int rounds = (n + kBlockSortThreads - 1) / kBlockSortThreads;
 #pragma unroll
   for (int r = 0; r < kBlockSortItems; ++r) {
     const int i = (w * rounds + r) * 64 + lane;
@@ -741,8 +743,8 @@ vbm_status sort_pairs_by_tile(uint32_t* const k[2], uint32_t* const v[2], int fi
   hipLaunchKernelGGL((k_radix_onesweep<kSweepThreads, kOrderItems, kOrderPass>),
                      dim3(static_cast<unsigned>(ceil_div(NT, kSweepThreads * kOrderItems))), dim3(kSweepThreads), 0, s,
                      lists.keys, static_cast<const uint32_t*>(nullptr), lists.keys + NT, lists.order, hist, look, NT,
-                     static_cast<const uint32_t*>(nullptr), 0, 8, static_cast<uint32_t*>(nullptr), static_cast<uint2*>(nullptr),
-                     lists);
+                     static_cast<const uint32_t*>(nullptr), 0, 8, static_cast<uint32_t*>(nullptr),
+                     static_cast<uint2*>(nullptr), lists);
   VBM_LAUNCH_CHECK("tile_order");
   return VBM_OK;
 }

@@ -28,8 +28,8 @@ constexpr int kRegion = kT * kPerThread;   // locations per region: its candidat
 constexpr int kBins[3] = {4096, 1024, 1024};
 constexpr int kShift[3] = {20, 10, 0};
 constexpr int kHistWords = 4096 + 1024 + 1024;
-// Blocks of the passes over the candidates.  Their counts meet at the same bins: 256 / 512 / 1024 blocks take 62 / 53 / 58 us in
-// the three digits and the count (512^3, K = 1M), 97 us with a region at a time per wave and 1024.
+// Blocks of the passes over the candidates.  Their counts meet at the same bins: 256 / 512 / 1024 blocks take 62 / 53
+// / 58 us in the three digits and the count (512^3, K = 1M), 97 us with a region at a time per wave and 1024.
 constexpr int kHistBlocks = 512;
 constexpr int kTallies = 64;               // candidate totals, spread over as many words
 constexpr int kGroup = 256;                // regions per partial sum of kept keys
@@ -258,9 +258,9 @@ __global__ __launch_bounds__(kT) void k_candidates_all(const float* __restrict__
 }
 
 // Calls fn with every candidate key of the wave's regions and done(region) after each: a wave per region, four keys a
-// lane at a time.  The regions go to the waves in turn (the coarse levels' are full, most others hold some 30 candidates),
-// and a wave asks for the counts and first 256 keys of four of them together, so that few blocks, whose counts then
-// meet at the same addresses, keep as much in flight as many.
+// lane at a time.  The regions go to the waves in turn (the coarse levels' are full, most others hold some 30
+// candidates), and a wave asks for the counts and first 256 keys of four of them together, so that few blocks, whose
+// counts then meet at the same addresses, keep as much in flight as many.
 template <class F, class D>
 __device__ __forceinline__ void for_candidates(const uint32_t* __restrict__ cand_key, const uint32_t* __restrict__ cnt,
                                                int64_t regions, F&& fn, D&& done) {

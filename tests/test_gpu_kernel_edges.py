@@ -94,8 +94,8 @@ def test_pair_lists_at_block_edges(n, views, W, H, tile, bits, opacity, log_scal
 
 
 # List lengths around what the compositing walks count in: 16 entries (shorter lists are not shared by four waves),
-# batches of 64 and of 32, closed-up batches that are no multiple of four; faint lists that are walked to the end and dense
-# ones whose pixels stop inside a batch; an image that ends inside a band.
+# batches of 64 and of 32, closed-up batches that are no multiple of four; faint lists that are walked to the end and
+# dense ones whose pixels stop inside a batch; an image that ends inside a band.
 @pytest.mark.parametrize("n,H,tile,opacity,log_scale", [
     (15, 16, 16, (0.2, 0.6), -2.0), (16, 16, 16, (0.2, 0.6), -2.0), (17, 13, 16, (0.9, 1.0), -1.5),
     (33, 16, 8, (0.2, 0.6), -2.0), (64, 16, 16, (0.2, 0.6), -2.0), (65, 10, 16, (0.02, 0.1), -2.0),
@@ -153,7 +153,8 @@ def test_counters_agree_between_walks():
 
 # The selection's candidate pass: grids below, at and above its 4096-location regions and the size from which a sample
 # bounds the candidates; K of 1, of everything and between; planes that start on a 4-byte boundary only; a sample that
-# misleads (only the sampled locations are large, so the bound leaves too few); ties at the K-th key; NaN and infinities.
+# misleads (only the sampled locations are large, so the bound leaves too few); ties at the K-th key; NaN and
+# infinities.
 @pytest.mark.parametrize("G,K,kind", [
     (4, 1, "plain"), (16, 4096, "plain"), (18, 1000, "odd"), (64, 5000, "plain"), (66, 1, "plain"), (66, 20000, "odd"),
     (72, 72 ** 3, "plain"), (96, 50000, "mislead"), (96, 300000, "ties"), (96, 2000, "special")])
@@ -182,7 +183,8 @@ def test_selection_candidates(G, K, kind):
     if kind == "special":
         # key order of the bit patterns: NaN above infinity above the finite keys
         with np.errstate(invalid="ignore"):
-            v = np.sqrt((((c[0] * c[0] + c[1] * c[1]) + c[2] * c[2]) + c[3] * c[3]).astype(np.float64)).astype(np.float32)
+            square = ((c[0] * c[0] + c[1] * c[1]) + c[2] * c[2]) + c[3] * c[3]
+            v = np.sqrt(square.astype(np.float64)).astype(np.float32)
         order = np.lexsort((np.arange(M), -np.nan_to_num(v, nan=np.inf).astype(np.float64), ~np.isnan(v)))
         ref = np.sort(order[:K])
     else:
@@ -262,9 +264,9 @@ def test_adaptive_parts(G, J, values, K_tot, params):
 
 
 # Batches of 3,000 longest lists or more take the backward's sums through LDS, two list entries at a time; each view
-# alone is below that and is reduced in registers, which the comparisons with the oracle cover.  The batch's gradient is the
-# sum of the views', to the same bound: lists of one entry and of odd and even length, alphas beyond the clamp (opacity 1),
-# images that end inside a tile.
+# alone is below that and is reduced in registers, which the comparisons with the oracle cover.  The batch's gradient
+# is the sum of the views', to the same bound: lists of one entry and of odd and even length, alphas beyond the clamp
+# (opacity 1), images that end inside a tile.
 @pytest.mark.parametrize("n,views,W,H,tile,opacity,log_scale", [
     (400, 400, 120, 116, 16, (0.5, 1.0), -3.4), (400, 160, 120, 116, 8, (0.5, 1.0), -3.4),
     (600, 400, 128, 120, 16, (0.02, 0.3), -3.2), (200, 240, 100, 90, 8, (0.9, 1.0), -4.0)])
