@@ -430,7 +430,9 @@ __device__ __forceinline__ void fwd_walk_pixels(LdsList& L, const uint32_t* __re
           const float a = stopped ? 0.0f : alpha[k];
           w[k] = a * T;
           T = attenuate(T, a);
-          const bool stop = T < kTMin;
+          // (only an entry that the pixel takes stops it: T + w may lie one unit in the last place below the
+          // threshold, and would stop the pixel again at every later entry and at the padding)
+          const bool stop = a > 0.0f && T < kTMin;
           T = stop ? T + w[k] : T;
           w[k] = stop ? 0.0f : w[k];
           fy = stop ? kDeadRow : fy;

@@ -308,3 +308,59 @@ def test_pair_lists_of_thin_footprints(tile):
     assert out.status[:2].tolist() == [0, total]
     assert np.array_equal(rp.region("pair_tile", torch.int32).cpu().numpy()[:total], ref["tile"])
     assert np.array_equal(rp.region("pair_item", torch.int32).cpu().numpy()[:total] & ITEM_MASK, ref["item"])
+
+
+def _stop_at_the_threshold(alpha):
+    """Entries i, j, k, s and a pixel p whose transmittance is exactly float32(1e-4) after i, j and k, and for which
+    T - s T + s T, each step rounded, falls below it: alpha float32 [entries][pixels], all at least one half, so that
+    every product below is exact in float64 before its one rounding."""
+    f = np.float32
+    c = float(f(1e-4))
+    i, j = np.triu_indices(alpha.shape[0])
+    for p in range(alpha.shape[1]):
+        a = alpha[:, p].astype(np.float64)
+        order = np.argsort(a)
+        T1 = 1.0 - a[i]
+        T2 = (T1 - T1 * a[j]).astype(f).astype(np.float64)
+        at = np.searchsorted(a[order], 1.0 - c / T2)
+        low = np.nonzero(f(c) * a.astype(f) + (c - c * a).astype(f) < f(c))[0]
+        for step in (-1, 0):
+            k = order[np.clip(at + step, 0, a.size - 1)]
+            hit = np.nonzero((T2 - T2 * a[k]).astype(f) == f(c))[0]
+            if hit.size and low.size:
+                return p, [int(i[hit[0]]), int(j[hit[0]]), int(k[hit[0]]), int(low[0])]
+    raise AssertionError("no such entries")
+
+
+# A pixel that an entry has stopped stays as that entry left it, whatever rounding made of its transmittance: the
+# entries behind it, and the padding of a group of four, neither move its count nor get a gradient from it.  (Gaussians
+# at one place, which the lists keep in the order they are given in.)
+@pytest.mark.parametrize("tile,behind", [(8, 2), (8, 9), (8, 70), (16, 2), (16, 13), (16, 70)])
+def test_stopped_pixel_stays_stopped(tile, behind):
+    api = _api()
+    n = 400
+    rng = np.random.default_rng(tile)
+    cam = vi.orbit_cameras(1, tile, tile, azimuth0=0.9)[0]
+    f = np.float32
+    gs = vi.GaussianSet(np.zeros((3, n), f), np.full((3, n), 3.0, f), np.tile(np.array([[1], [0], [0], [0]], f), (1, n)),
+                        rng.uniform(0.93, 0.985, n).astype(f), rng.uniform(0.2, 1.0, (3, n)).astype(f))
+    # every entry's alpha, alone in a view of its own (1 - T is exact from one half on)
+    rp = api.plan_batch([cam] * n, np.arange(n + 1), list(range(n)), tile=tile, pair_capacity=1 << 16)
+    alpha = f(1.0) - api.render_fwd(rp, to_dev(gs)).final_T.cpu().numpy().reshape(n, tile * tile)
+    assert alpha.min() >= 0.5
+    p, entries = _stop_at_the_threshold(alpha)
+    say(f"stopped pixel tile={tile}: pixel {p}, entries {entries}, {behind} behind")
+    idx = np.array(entries + list(range(behind)))
+    P = to_dev(gs.subset(idx))
+    rp = api.plan_batch([cam], [0, idx.size], tile=tile, pair_capacity=1 << 16)
+    out = api.render_fwd(rp, P)
+    assert out.status.tolist()[:2] == [0, idx.size]
+    assert int(out.n_contrib[p]) == 3
+    assert abs(float(out.final_T[p]) - float(f(1e-4))) <= 2 ** -37   # one unit in the last place
+    dL = torch.zeros_like(out.image)
+    dL[p::tile * tile] = 1.0
+    G = api.render_bwd(rp, P, dL, out).cpu().numpy()
+    assert not G[:, 3:].any()
+    a = alpha[idx[:3], p].astype(np.float64)
+    w = a * np.concatenate([[1.0], np.cumprod(1.0 - a)[:2]])
+    assert np.abs(G[11] - np.concatenate([w, np.zeros(idx.size - 3)])).max() <= GRAD_TOL * w.max()
