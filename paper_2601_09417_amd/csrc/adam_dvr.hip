@@ -133,7 +133,8 @@ __device__ __forceinline__ void dvr_transfer(const DevTF& tf, const DvrSegment* 
   e = f >= static_cast<double>(tf.x[n - 1]) ? n : e;
   e = f > static_cast<double>(tf.x[0]) ? e : 0;
   const DvrSegment& q = s[e];
-  const double t = (f - q.x0) * q.inv_w;
+  // (selected: f is infinite or not a number in the constant entries)
+  const double t = q.inv_w != 0.0 ? (f - q.x0) * q.inv_w : 0.0;
 #pragma unroll
   for (int k = 0; k < 4; ++k) c[k] = fma(t, q.delta[k], q.base[k]);
 }

@@ -364,3 +364,40 @@ def test_stopped_pixel_stays_stopped(tile, behind):
     a = alpha[idx[:3], p].astype(np.float64)
     w = a * np.concatenate([[1.0], np.cumprod(1.0 - a)[:2]])
     assert np.abs(G[11] - np.concatenate([w, np.zeros(idx.size - 3)])).max() <= GRAD_TOL * w.max()
+
+
+# Voxels that are not numbers or infinite: a sample that is not a number takes the first control point's colour, an
+# infinite one that of its end, as any value beyond the end points does.
+@pytest.mark.parametrize("step", [0.5, 0.75])
+def test_dvr_samples_that_are_not_finite(step, monkeypatch):
+    api = _api()
+    say(f"dvr of voxels that are not finite, step {step}")
+    rng = np.random.default_rng(3)
+    G = 21
+    vol = rng.uniform(size=(G, G, G)).astype(np.float32)
+    special = rng.choice(G ** 3, 90, replace=False)
+    vol.reshape(-1)[special] = np.repeat(np.array([np.nan, np.inf, -np.inf], np.float32), 30)
+    xs = np.array([0.1, 0.4, 0.4, 0.7, 0.9], np.float32)
+    rgba = rng.uniform(size=(5, 4)).astype(np.float32)
+    rgba[:, 3] *= np.float32(0.2)
+
+    def trilinear(v, p):
+        u = np.clip((p + 1.0) / (2.0 / G) - 0.5, 0.0, G - 1.0)
+        i = np.minimum(np.floor(u).astype(np.int64), G - 2)
+        f = u - i
+        x, y, z = i[..., 0], i[..., 1], i[..., 2]
+        lerp = lambda t, a, b: a + t * (b - a)  # noqa: E731
+        with np.errstate(invalid="ignore"):
+            row = [[lerp(f[..., 0], v[z + dz, y + dy, x], v[z + dz, y + dy, x + 1]) for dy in (0, 1)] for dz in (0, 1)]
+            s = lerp(f[..., 2], lerp(f[..., 1], *row[0]), lerp(f[..., 1], *row[1]))
+        return np.where(np.isnan(s), -np.inf, s)
+
+    monkeypatch.setattr(odvr, "trilinear", trilinear)
+    cams = [dataclasses.replace(c, fx=float(np.float32(c.fx)), fy=float(np.float32(c.fy)))
+            for c in vi.orbit_cameras(2, 61, 45, azimuth0=0.1)]
+    img = api.dvr_render(torch.from_numpy(vol).to(dev()), (xs, rgba), cams, step_vox=step)
+    for got, cam in zip(api.split_views(img, cams), cams):
+        ref, _, near = odvr.render(vol, xs, rgba, cam, step_vox=step, flag_rel=1e-6)
+        assert np.isfinite(ref).all() and near.sum() <= 2
+        err = np.abs(got.cpu().numpy() - ref)[:, ~near].max()
+        assert err <= 1e-5 * float(np.abs(ref).max())
