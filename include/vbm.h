@@ -70,7 +70,7 @@ typedef struct {
  *   coeffs  float32 [4][G^3] output, per channel in the packed subband layout
  *           [LLL_J][level J: o=1..7][level J-1: o=1..7]...[level 1: o=1..7],
  *           block (j, o) = [n^3] in [kz][ky][kx] order, n = G/2^j; orientation o has bit d set
- *           when the high-pass was taken along axis d (bit 0 = x, 1 = y, 2 = z)
+ *           when the high-pass was taken along axis d (bit 0 = x, 1 = y, 2 = z); may share memory with vol
  *   ws      workspace of vbm_dwt3d_workspace_size(G, J) bytes
  * Errors: VBM_ERR_INVALID on null pointers or sizes, VBM_ERR_UNSUPPORTED on an unknown wavelet
  * or more than VBM_TF_MAX_POINTS control points, VBM_ERR_WORKSPACE if ws_bytes is too small.

@@ -412,6 +412,12 @@ __global__ __launch_bounds__(256) void k_haar(const float* __restrict__ in, int6
   }
 }
 
+__global__ __launch_bounds__(256) void k_copy(const float* __restrict__ in, float* __restrict__ out, int64_t n) {
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < n;
+       i += static_cast<int64_t>(gridDim.x) * 256)
+    out[i] = in[i];
+}
+
 // z chunk of a bior4.4 block: a chunk re-reads seven planes, so it is as long as still leaves about
 // four blocks per CU; at least two outputs.
 int z_chunk(int h, int64_t tiles) {
@@ -476,6 +482,17 @@ extern "C" vbm_status vbm_dwt3d(const float* vol, int32_t G, int32_t J, int32_t 
   float* q = reinterpret_cast<float*>(static_cast<char*>(ws) + align_up(4 * G3 * sizeof(float), 256));
   const float* cur = vol;
   int64_t cur_cs = G3;
+  // The first level writes coefficients while other blocks still read the field: one that shares memory with them is
+  // read from a copy in the buffer that this level leaves alone.
+  const int64_t values = tf ? G3 : 4 * G3;
+  const uintptr_t v0 = reinterpret_cast<uintptr_t>(vol), c0 = reinterpret_cast<uintptr_t>(coeffs);
+  if (v0 < c0 + 4 * G3 * sizeof(float) && c0 < v0 + values * sizeof(float)) {
+    const int64_t blocks = ceil_div(values, 256);
+    hipLaunchKernelGGL(k_copy, dim3(static_cast<unsigned>(blocks < 8192 ? blocks : 8192)), dim3(256), 0, s, vol, q,
+                       values);
+    VBM_LAUNCH_CHECK("dwt_copy");
+    cur = q;
+  }
   for (int j = 1; j <= J; ++j) {
     const int n = G >> (j - 1);
     const int h = n >> 1;

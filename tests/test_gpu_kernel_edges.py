@@ -401,3 +401,32 @@ def test_dvr_samples_that_are_not_finite(step, monkeypatch):
         assert np.isfinite(ref).all() and near.sum() <= 2
         err = np.abs(got.cpu().numpy() - ref)[:, ~near].max()
         assert err <= 1e-5 * float(np.abs(ref).max())
+
+
+def _dwt_call(vol_ptr, G, J, wav, tf, coeffs):
+    import ctypes as C
+
+    from paper_2601_09417_amd import _lib as L
+    lib = L.load()
+    ws = torch.empty(lib.vbm_dwt3d_workspace_size(G, J), dtype=torch.uint8, device=dev())
+    t = _api().make_tf(*tf) if tf is not None else None
+    L.check(lib.vbm_dwt3d(vol_ptr, G, J, L.WAVELETS[wav], C.byref(t) if t else None, coeffs.data_ptr(), ws.data_ptr(),
+                          ws.numel(), torch.cuda.current_stream().cuda_stream), "vbm_dwt3d")
+
+
+# The coefficients may take the field's own memory: the whole of it (RGBA), or any part.
+@pytest.mark.parametrize("G,J,wav,with_tf,offset", [
+    (130, 1, "bior4.4", False, 0), (100, 2, "haar", False, 0), (4, 1, "haar", False, 0), (72, 3, "bior4.4", False, 0),
+    (130, 1, "bior4.4", True, 130 ** 3), (100, 1, "haar", True, 1001), (64, 5, "bior4.4", True, 0),
+    (64, 2, "bior4.4", True, 4 * 64 ** 3 - 7)])
+def test_dwt_over_its_own_input(G, J, wav, with_tf, offset):
+    api = _api()
+    say(f"dwt over its input G={G} J={J} {wav} tf={with_tf} offset={offset}")
+    g = torch.Generator(device="cuda").manual_seed(G)
+    vol = torch.rand((G, G, G) if with_tf else (4, G ** 3), generator=g, device=dev())
+    tf = (np.array([0.1, 0.3, 0.8], np.float32), np.linspace(0.0, 1.0, 12, dtype=np.float32).reshape(3, 4))
+    ref = api.dwt3d(vol, J, wav, tf if with_tf else None)
+    shared = torch.full((4 * G ** 3 + vol.numel(),), float("nan"), device=dev())
+    shared[offset:offset + vol.numel()] = vol.reshape(-1)
+    _dwt_call(shared[offset:].data_ptr(), G, J, wav, tf if with_tf else None, shared)
+    assert torch.equal(shared[:4 * G ** 3].view(4, -1), ref)
