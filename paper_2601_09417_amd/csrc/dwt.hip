@@ -27,26 +27,31 @@ namespace {
 // segment between points i - 1 and i, entry n the constant from the last point on.  A lane's segment index varies, so
 // the table is read from LDS (three 16-byte reads) rather than from the kernel arguments.
 constexpr int kTfEntries = VBM_TF_MAX_POINTS + 1;
+
+// What the first level reads: RGBA, or a scalar field through the transfer function.  A position in a segment is the
+// product with the width's reciprocal, or the quotient where some width has none to work with (tf_form).
+enum Input { kRGBA, kTF, kTFDivide };
 struct TfSegment {
-  float x0, w, inv_w, pad;   // inv_w = 1 / w rounded, 0 where the position is not used (t = 1)
+  float x0, w, inv_w, pad;   // inv_w = 1 / w rounded (kTFDivide: any), 0 where the position is not used (t = 1)
   float base[4];
   float delta[4];
 };
 
 // Fills the table (every thread of the block calls it; the caller synchronises).
+template <Input kInput>
 __device__ __forceinline__ void tf_load(const DevTF& tf, TfSegment* __restrict__ s, int threads) {
   for (int e = threadIdx.x; e <= tf.n; e += threads) {
     const int a = e == 0 ? 0 : e - 1, b = e == 0 || e == tf.n ? a : e;
     TfSegment q;
     q.x0 = tf.x[a];
     q.w = tf.x[b] - tf.x[a];
-    q.inv_w = q.w > 0.0f ? fminf(__fdiv_rn(1.0f, q.w), 3.402823466e38f) : 0.0f;   // (finite for a subnormal width)
+    q.inv_w = !(q.w > 0.0f) ? 0.0f : kInput == kTFDivide ? 1.0f : __fdiv_rn(1.0f, q.w);
     q.pad = 0.0f;
     for (int c = 0; c < 4; ++c) {
-      // t = 1 in an entry without a position: a constant entry keeps its point (delta 0), a segment of no width takes
-      // its end
+      // t = 1 in an entry without a position: a constant entry keeps its point (delta 0, an infinite one too), a
+      // segment of no width takes its end
       q.base[c] = tf.rgba[a][c];
-      q.delta[c] = tf.rgba[b][c] - tf.rgba[a][c];
+      q.delta[c] = a == b ? 0.0f : tf.rgba[b][c] - tf.rgba[a][c];
     }
     s[e] = q;
   }
@@ -74,12 +79,18 @@ __device__ __forceinline__ void tf_find(const DevTF& tf, const float (&f)[N], in
 
 // The RGBA of a value in table entry e.  The quotient (f - x0) / w is the product with the
 // rounded reciprocal, corrected once by its exact remainder.
+template <Input kInput>
 __device__ __forceinline__ float4 tf_value(const TfSegment* __restrict__ s, int e, float f) {
   const float4* q = reinterpret_cast<const float4*>(s + e);
   const float4 h = q[0], b = q[1], d = q[2];
   const float num = f - h.x;
-  float t = num * h.z;
-  t = fmaf(fmaf(-t, h.y, num), h.z, t);
+  float t;
+  if (kInput == kTFDivide) {
+    t = num / h.y;
+  } else {
+    t = num * h.z;
+    t = fmaf(fmaf(-t, h.y, num), h.z, t);
+  }
   t = h.z != 0.0f ? t : 1.0f;
   return make_float4(fmaf(t, d.x, b.x), fmaf(t, d.y, b.y), fmaf(t, d.z, b.z), fmaf(t, d.w, b.w));
 }
@@ -139,9 +150,10 @@ constexpr int kXcds = 8;
 // channels through memory three times: 8.83 ms for 512^3, five levels; this kernel takes 1.09 ms
 // (three quarters of it level 1; reading the field and writing the coefficients once is 2.7 GB, 0.52 ms at
 // the rate of a large copy).
-template <bool kWithTF>
+template <Input kInput>
 __global__ __launch_bounds__(kNT) void k_dwt97(const float* __restrict__ in, int64_t in_cs, int n, int zc, int tiles_x,
                                                int tiles_y, int n_blocks, LevelOut out, Taps97 taps, DevTF tf) {
+  constexpr bool kWithTF = kInput != kRGBA;
   __shared__ __align__(16) float s_in[4][kIY][kIX];
   __shared__ __align__(16) float s_x[4][kIY][2 * kKX];
   __shared__ __align__(16) TfSegment s_tf[kWithTF ? kTfEntries : 1];
@@ -155,7 +167,7 @@ __global__ __launch_bounds__(kNT) void k_dwt97(const float* __restrict__ in, int
   const int kx0 = (blk % tiles_x) * kKX, ky0 = (blk / tiles_x % tiles_y) * kKY, kz0 = blk / (tiles_x * tiles_y) * zc;
   const int planes = 2 * min(zc, h - kz0) + 7;
   const int64_t nn = static_cast<int64_t>(n) * n;
-  if (kWithTF) tf_load(tf, s_tf, kNT);
+  if (kWithTF) tf_load<kInput>(tf, s_tf, kNT);
 
   // The taps in vector registers, the equal ones (both filters are symmetric) once: a SIMD issues a multiply-add with a
   // scalar operand at half the rate (1.13 against 1.09 ms).
@@ -223,7 +235,7 @@ __global__ __launch_bounds__(kNT) void k_dwt97(const float* __restrict__ in, int
 #pragma unroll
       for (int e = 0; e < kLoads; ++e) {
         __builtin_amdgcn_sched_barrier(0);   // one table entry in registers at a time
-        const float4 c = tf_value(s_tf, seg[e], v[0][e]);
+        const float4 c = tf_value<kInput>(s_tf, seg[e], v[0][e]);
         if (dst[e] >= 0) {
           s_flat[dst[e]] = c.x;
           s_flat[kIY * kIX + dst[e]] = c.y;
@@ -349,12 +361,13 @@ typedef float float2u __attribute__((ext_vector_type(2), aligned(4)));
 // A thread owns the 2x2x2 cell (kx, ky, kz), all four channels, so each value is read and written once and
 // neighbouring lanes read neighbouring pairs: bound by memory.  RGBA 200^3, three levels: 0.226 ms
 // with a kernel per axis, 0.060 ms now (0.050 ms for 256 MB at the rate of a large copy).
-template <bool kWithTF>
+template <Input kInput>
 __global__ __launch_bounds__(256) void k_haar(const float* __restrict__ in, int64_t in_cs, int n, LevelOut out,
                                               TapsHaar f, DevTF tf) {
+  constexpr bool kWithTF = kInput != kRGBA;
   __shared__ __align__(16) TfSegment s_tf[kWithTF ? kTfEntries : 1];
   if (kWithTF) {
-    tf_load(tf, s_tf, 256);
+    tf_load<kInput>(tf, s_tf, 256);
     __syncthreads();
   }
   const int h = n >> 1;
@@ -376,7 +389,7 @@ __global__ __launch_bounds__(256) void k_haar(const float* __restrict__ in, int6
       tf_find<8>(tf, v, seg);
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        const float4 q = tf_value(s_tf, seg[k], v[k]);
+        const float4 q = tf_value<kInput>(s_tf, seg[k], v[k]);
         rgba[k][0] = q.x;
         rgba[k][1] = q.y;
         rgba[k][2] = q.z;
@@ -410,6 +423,16 @@ __global__ __launch_bounds__(256) void k_haar(const float* __restrict__ in, int6
       }
     }
   }
+}
+
+// The quotient where a segment's width is infinite or its reciprocal would not be a normal number with room for the
+// remainder, else the product.
+Input tf_form(const DevTF& tf) {
+  for (int i = 1; i < tf.n; ++i) {
+    const float w = tf.x[i] - tf.x[i - 1];
+    if (w > 0.0f && !(w >= 0x1p-100f && w <= 0x1p100f)) return kTFDivide;
+  }
+  return kTF;
 }
 
 __global__ __launch_bounds__(256) void k_copy(const float* __restrict__ in, float* __restrict__ out, int64_t n) {
@@ -505,7 +528,7 @@ extern "C" vbm_status vbm_dwt3d(const float* vol, int32_t G, int32_t J, int32_t 
     // packed offset of block (j, 1): n_J^3 + sum_{j' > j} 7 n_{j'}^3
     out.level_base = static_cast<int64_t>(G >> J) * (G >> J) * (G >> J);
     for (int jj = J; jj > j; --jj) out.level_base += 7LL * (G >> jj) * (G >> jj) * (G >> jj);
-    const bool with_tf = j == 1 && tf;
+    const Input input = j == 1 && tf ? tf_form(dtf) : kRGBA;
     if (wavelet == VBM_WAVELET_HAAR) {
       TapsHaar f;
       for (int i = 0; i < 2; ++i) {
@@ -513,10 +536,8 @@ extern "C" vbm_status vbm_dwt3d(const float* vol, int32_t G, int32_t J, int32_t 
         f.hi[i] = static_cast<float>(fb.hi_a.taps[i]);
       }
       const dim3 grid(static_cast<unsigned>(ceil_div(out.h3, 256) < 65536 ? ceil_div(out.h3, 256) : 65536));
-      if (with_tf)
-        hipLaunchKernelGGL(k_haar<true>, grid, dim3(256), 0, s, cur, cur_cs, n, out, f, dtf);
-      else
-        hipLaunchKernelGGL(k_haar<false>, grid, dim3(256), 0, s, cur, cur_cs, n, out, f, dtf);
+      const auto kernel = input == kRGBA ? k_haar<kRGBA> : input == kTF ? k_haar<kTF> : k_haar<kTFDivide>;
+      hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, cur, cur_cs, n, out, f, dtf);
     } else {
       Taps97 f;
       for (int i = 0; i < 9; ++i) f.lo[i] = static_cast<float>(fb.lo_a.taps[i]);
@@ -525,10 +546,8 @@ extern "C" vbm_status vbm_dwt3d(const float* vol, int32_t G, int32_t J, int32_t 
       const int zc = z_chunk(h, static_cast<int64_t>(tx) * ty);
       const int nb = tx * ty * static_cast<int>(ceil_div(h, zc));
       const dim3 grid(static_cast<unsigned>(kXcds * ceil_div(nb, kXcds)));
-      if (with_tf)
-        hipLaunchKernelGGL(k_dwt97<true>, grid, dim3(kNT), 0, s, cur, cur_cs, n, zc, tx, ty, nb, out, f, dtf);
-      else
-        hipLaunchKernelGGL(k_dwt97<false>, grid, dim3(kNT), 0, s, cur, cur_cs, n, zc, tx, ty, nb, out, f, dtf);
+      const auto kernel = input == kRGBA ? k_dwt97<kRGBA> : input == kTF ? k_dwt97<kTF> : k_dwt97<kTFDivide>;
+      hipLaunchKernelGGL(kernel, grid, dim3(kNT), 0, s, cur, cur_cs, n, zc, tx, ty, nb, out, f, dtf);
     }
     VBM_LAUNCH_CHECK("dwt3d");
     cur = p;

@@ -430,3 +430,42 @@ def test_dwt_over_its_own_input(G, J, wav, with_tf, offset):
     shared[offset:offset + vol.numel()] = vol.reshape(-1)
     _dwt_call(shared[offset:].data_ptr(), G, J, wav, tf if with_tf else None, shared)
     assert torch.equal(shared[:4 * G ** 3].view(4, -1), ref)
+
+
+# Segments whose width has no float32 reciprocal (infinite, or below the normal range), and colours that are infinite
+# beyond an end point.
+@pytest.mark.parametrize("kind,wav", [("infinite", "haar"), ("infinite", "bior4.4"), ("subnormal", "haar"),
+                                      ("subnormal", "bior4.4"), ("wide", "haar"), ("wide", "bior4.4"),
+                                      ("colour", "haar")])
+def test_dwt_transfer_function_segments(kind, wav):
+    api = _api()
+    G = 8
+    say(f"dwt transfer function {kind} {wav}")
+    rng = np.random.default_rng(9)
+    rgba = rng.uniform(size=(3, 4)).astype(np.float32)
+    vol = rng.uniform(size=(G, G, G)).astype(np.float32)
+    xs = np.array([0.1, 0.5, 0.8], np.float32)
+    if kind == "infinite":
+        xs[2] = np.inf
+    elif kind == "wide":
+        xs[:] = [-3e38, 1e37, 3.3e38]
+        vol = (vol.astype(np.float64) * 6e38 - 3e38).astype(np.float32)
+    elif kind == "subnormal":
+        xs[:] = [0.0, 2.0 ** -138, 1.0]
+        vol.reshape(-1)[::2] = (rng.integers(0, 2 ** 11, vol.size // 2) * 2.0 ** -149).astype(np.float32)
+    elif kind == "colour":
+        rgba[2, 3] = np.inf
+        vol[:] = 0.9
+    # t = (f - x0) / (x1 - x0) in the segment, the end point's colour outside
+    e = np.clip(np.searchsorted(xs, vol, side="right") - 1, 0, 1)
+    with np.errstate(invalid="ignore", over="ignore"):
+        x0, x1 = xs[e].astype(np.float64), xs[e + 1].astype(np.float64)
+        t = np.clip((vol - x0) / (x1 - x0), 0.0, 1.0)[None]
+        c0, c1 = np.moveaxis(rgba[e], -1, 0).astype(np.float64), np.moveaxis(rgba[e + 1], -1, 0).astype(np.float64)
+        c = np.where(t >= 1.0, c1, c0 + t * (c1 - c0))
+    got = api.dwt3d(torch.from_numpy(vol).to(dev()), 1, wav, (xs, rgba)).cpu().numpy()
+    if kind == "colour":
+        assert np.isposinf(got[3, :(G // 2) ** 3]).all() and np.isfinite(got[:3]).all()
+        return
+    ref = odwt.dwt3d_rgba(c, 1, wav)
+    assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max()
