@@ -424,20 +424,20 @@ __device__ __forceinline__ void fwd_walk_pixels(LdsList& L, const uint32_t* __re
       if (wave_any(T < kTMin)) {
         __asm__ volatile("" ::: "memory");   // keeps this a branch
         T = T0;
-        bool stopped = false;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          const float a = stopped ? 0.0f : alpha[k];
-          w[k] = a * T;
-          T = attenuate(T, a);
-          // (only an entry that the pixel takes stops it: T + w may lie one unit in the last place below the
-          // threshold, and would stop the pixel again at every later entry and at the padding)
-          const bool stop = a > 0.0f && T < kTMin;
-          T = stop ? T + w[k] : T;
-          w[k] = stop ? 0.0f : w[k];
-          fy = stop ? kDeadRow : fy;
-          nvis = stop ? __float_as_int(L.c[i + k].y) : nvis;
-          stopped |= stop;
+          w[k] = 0.0f;
+          if (fy < kLiveBound) {   // a stopped pixel's T may lie one unit in the last place below the threshold
+            const float wk = alpha[k] * T;
+            T = attenuate(T, alpha[k]);
+            if (T < kTMin) {
+              T = T + wk;
+              fy = kDeadRow;
+              nvis = __float_as_int(L.c[i + k].y);
+            } else {
+              w[k] = wk;
+            }
+          }
         }
       }
 #pragma unroll
