@@ -264,7 +264,7 @@ typedef struct {
 #define VBM_REGION_COUNTERS 0    /* uint32 [16]: [0] visible items, [1] pairs, [2] overflow, [4..5]
                                   * uint64 ballot words taken by large footprints, [6] and [7] the
                                   * tiles (the first of the launch order) whose lists four waves share
-                                  * in the forward and in the backward */
+                                  * in the forward and in the backward, [8] the longest list's entries */
 #define VBM_REGION_ITEM_DEPTH 1  /* float32 [n_items] camera depth (0 when culled) */
 #define VBM_REGION_ITEM_RECT 2   /* uint32 [n_items][4], the binning entry of each item:
                                   * [0] x0 | x1 << 16 and [1] y0 | y1 << 16, the candidate

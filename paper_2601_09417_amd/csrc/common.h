@@ -122,6 +122,7 @@ constexpr int kMaxSplit = 20480;        // at most
 constexpr int kSplitAllTiles = 20480;
 constexpr uint32_t kSplitForward = 8192, kSplitBackward = 2048;
 constexpr int kSplitCounter = 6;        // their numbers for the forward and the backward, among the forward's counters
+constexpr int kLongestCounter = 8;      // entries of the longest list, among the same
 
 // The tiles' lists after the pair sort.
 struct TileLists {
@@ -129,7 +130,7 @@ struct TileLists {
   int64_t n_tiles;
   uint32_t* order;           // [n_tiles]: tiles in launch order, longest lists first (in steps of 8 entries, stable)
   uint32_t* keys;            // [2][n_tiles]: the order's sort keys
-  uint32_t* counters;        // of the forward: the numbers of split tiles go to [6] and [7]
+  uint32_t* counters;        // of the forward: the numbers of split tiles go to [6] and [7], the longest list's to [8]
   int32_t* status;           // the caller's
   uint32_t split_fwd, split_bwd;   // shares of split_key
 };

@@ -14,6 +14,7 @@ struct CompositeArgs {
   const uint32_t* n_split;      // device: the first n_split[0] tiles of the order are shared by four waves in the
                                 // forward, the first n_split[1] <= n_split[0] in the backward (16x16 tiles)
   const uint32_t* n_pairs;      // device: pairs of the batch
+  const uint32_t* longest;      // device: entries of its longest list
   const uint32_t* pair_item;    // sorted pair values
   uint32_t* pair_marked;        // the forward's marked copy
   uint32_t* planes;             // the marks of split tiles, a bit per entry and band (see mark_plane)

@@ -831,7 +831,7 @@ constexpr int kBwdThreads = TILE == 16 ? 256 : TileCfg<TILE>::kThreads;
 // Batches whose pairs are kLdsSumShare longest lists or more keep every SIMD supplied with waves, and the instructions
 // that a SIMD can issue set the backward's time: sums through LDS and branches around the rare cases save some.
 // With fewer, the time is that of the longest lists, whose waves wait for each LDS round trip and branch.  us with
-// sums in registers / this form (pairs over the longest list; the launch order's first tile has it, to a few entries):
+// sums in registers / this form (pairs over the longest list):
 // 710 / 871 (1,800), 736 / 851 (2,400), 888 / 815 (3,700), 1248 / 1115 (4,700), 1559 / 1435 (7,400), 4028 / 3617
 // (11,000), 1291 / 1151 (12,500); with 8x8 tiles 96 / 105 (2,200), 249 / 207 (6,000), 2177 / 2035 (50,000).
 constexpr uint32_t kLdsSumShare = 3000;
@@ -982,8 +982,8 @@ template <int TILE, bool STATS, int LDSB>
 __global__ __launch_bounds__(kBwdThreads<TILE>) void k_composite_bwd(
     const DevView* __restrict__ views, int n_views, int n_tiles, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ tile_order, const uint32_t* __restrict__ n_split,
-    const uint32_t* __restrict__ n_pairs, const uint32_t* __restrict__ pair_item,
-    const uint32_t* __restrict__ pair_marked, const float* __restrict__ coef,
+    const uint32_t* __restrict__ n_pairs, const uint32_t* __restrict__ longest,
+    const uint32_t* __restrict__ pair_item, const uint32_t* __restrict__ pair_marked, const float* __restrict__ coef,
     const float* __restrict__ blue, const float* __restrict__ final_T, const int32_t* __restrict__ n_contrib,
     const float* __restrict__ dL_dimg, float* __restrict__ grad2d, int64_t n_items,
     unsigned long long* __restrict__ stats) {
@@ -1053,8 +1053,7 @@ __global__ __launch_bounds__(kBwdThreads<TILE>) void k_composite_bwd(
   const BwdTile tile_data{values, crec, blue, imax, lane, fx,
                           static_cast<float>(tx * TILE + (4 * (lane & 3)) % TILE) + 0.5f, grad2d};
   if constexpr (kBwdSums<TILE, STATS, LDSB>) {
-    const uint2 longest = ranges[tile_order[0]];
-    if (*n_pairs / kLdsSumShare >= longest.y - longest.x) {
+    if (*n_pairs / kLdsSumShare >= *longest) {
       bwd_walk_tile<TILE, LDSB, true, STATS>(tile_data, wave_lds, load, n_eval, n_used);
       return;
     }
@@ -1133,8 +1132,8 @@ static vbm_status launch_bwd_t(const CompositeArgs& a, const float* final_T, con
   const dim3 block(kBwdThreads<TILE>);
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, block, 0, s, a.views, a.n_views, static_cast<int>(a.n_tiles), a.ranges,
-                       a.tile_order, a.n_split, a.n_pairs, a.pair_item, a.pair_marked, a.coef, a.blue, final_T,
-                       n_contrib, dL_dimg, grad2d, a.n_items, a.stats);
+                       a.tile_order, a.n_split, a.n_pairs, a.longest, a.pair_item, a.pair_marked, a.coef, a.blue,
+                       final_T, n_contrib, dL_dimg, grad2d, a.n_items, a.stats);
   };
   launch(a.stats ? k_composite_bwd<TILE, true, LDSB> : k_composite_bwd<TILE, false, LDSB>);
   VBM_LAUNCH_CHECK("composite_bwd");

@@ -179,6 +179,7 @@ CompositeArgs composite_args(const vbm_plan* p, const void* view_table, void* ws
   a.tile_order = tile_order(p, ws);
   a.n_split = region<uint32_t>(p, ws, R_COUNTERS) + kSplitCounter;
   a.n_pairs = region<uint32_t>(p, ws, R_COUNTERS) + 1;
+  a.longest = region<uint32_t>(p, ws, R_COUNTERS) + kLongestCounter;
   a.pair_item = region<uint32_t>(p, ws, R_PITEM);
   a.pair_marked = region<uint32_t>(p, ws, R_PITEM_ALT);
   a.planes = region<uint32_t>(p, ws, R_PTILE_ALT);

@@ -163,11 +163,12 @@ __global__ __launch_bounds__(kUpThreads) void k_radix_upsweep(const uint32_t* __
 }
 
 // Coarse length key of a tile's list: the longest first, one step per 8 entries, lists of 2040 or more share
-// the first.
+// the first (the longest list's own length goes to the forward's counters).
 __device__ __forceinline__ uint32_t length_key(uint2 r) { return 255u - min(255u, (r.y - r.x) >> 3); }
 
 // The length key below which a tile's list is composited by four waves: lists of kSplitLeast entries or more,
-// and of pairs / share or more (TileLists says which shares).
+// and of pairs / share or more (TileLists says which shares).  No list where that is more than the 2040 entries up to
+// which the keys tell lengths apart: from 4.2M pairs in the backward, from 16.7M in the forward of many tiles.
 constexpr uint32_t kSplitLeast = 16;
 __device__ __forceinline__ uint32_t split_key(uint32_t pairs, uint32_t share) {
   const uint32_t steps = max(kSplitLeast, pairs / share) >> 3;   // lists of 8 steps entries or more
@@ -435,6 +436,17 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t v) {
          __builtin_amdgcn_readlane(v, 63);
 }
 
+// Maximum over the wave's lanes, by all of them.
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+  v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true)));   // as in wave_or
+  v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true)));
+  v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true)));
+  v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true)));
+  const uint32_t a = __builtin_amdgcn_readlane(v, 15), b = __builtin_amdgcn_readlane(v, 31);
+  const uint32_t c = __builtin_amdgcn_readlane(v, 47), d = __builtin_amdgcn_readlane(v, 63);
+  return max(max(a, b), max(c, d));
+}
+
 // kSparse: the depth sort (see radix_sort_sparse).  kPairs: the pair sort with what follows it, the
 // tiles' ranges (cleared beforehand), launch order and the caller's status.  The output may be the input.
 template <bool kSparse, bool kPairs>
@@ -445,7 +457,7 @@ __global__ __launch_bounds__(kBlockSortThreads) void k_sort_block(const uint32_t
   __shared__ uint32_t s_key[kBlockSort];
   __shared__ uint32_t s_val[kBlockSort];
   __shared__ uint32_t s_cnt[kBlockSortWaves][256];   // per-wave digit counts, then per-wave digit bases
-  __shared__ uint2 s_bits[kBlockSortWaves];
+  __shared__ uint2 s_bits[kBlockSortWaves];          // kSparse: the bits in which keys differ; kPairs: longest list (x)
   int n = static_cast<int>(active_count(n_max, n_dev));
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   uint32_t keys[kBlockSortItems], vals[kBlockSortItems], digit[kBlockSortItems], slot[kBlockSortItems];
@@ -535,6 +547,7 @@ __global__ __launch_bounds__(kBlockSortThreads) void k_sort_block(const uint32_t
     }
     __syncthreads();
     rounds = (tiles + kBlockSortThreads - 1) / kBlockSortThreads;
+    uint32_t longest = 0;
 #pragma unroll
     for (int r = 0; r < kBlockSortItems; ++r) {
       const int i = (w * rounds + r) * 64 + lane;
@@ -543,8 +556,11 @@ __global__ __launch_bounds__(kBlockSortThreads) void k_sort_block(const uint32_t
         const uint2 range = make_uint2(s_key[i], s_val[i]);
         lists.ranges[i] = range;
         digit[r] = length_key(range);
+        longest = max(longest, range.y - range.x);
       }
     }
+    longest = wave_max(longest);
+    if (lane == 0) s_bits[w].x = longest;
     block_places(digit, rounds, s_cnt, slot);
 #pragma unroll
     for (int r = 0; r < kBlockSortItems; ++r)
@@ -554,20 +570,24 @@ __global__ __launch_bounds__(kBlockSortThreads) void k_sort_block(const uint32_t
       const uint32_t pairs = lists.counters[1], most = kMaxSplit;
       lists.counters[kSplitCounter] = min(s_cnt[0][split_key(pairs, lists.split_fwd)], most);
       lists.counters[kSplitCounter + 1] = min(s_cnt[0][split_key(pairs, lists.split_bwd)], most);
+      for (int ww = 1; ww < kBlockSortWaves; ++ww) longest = max(longest, s_bits[ww].x);
+      lists.counters[kLongestCounter] = longest;
       write_status(lists.counters, lists.status);
     }
   }
 }
 
 // Tile order of larger batches: this kernel turns the last sort pass's (~first, last + 1) into ranges (an
-// untouched tile keeps (0, 0)), writes each tile's length key with bit 8 set and their counts, and clears the look-back
-// words of the sparse sort pass that follows; block 0 writes the caller's status.
+// untouched tile keeps (0, 0)), writes each tile's length key with bit 8 set and their counts and the longest list's
+// length, and clears the look-back words of the sparse sort pass that follows; block 0 writes the caller's status.
 __global__ __launch_bounds__(256) void k_tile_keys(TileLists lists, int64_t capacity, int one_tile,
                                                    uint32_t* __restrict__ keys, uint32_t* __restrict__ hist,
                                                    uint32_t* __restrict__ clear, int64_t clear_n) {
   __shared__ uint32_t s_hist[256];
+  __shared__ uint32_t s_longest[4];
   s_hist[threadIdx.x] = 0u;
   __syncthreads();
+  uint32_t longest = 0;
   const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   for (int64_t i = t; i < clear_n; i += static_cast<int64_t>(gridDim.x) * 256) clear[i] = 0u;
   if (t < lists.n_tiles) {
@@ -581,8 +601,13 @@ __global__ __launch_bounds__(256) void k_tile_keys(TileLists lists, int64_t capa
     const uint32_t key = length_key(r);
     keys[t] = key | 256u;
     atomicAdd(&s_hist[key], 1u);
+    longest = r.y - r.x;
   }
+  longest = wave_max(longest);
+  if (lane_id() == 0) s_longest[threadIdx.x >> 6] = longest;
   __syncthreads();
+  if (threadIdx.x == 0)
+    atomicMax(&lists.counters[kLongestCounter], max(max(s_longest[0], s_longest[1]), max(s_longest[2], s_longest[3])));
   if (s_hist[threadIdx.x]) atomicAdd(&hist[threadIdx.x], s_hist[threadIdx.x]);
   if (t == 0) write_status(lists.counters, lists.status);
 }

@@ -469,3 +469,32 @@ def test_dwt_transfer_function_segments(kind, wav):
         return
     ref = odwt.dwt3d_rgba(c, 1, wav)
     assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max()
+
+
+# Lists beyond the 2,040 entries at which the launch order's length steps end: two scenes of one tile each, the longer
+# list second; sorted by one block (room for 8,192 pairs) and by the radix passes.
+@pytest.mark.parametrize("capacity", [8192, 40000])
+@pytest.mark.parametrize("tile", [8, 16])
+def test_lists_beyond_the_length_steps(tile, capacity):
+    api = _api()
+    counts = [2100, 5000]
+    say(f"long lists tile={tile} capacity={capacity}")
+    gs = vi.random_gaussians(sum(counts), 5, log_scale_mean=-1.0, log_scale_std=0.1, opacity_range=(0.004, 0.01))
+    so = np.concatenate([[0], np.cumsum(counts)])
+    cams = vi.orbit_cameras(2, tile, tile, azimuth0=0.4)
+    P = to_dev(gs)
+    rp = api.plan_batch(cams, so, [0, 1], tile=tile, pair_capacity=capacity)
+    out = api.render_fwd(rp, P)
+    lists = rp.region("ranges", torch.int32).cpu().numpy().reshape(-1, 2)
+    lists = lists[:, 1] - lists[:, 0]
+    assert int(out.status[0]) == 0 and lists[0] >= 2040 and lists[1] >= lists[0] + 1000
+    assert int(rp.region("counters", torch.int32)[8]) == lists.max()
+    batch = render.Batch(gs, cams, tile, [0, 1], so)
+    ref = render.render_forward(batch)
+    for v, got in enumerate(api.split_views(out.image, cams)):
+        assert image_error(got.cpu().numpy(), ref[v]["image"], ref[v]["flagged"]) <= IMG_TOL
+    dL = masked_dL(cams, [r["flagged"] for r in ref], seed=tile)
+    g_ref, _ = render.render_backward(batch, dL)
+    G = api.render_bwd(rp, P, flat(dL), out).cpu().numpy()
+    for name, rows in ROWS.items():
+        assert group_error(G[rows], g_ref[name].reshape(rows.stop - rows.start, -1)) <= GRAD_TOL, name
