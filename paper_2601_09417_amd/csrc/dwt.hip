@@ -5,7 +5,7 @@
 // the transfer function applied once per voxel read) and writes the seven detail octants straight into the
 // packed subband layout and LLL into the next level's input.  The three separable filters (x, then y,
 // then z) run inside the block, so nothing between them goes through memory:
-//   bior4.4  a block owns a column of 64 x 16 voxels and marches along z: a plane's tile with its
+//   bior4.4  a block owns a column of 64 x 16 voxels (64 x 4 in small levels) and marches along z: a plane's tile with its
 //            halo goes to LDS, is filtered along x (LDS to LDS) and along y (LDS to registers), and
 //            each thread keeps the running z sums of its eight (x, y) outputs in registers.
 //   Haar     no halo: a thread owns a 2x2x2 cell.
@@ -135,12 +135,9 @@ struct Taps97 {
 };
 
 constexpr int kKX = 32;              // output pairs of a tile along x (64 voxels, one wave's lanes)
-constexpr int kKY = 8;               // output pairs along y
 constexpr int kIX = 2 * kKX + 8;     // tile with halo (2 kKX + 7 voxels, one of padding)
-constexpr int kIY = 2 * kKY + 7;
 constexpr int kXG = 4;               // output pairs per x-filter task (16 inputs, four 16-byte reads)
-constexpr int kYG = 4;               // output pairs per thread along y
-constexpr int kNT = 2 * kKX * 4 * (kKY / kYG);   // a thread per (x output, channel, half of the tile's rows)
+constexpr int kNT = 2 * kKX * 4 * 2;  // a thread per (x output, channel, half of the tile's rows)
 constexpr int kXcds = 8;
 
 // Bounded at level 1 by VALU issue and LDS (per voxel of four channels: a transfer-function value for each of
@@ -150,10 +147,12 @@ constexpr int kXcds = 8;
 // channels through memory three times: 8.83 ms for 512^3, five levels; this kernel takes 1.09 ms
 // (three quarters of it level 1; reading the field and writing the coefficients once is 2.7 GB, 0.52 ms at
 // the rate of a large copy).
-template <Input kInput>
+// kYG: output pairs per thread along y, of which a tile has two threads' worth.
+template <Input kInput, int kYG>
 __global__ __launch_bounds__(kNT) void k_dwt97(const float* __restrict__ in, int64_t in_cs, int n, int zc, int tiles_x,
                                                int tiles_y, int n_blocks, LevelOut out, Taps97 taps, DevTF tf) {
   constexpr bool kWithTF = kInput != kRGBA;
+  constexpr int kKY = 2 * kYG, kIY = 2 * kKY + 7;   // output pairs of the tile, its rows with the halo
   __shared__ __align__(16) float s_in[4][kIY][kIX];
   __shared__ __align__(16) float s_x[4][kIY][2 * kKX];
   __shared__ __align__(16) TfSegment s_tf[kWithTF ? kTfEntries : 1];
@@ -441,12 +440,23 @@ __global__ __launch_bounds__(256) void k_copy(const float* __restrict__ in, floa
     out[i] = in[i];
 }
 
-// z chunk of a bior4.4 block: a chunk re-reads seven planes, so it is as long as still leaves about
-// four blocks per CU; at least two outputs.
-int z_chunk(int h, int64_t tiles) {
-  int zc = 32;
-  while (zc > 2 && tiles * ceil_div(h, zc) < 1024) zc >>= 1;
-  return zc;
+// Tile of a bior4.4 level of h output pairs a side.
+struct Tile97 {
+  int yg, zc;   // output pairs per thread along y, output pairs per block along z
+};
+Tile97 tile97(int h) {
+  // Levels of up to one small tile per CU take as long as a block: planes in turn, each the loads' latency and one
+  // wave's instructions.  Four times fewer of these and the fewest planes count there.  us a level of RGBA, a kernel per
+  // axis / 8 rows, zc 2 / 2 rows, zc 1 / 2 rows, zc 2: 16.1 / 20.2 / 9.7 / 11.4 (side 32), 20.0 / 20.2 / 13.1 / 11.7
+  // (64), 43.4 / 29.8 / 38.8 / 29.2 (96).
+  constexpr int64_t kCUs = 256;
+  for (int zc = 1; zc <= 2; ++zc)
+    if (ceil_div(h, kKX) * ceil_div(h, 2) * ceil_div(h, zc) <= kCUs) return {1, zc};
+  // A chunk re-reads seven planes, so it is as long as still leaves about four blocks per CU; at least two outputs.
+  Tile97 t{4, 32};
+  const int64_t tiles = ceil_div(h, kKX) * ceil_div(h, 2 * t.yg);
+  while (t.zc > 2 && tiles * ceil_div(h, t.zc) < 4 * kCUs) t.zc >>= 1;
+  return t;
 }
 
 }  // namespace
@@ -542,12 +552,17 @@ extern "C" vbm_status vbm_dwt3d(const float* vol, int32_t G, int32_t J, int32_t 
       Taps97 f;
       for (int i = 0; i < 9; ++i) f.lo[i] = static_cast<float>(fb.lo_a.taps[i]);
       for (int i = 0; i < 7; ++i) f.hi[i] = static_cast<float>(fb.hi_a.taps[i]);   // symmetric as rounded, like lo
-      const int tx = static_cast<int>(ceil_div(h, kKX)), ty = static_cast<int>(ceil_div(h, kKY));
-      const int zc = z_chunk(h, static_cast<int64_t>(tx) * ty);
-      const int nb = tx * ty * static_cast<int>(ceil_div(h, zc));
+      const Tile97 t = tile97(h);
+      const int tx = static_cast<int>(ceil_div(h, kKX)), ty = static_cast<int>(ceil_div(h, 2 * t.yg));
+      const int nb = tx * ty * static_cast<int>(ceil_div(h, t.zc));
       const dim3 grid(static_cast<unsigned>(kXcds * ceil_div(nb, kXcds)));
-      const auto kernel = input == kRGBA ? k_dwt97<kRGBA> : input == kTF ? k_dwt97<kTF> : k_dwt97<kTFDivide>;
-      hipLaunchKernelGGL(kernel, grid, dim3(kNT), 0, s, cur, cur_cs, n, zc, tx, ty, nb, out, f, dtf);
+      auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(kNT), 0, s, cur, cur_cs, n, t.zc, tx, ty, nb, out, f, dtf);
+      };
+      if (t.yg == 4)
+        launch(input == kRGBA ? k_dwt97<kRGBA, 4> : input == kTF ? k_dwt97<kTF, 4> : k_dwt97<kTFDivide, 4>);
+      else
+        launch(input == kRGBA ? k_dwt97<kRGBA, 1> : input == kTF ? k_dwt97<kTF, 1> : k_dwt97<kTFDivide, 1>);
     }
     VBM_LAUNCH_CHECK("dwt3d");
     cur = p;

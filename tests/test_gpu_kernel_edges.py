@@ -498,3 +498,11 @@ def test_lists_beyond_the_length_steps(tile, capacity):
     G = api.render_bwd(rp, P, flat(dL), out).cpu().numpy()
     for name, rows in ROWS.items():
         assert group_error(G[rows], g_ref[name].reshape(rows.stop - rows.start, -1)) <= GRAD_TOL, name
+
+
+# The levels that the small tile takes: sides of one and of several of its four rows, with a remainder or none, and of
+# one and two outputs per block along z (30 to 36: one, 46 and 64: two).
+@pytest.mark.parametrize("G,J,with_tf,offset", [(10, 1, True, 0), (30, 1, False, 1), (36, 2, True, 1), (46, 1, True, 0),
+                                                (64, 1, False, 0)])
+def test_dwt_small_levels(G, J, with_tf, offset):
+    test_dwt_tile_edges(G, J, "bior4.4", with_tf, offset)
