@@ -118,9 +118,14 @@ vbm_status radix_sort_sparse(const uint32_t* keys, int64_t n, uint32_t* k0, uint
 //   Backward (its sums over a band cost as much as over a tile): lists of pairs / 2048 entries or more.  us with a wave
 //     per list / this rule / pairs / 4096: 773 / 695 / 882 (8,400 tiles, 3.4M pairs), 210 / 141 / 138 (2,400, 0.6M),
 //     829 / 751 / 887 (12,544, 4.0M), 115 / 69 / 69 (600, 0.1M).
+//     None where that is more than kSplitFew lists and the longest is below pairs / kSplitUneven: most of the pairs are
+//     then shared, and the chip was full without.  us with a wave per list / shared (pairs over the longest list, lists
+//     shared): 134 / 151 (1187, 1089), 247 / 279 (1247, 1089), 214 / 233 (864, 948), 269 / 280 (1322, 608), but
+//     364 / 325 (673, 856), 109 / 74 (677, 890), 167 / 135 (493, 672), 759 / 687 (1806, 107).
 constexpr int kMaxSplit = 20480;        // at most
 constexpr int kSplitAllTiles = 20480;
 constexpr uint32_t kSplitForward = 8192, kSplitBackward = 2048;
+constexpr uint32_t kSplitFew = 256, kSplitUneven = 700;
 constexpr int kSplitCounter = 6;        // their numbers for the forward and the backward, among the forward's counters
 constexpr int kLongestCounter = 8;      // entries of the longest list, among the same
 

@@ -870,9 +870,10 @@ __device__ __forceinline__ void bwd_walk_tile(const BwdTile& t, unsigned char* _
   constexpr int PPL = C::kPPL;
   constexpr bool kCols = 16 % TILE == 0;   // lanes l, l + 16, l + 32, l + 48 share a pixel column
   static_assert(!SUMS || (kCols && LDSB == 0), "sums through LDS: columns in rows of 16, no staged lists");
-  // 16x16 tiles walk the forward's marked copy.  An 8x8 tile has one group, which the projection has found within reach;
-  // where its pixels in reach have stopped, the entry ends at the first test of bwd_step (two views of 256x256 with opacities
-  // of 0.5 and more: 101.7 us with every entry summed, 84.9 us; the same test in shared 16x16 lists 133 -> 144 us).
+  // 16x16 tiles walk the forward's marked copy.  An 8x8 tile has one group, which the projection has found within
+  // reach; where its pixels in reach have stopped, the entry ends at the first test of bwd_step (two views of 256x256
+  // with opacities of 0.5 and more: 101.7 us with every entry summed, 84.9 us; the same test in shared 16x16 lists:
+  // 133 -> 144 us).
   constexpr bool kMarked = TILE == 16;
   const int lane = t.lane;
   BwdPix<PPL> P;

@@ -174,6 +174,10 @@ __device__ __forceinline__ uint32_t split_key(uint32_t pairs, uint32_t share) {
   const uint32_t steps = max(kSplitLeast, pairs / share) >> 3;   // lists of 8 steps entries or more
   return steps > 255u ? 0u : 256u - steps;
 }
+// Of n such lists the number shared in the backward.
+__device__ __forceinline__ uint32_t split_backward(uint32_t n, uint32_t pairs, uint32_t longest) {
+  return n <= kSplitFew || longest >= pairs / kSplitUneven ? n : 0u;
+}
 
 // One stable pass over tiles of NT x I keys.  Wave w of a tile owns keys [64 I w, 64 I (w + 1))
 // and ranks them in I rounds of 64 against its own LDS digit counters: a lane's rank among the
@@ -278,7 +282,8 @@ __global__ __launch_bounds__(NT) void k_radix_onesweep(const uint32_t* __restric
       // tiles with a lower key are split
       const uint32_t n_split = min(below, static_cast<uint32_t>(kMaxSplit));
       if (threadIdx.x == split_key(counters[1], lists.split_fwd)) counters[kSplitCounter] = n_split;
-      if (threadIdx.x == split_key(counters[1], lists.split_bwd)) counters[kSplitCounter + 1] = n_split;
+      if (threadIdx.x == split_key(counters[1], lists.split_bwd))
+        counters[kSplitCounter + 1] = split_backward(n_split, counters[1], counters[kLongestCounter]);
     }
     if (has) {
       uint32_t* mine = status + tile * radix + threadIdx.x;
@@ -568,10 +573,11 @@ __global__ __launch_bounds__(kBlockSortThreads) void k_sort_block(const uint32_t
     if (threadIdx.x == 0) {
       // the first wave's base of a length key is the key's: the tiles with a lower one
       const uint32_t pairs = lists.counters[1], most = kMaxSplit;
-      lists.counters[kSplitCounter] = min(s_cnt[0][split_key(pairs, lists.split_fwd)], most);
-      lists.counters[kSplitCounter + 1] = min(s_cnt[0][split_key(pairs, lists.split_bwd)], most);
       for (int ww = 1; ww < kBlockSortWaves; ++ww) longest = max(longest, s_bits[ww].x);
       lists.counters[kLongestCounter] = longest;
+      lists.counters[kSplitCounter] = min(s_cnt[0][split_key(pairs, lists.split_fwd)], most);
+      lists.counters[kSplitCounter + 1] =
+          split_backward(min(s_cnt[0][split_key(pairs, lists.split_bwd)], most), pairs, longest);
       write_status(lists.counters, lists.status);
     }
   }

@@ -506,3 +506,35 @@ def test_lists_beyond_the_length_steps(tile, capacity):
                                                 (64, 1, False, 0)])
 def test_dwt_small_levels(G, J, with_tf, offset):
     test_dwt_tile_edges(G, J, "bior4.4", with_tf, offset)
+
+
+# The lists that four waves share in the backward: some of an uneven batch's (a view with a dense middle), none of a batch
+# whose longest list is a small share of its pairs and that has many of that length.  Either way the gradient is that of
+# the views alone.
+@pytest.mark.parametrize("n,views,W,H,log_scale,shared",
+                         [(1500, 2, 480, 360, -2.2, True), (300, 6, 480, 320, -1.0, False)])
+def test_backward_shares_lists_of_uneven_batches(n, views, W, H, log_scale, shared):
+    api = _api()
+    say(f"shared lists n={n} {views} views {W}x{H} log scale {log_scale}")
+    gs = vi.random_gaussians(n, 41 + n, log_scale_mean=log_scale, opacity_range=(0.02, 0.3))
+    cams = vi.orbit_cameras(views, W, H)
+    P = to_dev(gs)
+    dL = torch.from_numpy(np.random.default_rng(n).normal(size=views * 3 * W * H).astype(np.float32)).to(dev())
+
+    def grad(batch, dl, tile):
+        rp = api.plan_batch(batch, [0, n], tile=tile, pair_capacity=1 << 22)
+        out = api.render_fwd(rp, P)
+        lists = rp.region("ranges", torch.int32).cpu().numpy().reshape(-1, 2)
+        lists = lists[:, 1] - lists[:, 0]
+        split, longest = rp.region("counters", torch.int32)[7:9].tolist()
+        assert longest == lists.max()
+        many = np.count_nonzero(lists >> 3 >= max(16, lists.sum() // 2048) >> 3)
+        if tile == 16:
+            assert split == (many if many <= 256 or longest >= lists.sum() // 700 else 0)
+        return split, api.render_bwd(rp, P, dl.contiguous(), out).cpu().numpy().astype(np.float64)
+
+    split, G = grad(cams, dL, 16)
+    assert (split > 256) == shared and (split == 0) == (not shared)
+    ref = sum(grad(cams[v:v + 1], dL[3 * W * H * v:3 * W * H * (v + 1)], 32)[1] for v in range(views))
+    for name, rows in ROWS.items():
+        assert group_error(G[rows], ref[rows]) <= GRAD_TOL, name
