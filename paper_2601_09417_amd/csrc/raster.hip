@@ -238,8 +238,10 @@ __device__ __forceinline__ bool any_live(const float (&fy)[PPL]) {
 // alpha = min(0.99, 2^e2); a pixel takes the Gaussian when alpha >= 1/255, unless the new
 // transmittance would fall below 1e-4, in which case the pixel stops without it and records pos as
 // the number of list entries its compositing took into account.  Only the lane groups in `reach`
-// (uniform, every group with a pixel that passes the alpha test among them) are looked at.
-template <int PPL, bool STATS>
+// (uniform, every group with a pixel that passes the alpha test among them) are looked at.  REACH: they are the groups
+// that the footprint can reach; else (32x32 tiles mark every group) a group that it does not reach ends before the
+// exponential (200,000 faint Gaussians at 512x512: 1567 us without the test, 1431 us).
+template <int PPL, bool REACH, bool STATS>
 __device__ __forceinline__ void fwd_step(const Rec& r, uint32_t reach, int pos, float fx, float (&fy)[PPL],
                                          float (&T)[PPL], float (&cr)[PPL], float (&cg)[PPL], float (&cb)[PPL],
                                          int (&nvis)[PPL], uint32_t& n_used) {
@@ -251,7 +253,9 @@ __device__ __forceinline__ void fwd_step(const Rec& r, uint32_t reach, int pos, 
     // a group out of the footprint's reach: nothing to evaluate (a scalar bit test)
     if (!((reach >> k) & 1u)) continue;
     const float dy = r.my - fy[k];
-    const float alpha = fminf(kAlphaMax, __builtin_amdgcn_exp2f(exponent2(r, u, vb, dy)));
+    const float e2 = exponent2(r, u, vb, dy);
+    if (!REACH && !wave_any(e2 >= kE2Skip)) continue;
+    const float alpha = fminf(kAlphaMax, __builtin_amdgcn_exp2f(e2));
     const bool ok = alpha >= kAlphaMin;
     if (ok) {   // (with selects instead of the lanes masked off: 1.62 against 1.56 ms, 27M pairs at 1080p)
       float w = alpha * T[k];
@@ -602,7 +606,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) __attribute__((amdgpu_wave
       for (int b = 0; b < n; ++b) {
         const Rec r = lds_get<kFwdBatch>(L, buf, b);
         const uint32_t reach = lds_pv<kFwdBatch>(L, buf, b) >> kItemBits;
-        fwd_step<PPL, STATS>(r, reach, pos0 + b, fx, fy, T, cr, cg, cb, nvis, n_used);
+        fwd_step<PPL, kMark, STATS>(r, reach, pos0 + b, fx, fy, T, cr, cg, cb, nvis, n_used);
       }
       buf ^= 1;
       stage(buf, nb);
