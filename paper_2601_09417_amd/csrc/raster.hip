@@ -427,21 +427,23 @@ __device__ __forceinline__ void fwd_walk_pixels(LdsList& L, const uint32_t* __re
       }
       if (wave_any(T < kTMin)) {
         __asm__ volatile("" ::: "memory");   // keeps this a branch
-        T = T0;
+        // the pixels that stop here, again one entry after the other (one that has stopped before may have a T one unit in
+        // the last place below the threshold)
+        if (T < kTMin && fy < kLiveBound) {
+          T = T0;
+          bool go = true;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          w[k] = 0.0f;
-          if (fy < kLiveBound) {   // a stopped pixel's T may lie one unit in the last place below the threshold
-            const float wk = alpha[k] * T;
-            T = attenuate(T, alpha[k]);
-            if (T < kTMin) {
-              T = T + wk;
-              fy = kDeadRow;
-              nvis = __float_as_int(L.c[i + k].y);
-            } else {
-              w[k] = wk;
-            }
+          for (int k = 0; k < 4; ++k) {
+            const float a = go ? alpha[k] : 0.0f;
+            w[k] = a * T;
+            T = attenuate(T, a);
+            const bool stop = go && T < kTMin;
+            T = stop ? T + w[k] : T;
+            w[k] = stop ? 0.0f : w[k];
+            nvis = stop ? __float_as_int(L.c[i + k].y) : nvis;
+            go = go && !stop;
           }
+          fy = kDeadRow;
         }
       }
 #pragma unroll
