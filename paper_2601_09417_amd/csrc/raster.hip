@@ -225,6 +225,11 @@ constexpr float kLiveBound = 1e29f;
 // Transmittance behind a Gaussian: T - alpha T in one rounding, written out so that every walk takes the
 // same one.
 __device__ __forceinline__ float attenuate(float T, float alpha) { return fmaf(-T, alpha, T); }
+// And back to the T before a Gaussian whose weight is w, never as one multiply-add with w's product.
+__device__ __forceinline__ float restore(float T, float w) {
+#pragma clang fp contract(off)
+  return T + w;
+}
 
 template <int PPL>
 __device__ __forceinline__ bool any_live(const float (&fy)[PPL]) {
@@ -266,7 +271,7 @@ __device__ __forceinline__ void fwd_step(const Rec& r, uint32_t reach, int pos, 
       if (wave_any(T[k] < kTMin)) {
         __asm__ volatile("" ::: "memory");   // keeps this a branch: the compiler would select both ways
         const bool stop = T[k] < kTMin;
-        T[k] = stop ? T[k] + w : T[k];
+        T[k] = stop ? restore(T[k], w) : T[k];
         w = stop ? 0.0f : w;
         fy[k] = stop ? kDeadRow : fy[k];
         nvis[k] = stop ? pos : nvis[k];
@@ -438,7 +443,7 @@ __device__ __forceinline__ void fwd_walk_pixels(LdsList& L, const uint32_t* __re
             w[k] = a * T;
             T = attenuate(T, a);
             const bool stop = go && T < kTMin;
-            T = stop ? T + w[k] : T;
+            T = stop ? restore(T, w[k]) : T;
             w[k] = stop ? 0.0f : w[k];
             nvis = stop ? __float_as_int(L.c[i + k].y) : nvis;
             go = go && !stop;

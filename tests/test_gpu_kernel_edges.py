@@ -538,3 +538,17 @@ def test_backward_shares_lists_of_uneven_batches(n, views, W, H, log_scale, shar
     ref = sum(grad(cams[v:v + 1], dL[3 * W * H * v:3 * W * H * (v + 1)], 32)[1] for v in range(views))
     for name, rows in ROWS.items():
         assert group_error(G[rows], ref[rows]) <= GRAD_TOL, name
+
+
+def test_walks_leave_the_same_transmittance():
+    """Pixels that stop go back to the transmittance before the entry that stopped them; the walks of 8x8, shared 16x16
+    and 32x32 tiles leave the same value and image bit for bit (opacities up to 0.34: the tilings list the same)."""
+    api = _api()
+    say("walks leave the same transmittance")
+    gs = vi.random_gaussians(20000, 5, log_scale_mean=-2.6, opacity_range=(0.05, 0.34))
+    cams = vi.orbit_cameras(2, 131, 77)
+    P = to_dev(gs)
+    outs = [api.render_fwd(api.plan_batch(cams, [0, gs.n], tile=t, pair_capacity=1 << 19), P) for t in (8, 16, 32)]
+    assert int((outs[0].final_T < 1.2e-4).sum()) > 1000      # many have stopped
+    for o in outs[1:]:
+        assert torch.equal(o.final_T, outs[0].final_T) and torch.equal(o.image, outs[0].image)
