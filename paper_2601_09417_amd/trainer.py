@@ -229,7 +229,8 @@ def render_images(P: torch.Tensor, cams, scene_offsets=None, view_scene=None, ti
 
 # (tile edge, tile-sort digit width, LDS batch depth of the forward and of the backward compositing
 # list walk; 0 = scalar cache, in the backward only: the forward stages its lists in LDS whatever the
-# value), in order of preference: the tuner keeps the first one within TUNE_MARGIN of the fastest
+# value, so candidates that differ in it alone are one schedule, timed once), in order of preference:
+# the tuner keeps the first one within TUNE_MARGIN of the fastest
 TUNE_CANDIDATES = ((16, 8, 0, 0), (16, 4, 0, 0), (8, 8, 0, 0), (32, 8, 0, 0), (16, 8, 32, 0), (16, 8, 64, 0),
                    (16, 8, 32, 32))
 TUNE_MARGIN = 0.01
@@ -266,22 +267,27 @@ def autotune(P: torch.Tensor, cams, targets: torch.Tensor, scene_offsets=None, v
     """Chooses the tile edge, the radix digit width of the tile sort and the LDS batch depth of the
     compositing list walk for a batch.
 
-    Each candidate (tile, sort_bits, lds_batch, lds_batch_bwd) gets its own plan (exact pair counts, capacity
-    margin) and runs ``warmup`` + ``steps`` eager batched iterations on a copy of P (FineTuner
+    Each schedule among the candidates (tile, sort_bits, lds_batch, lds_batch_bwd) gets its own plan (exact pair
+    counts, capacity margin) and runs ``warmup`` + ``steps`` eager batched iterations on a copy of P (FineTuner
     clones it), timed with a device synchronisation on both sides.  The pick is the first candidate,
     in the given order of preference, whose time is within ``margin`` (a fraction) of the fastest,
     so that differences at the level of timing noise do not change the schedule from run to run.
     Returns it as dict(tile, sort_bits, lds_batch, lds_batch_bwd, ms) plus the table of every
     candidate's ms per step.
     """
-    table = []
+    table, timed = [], {}
     for cand in candidates:
         tile, bits, lds, lds_bwd = (tuple(cand) + (0, 0))[:4]
-        ft = FineTuner(P, cams, targets, scene_offsets, view_scene, tile=tile, sort_bits=bits, lds_batch=lds,
-                       lds_batch_bwd=lds_bwd, loss=loss, lam=lam, schedule="batched")
-        table.append(dict(tile=tile, sort_bits=bits, lds_batch=lds, lds_batch_bwd=lds_bwd,
-                          ms=_time_steps(ft, steps, warmup)))
-        del ft
+        key = (tile, bits, lds_bwd)      # what the step depends on
+        # The first series of a process comes out a few percent slower than the same one later (eight 1080p views: 3.65
+        # against 3.56 ms), more than the margin: it is run again, the plan included, as the others are run.
+        for _ in range(0 if key in timed else 1 if timed else 2):
+            ft = FineTuner(P, cams, targets, scene_offsets, view_scene, tile=tile, sort_bits=bits, lds_batch=lds,
+                           lds_batch_bwd=lds_bwd, loss=loss, lam=lam, schedule="batched")
+            ms = _time_steps(ft, steps, warmup)
+            del ft
+        timed.setdefault(key, ms)
+        table.append(dict(tile=tile, sort_bits=bits, lds_batch=lds, lds_batch_bwd=lds_bwd, ms=timed[key]))
     fastest = min(d["ms"] for d in table)
     best = next(d for d in table if d["ms"] <= fastest * (1.0 + margin))
     return dict(tile=best["tile"], sort_bits=best["sort_bits"], lds_batch=best["lds_batch"],
