@@ -240,8 +240,8 @@ typedef struct {
   int32_t sort_bits;     /* radix digit width for the tile sort: 4..8 */
   int64_t pair_capacity; /* pair slots reserved in the workspace, in [1, 2^30) */
   int32_t mode;          /* VBM_MODE_BATCHED or VBM_MODE_EXACT */
-  int32_t lds_batch;     /* 0, or 32 or 64 with 8x8 or 16x16 tiles: the forward compositing stages its
-                          * lists in LDS whatever the value (it once chose between walks) */
+  int32_t lds_batch;     /* 0, or 32 or 64 with 8x8 or 16x16 tiles.  Not used: the forward compositing
+                          * stages its lists in LDS in batches of its own size */
   int32_t lds_batch_bwd; /* record staging of the backward compositing: 0 = each record through the
                           * scalar cache into registers; 32 or 64 = the tile's list staged in LDS
                           * batches of that many entries (8x8 and 16x16 tiles only).  Results are

@@ -65,6 +65,10 @@ struct DevScene {
   int32_t gauss_offset, n_gauss;
 };
 
+// ------------------------------------------------------------------ limits
+constexpr int kMaxViewSide = 16384;                                             // pixels; checked by the plan
+constexpr int64_t kMaxRectTiles = int64_t{kMaxViewSide / 8} * (kMaxViewSide / 8);   // of a footprint, with 8x8 tiles
+
 // ------------------------------------------------------------------ pair values
 // A pair value holds the item id in bits 0..26 (the plan keeps items below 2^27) and a 4-bit mask
 // of the tile's lane groups in bits 27..30.  With 16x16 tiles lane group k is pixel rows
@@ -143,7 +147,7 @@ struct TileLists {
 // read from *n_dev when non-null, and is at most n_max), and writes the tiles' ranges (cleared beforehand),
 // launch order and the status (scratch: radix_scratch_bytes of n_max and of the tiles).  The kTileOrderCounts words at
 // tile_order_counts() are cleared beforehand.
-constexpr int kTileOrderCounts = 2 * 256;
+constexpr int kTileOrderCounts = 256;
 inline uint32_t* tile_order_counts(void* scratch) { return static_cast<uint32_t*>(scratch); }
 int sort_pairs_first(int64_t n_max, int64_t n_tiles, int end_bit, int digit_bits);
 vbm_status sort_pairs_by_tile(uint32_t* const k[2], uint32_t* const v[2], int first, int64_t capacity, int64_t n_max,

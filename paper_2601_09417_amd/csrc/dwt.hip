@@ -5,9 +5,9 @@
 // the transfer function applied once per voxel read) and writes the seven detail octants straight into the
 // packed subband layout and LLL into the next level's input.  The three separable filters (x, then y,
 // then z) run inside the block, so nothing between them goes through memory:
-//   bior4.4  a block owns a column of 64 x 16 voxels (64 x 4 in small levels) and marches along z: a plane's tile with its
-//            halo goes to LDS, is filtered along x (LDS to LDS) and along y (LDS to registers), and
-//            each thread keeps the running z sums of its eight (x, y) outputs in registers.
+//   bior4.4  a block owns a column of 64 x 16 voxels (64 x 4 in small levels) and marches along z: a
+//            plane's tile with its halo goes to LDS, is filtered along x (LDS to LDS) and along y (LDS
+//            to registers), and each thread keeps the running z sums of its (x, y) outputs in registers.
 //   Haar     no halo: a thread owns a 2x2x2 cell.
 #include <hip/hip_runtime.h>
 
@@ -446,9 +446,9 @@ struct Tile97 {
 };
 Tile97 tile97(int h) {
   // Levels of up to one small tile per CU take as long as a block: planes in turn, each the loads' latency and one
-  // wave's instructions.  Four times fewer of these and the fewest planes count there.  us a level of RGBA, a kernel per
-  // axis / 8 rows, zc 2 / 2 rows, zc 1 / 2 rows, zc 2: 16.1 / 20.2 / 9.7 / 11.4 (side 32), 20.0 / 20.2 / 13.1 / 11.7
-  // (64), 43.4 / 29.8 / 38.8 / 29.2 (96).
+  // wave's instructions.  Few of these and few planes count there.  us a level of RGBA with a kernel per axis / yg 4,
+  // zc 2 / yg 1, zc 1 / yg 1, zc 2: 16.1 / 20.2 / 9.7 / 11.4 (side 32), 20.0 / 20.2 / 13.1 / 11.7 (64), 43.4 / 29.8 /
+  // 38.8 / 29.2 (96).
   constexpr int64_t kCUs = 256;
   for (int zc = 1; zc <= 2; ++zc)
     if (ceil_div(h, kKX) * ceil_div(h, 2) * ceil_div(h, zc) <= kCUs) return {1, zc};

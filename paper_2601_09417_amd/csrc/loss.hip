@@ -474,7 +474,7 @@ extern "C" size_t vbm_image_loss_workspace_size(const int32_t* dims, int32_t n_v
     px += W * H;
     blocks += ceil_div(W, TX) * ceil_div(H, TY) * 3;
   }
-  constexpr size_t red = 4096;   // not used since the loss is formed by one block; callers know the size
+  constexpr size_t red = 4096;   // not used, but part of the size against which vbm_image_loss_static has its limit
   if (kind == 0) return align_up(kL1Blocks * 4, 256) + red;
   return 3 * align_up(3 * px * 4, 256) + 2 * align_up(blocks * 4, 256) + red;
 }
@@ -602,8 +602,8 @@ extern "C" vbm_status vbm_image_loss_static(const float* image, const float* tar
   }
   void* ws = static_scratch_ptr();
   if (!ws) return VBM_ERR_HIP;
-  // The passes write every scratch value before they read it (maps, per-block partial sums, the
-  // reduction stage), so nothing is cleared first.
+  // The passes write every scratch value before they read it (maps, per-block partial sums), so nothing is cleared
+  // first.
   return vbm_image_loss(image, target, dims, n_views, kind, lambda, grad, loss, ws,
                         static_cast<size_t>(VBM_IMAGE_LOSS_STATIC_SCRATCH_BYTES), stream);
 }

@@ -493,7 +493,8 @@ __global__ __launch_bounds__(256) void k_emit(const DevView* __restrict__ views,
   const uint32_t x0 = b.x & 0xFFFFu, x1 = b.x >> 16, y0 = b.y & 0xFFFu, y1 = (b.y >> 16) & 0xFFFu;
   const uint32_t w = x1 - x0, h = y1 - y0;
   const bool small = w * h <= kSmallRect;
-  // pairs of every rectangle (low half, at most 256 x 2^20) and of the small ones
+  // pairs of every rectangle (low half, at most 2^30) and of the small ones
+  static_assert(256 * kMaxRectTiles < int64_t{1} << 32, "a block's pairs fit the low half");
   unsigned long long both;
   const unsigned long long before_me =
       block_excl_scan(b.w | (small ? static_cast<unsigned long long>(b.w) << 32 : 0ull), &both);

@@ -432,8 +432,8 @@ __device__ __forceinline__ void fwd_walk_pixels(LdsList& L, const uint32_t* __re
       }
       if (wave_any(T < kTMin)) {
         __asm__ volatile("" ::: "memory");   // keeps this a branch
-        // the pixels that stop here, again one entry after the other (one that has stopped before may have a T one unit in
-        // the last place below the threshold)
+        // the pixels that stop here, again one entry after the other (one that has stopped before may have a T one unit
+        // in the last place below the threshold)
         if (T < kTMin && fy < kLiveBound) {
           T = T0;
           bool go = true;

@@ -52,7 +52,8 @@ enum Region {
   R_SORTKEY = 18,   // uint32 [n_items]: depth bits of the visible items, 0 for the others
   R_COEF = VBM_REGION_ITEM_COEF,
   R_UNUSED20 = 20,
-  R_TORDER = 21,   // uint32 [4][n_tiles]: sort keys, sorted keys, (unused), the tiles in launch order
+  R_TORDER = 21,   // uint32 [4][n_tiles]: sort keys, sorted keys, nothing, the tiles in launch order (readers of the
+                   // workspace find the order in the last quarter and both regions by number, so the gaps stay)
   R_WORDS = 22,    // uint64 [ballot_words(n_items)]: large rectangles' reached-tile ballots
   R_COUNT = 23
 };
@@ -253,7 +254,7 @@ extern "C" vbm_status vbm_plan_make(const vbm_view* views, int32_t n_views, cons
       set_error("vbm_plan_make: view %d references scene %d of %d", v, in.scene, n_scenes);
       return VBM_ERR_INVALID;
     }
-    if (in.width < 1 || in.height < 1 || in.width > 16384 || in.height > 16384) {
+    if (in.width < 1 || in.height < 1 || in.width > kMaxViewSide || in.height > kMaxViewSide) {
       set_error("vbm_plan_make: view %d has size %dx%d", v, in.width, in.height);
       return VBM_ERR_INVALID;
     }

@@ -1,4 +1,5 @@
-// Stable LSD radix sort (gfx950, wave64, 256-thread blocks).
+// Stable LSD radix sorts (gfx950, wave64): one-sweep passes of 512-thread blocks, and one block of 1024 for few
+// elements.
 //
 // One histogram kernel counts the digits of every pass in one read of the
 // keys, then each pass is a single kernel over tiles of 8192 keys (4096 or 2048 for few keys) that ranks equal digits
@@ -17,10 +18,8 @@ namespace vbm {
 
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kItems = 16;
-constexpr int kChunk = kThreads * kItems;  // elements per block
-static_assert(kThreads == 256, "one thread per 8-bit digit in the scatter's LDS bookkeeping");
+constexpr int kItems = 16;            // keys per thread of a pass over many keys
+constexpr int kChunk = 256 * kItems;  // keys of a histogram block's step and of the smallest depth or pair tile
 
 __device__ __forceinline__ bool aligned16(const void* p) {
   return (reinterpret_cast<uintptr_t>(p) & 15u) == 0;
@@ -633,7 +632,7 @@ namespace {
 // Scratch of one sort: a head of kRadixHead bytes that the sort leaves alone (the renderer keeps the tile-order
 // counts there), digit totals, then the look-back status words of every pass, which the histogram kernel clears.
 struct RadixLayout {
-  int64_t nb;        // 4096-key tiles (status words are sized for them, twice what a pass uses)
+  int64_t nb;        // 4096-key tiles (status words are sized for them, twice what a pass over tiles of 8192 uses)
   int passes_max;    // passes of a 32-bit key
   int radix;         // 1 << digit width
   int G;             // histogram blocks
